@@ -33,15 +33,17 @@ __host__ __device__ inline double mass2_of(uint8_t t) {
 // a position inside the grid (what the push may start from)
 template <class T>
 __device__ inline bool in_grid(const Grid& g, int i1, T dx1, int i2, T dx2) {
-  return i1 >= 0 && i1 < g.n_r && i2 >= 0 && i2 < g.n_th && dx1 >= (T)0 && dx1 <= (T)1 &&
-         dx2 >= (T)0 && dx2 <= (T)1;
+  // (no short-circuit: a branch per term would make each array's load wait
+  // for the one before it)
+  return (i1 >= 0) & (i1 < g.n_r) & (i2 >= 0) & (i2 < g.n_th) & (dx1 >= (T)0) & (dx1 <= (T)1) &
+         (dx2 >= (T)0) & (dx2 <= (T)1);
 }
 
 // a position the deposit may write around: one cell beyond the radial edges
 template <class T>
 __device__ inline bool in_deposit_range(const Grid& g, int i1, T dx1, int i2, T dx2) {
-  return i1 >= -1 && i1 <= g.n_r && i2 >= 0 && i2 < g.n_th && dx1 >= (T)0 && dx1 <= (T)1 &&
-         dx2 >= (T)0 && dx2 <= (T)1;
+  return (i1 >= -1) & (i1 <= g.n_r) & (i2 >= 0) & (i2 < g.n_th) & (dx1 >= (T)0) & (dx1 <= (T)1) &
+         (dx2 >= (T)0) & (dx2 <= (T)1);
 }
 
 template <class T>
@@ -412,6 +414,36 @@ __device__ inline int cell_key(const Grid& g, uint8_t t, int i1, int i2) {
   return i1 * g.n_th + i2;
 }
 
+// The state a push starts from, its eight loads issued together: behind a
+// branch on the tag, and one per term of the bounds check, they would be five
+// memory latencies one after the other in every wavefront (ten steps and a
+// sort: 4096^2 with 16 per cell in single precision 141.1 -> 132.1 ms, 1024^2
+// with 90 per cell in double precision 81.7 -> 76.6 ms).
+template <class T>
+struct StateT {
+  uint8_t t;
+  int i1, i2;
+  T dx1, dx2, u1, u2, u3;
+};
+
+template <class T>
+__device__ inline StateT<T> load_state(const ParticleArraysT<T>& P, int64_t k) {
+  StateT<T> s;
+  s.t = P.tag[k];
+  s.i1 = P.i1[k];
+  s.i2 = P.i2[k];
+  s.dx1 = P.dx1[k];
+  s.dx2 = P.dx2[k];
+  s.u1 = P.u1[k];
+  s.u2 = P.u2[k];
+  s.u3 = P.u3[k];
+  // (the empty asm keeps the compiler from moving a load down to its first use)
+  uint32_t t = s.t;
+  asm volatile("" : "+v"(t), "+v"(s.i1), "+v"(s.i2), "+v"(s.dx1), "+v"(s.dx2), "+v"(s.u1), "+v"(s.u2), "+v"(s.u3));
+  s.t = (uint8_t)t;
+  return s;
+}
+
 // What the deposit needs from one particle's move (Sec. 3.2).
 template <class T>
 struct Move {
@@ -434,19 +466,20 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   mv.dep = false;
   mv.cell = g.n_r * g.n_th;
   if (k >= P.n) return mv;
-  uint8_t t = P.tag[k];
+  const StateT<double> st = load_state(P, k);
+  uint8_t t = st.t;
   if (!is_live(t)) return mv;
   if (t & kLeaving) {
     P.tag[k] = 0;
     return mv;
   }
-  int i1 = P.i1[k], i2 = P.i2[k];
-  double dx1 = P.dx1[k], dx2 = P.dx2[k];
+  int i1 = st.i1, i2 = st.i2;
+  double dx1 = st.dx1, dx2 = st.dx2;
   if (!in_grid(g, i1, dx1, i2, dx2)) {  // corrupt input: drop, never index with it
     P.tag[k] = kInvalid;
     return mv;
   }
-  double u1 = P.u1[k], u2 = P.u2[k], u3 = P.u3[k];
+  double u1 = st.u1, u2 = st.u2, u3 = st.u3;
   if (kPrev) {  // the previous position, for a separate deposit
     P.i1p[k] = i1;
     P.i2p[k] = i2;
@@ -570,19 +603,20 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
   mv.dep = false;
   mv.cell = g.n_r * g.n_th;
   if (k >= P.n) return mv;
-  uint8_t t = P.tag[k];
+  const StateT<float> st = load_state(P, k);
+  uint8_t t = st.t;
   if (!is_live(t)) return mv;
   if (t & kLeaving) {
     P.tag[k] = 0;
     return mv;
   }
-  int i1 = P.i1[k], i2 = P.i2[k];
-  float dx1 = P.dx1[k], dx2 = P.dx2[k];
+  int i1 = st.i1, i2 = st.i2;
+  float dx1 = st.dx1, dx2 = st.dx2;
   if (!in_grid(g, i1, dx1, i2, dx2)) {
     P.tag[k] = kInvalid;
     return mv;
   }
-  float u1 = P.u1[k], u2 = P.u2[k], u3 = P.u3[k];
+  float u1 = st.u1, u2 = st.u2, u3 = st.u3;
   if (kPrev) {  // the previous position, for a separate deposit
     P.i1p[k] = i1;
     P.i2p[k] = i2;
