@@ -70,10 +70,10 @@ template <int N>
 __device__ inline FrameT<double> value_of(const FrameT<Tan<N>>& f) {
   FrameT<double> o;
   o.c = CoeffsT<double>{f.c.alpha.v, f.c.beta1.v, f.c.hu11.v, f.c.hu22.v, f.c.hu33.v, f.c.hu13.v};
-  o.s11 = f.s11.v;
+  o.is11 = f.is11.v;
   o.s22 = f.s22.v;
   o.s33 = f.s33.v;
-  o.k13 = f.k13.v;
+  o.is33 = f.is33.v;
   return o;
 }
 
@@ -84,11 +84,11 @@ __device__ inline GradT<double> value_of(const GradT<Tan<N>>& d) {
   for (int q = 0; q < 2; ++q) {
     o.alpha[q] = d.alpha[q].v;
     o.beta1[q] = d.beta1[q].v;
-    o.hu11[q] = d.hu11[q].v;
-    o.hu22[q] = d.hu22[q].v;
-    o.hu33[q] = d.hu33[q].v;
-    o.hu13[q] = d.hu13[q].v;
+    o.l11[q] = d.l11[q].v;
+    o.z[q] = d.z[q].v;
   }
+  o.ct = d.ct.v;
+  o.tt = d.tt.v;
   return o;
 }
 
@@ -99,11 +99,11 @@ __device__ inline GradT<R> lift(const GradT<double>& d) {
   for (int q = 0; q < 2; ++q) {
     o.alpha[q] = R(d.alpha[q]);
     o.beta1[q] = R(d.beta1[q]);
-    o.hu11[q] = R(d.hu11[q]);
-    o.hu22[q] = R(d.hu22[q]);
-    o.hu33[q] = R(d.hu33[q]);
-    o.hu13[q] = R(d.hu13[q]);
+    o.l11[q] = R(d.l11[q]);
+    o.z[q] = R(d.z[q]);
   }
+  o.ct = R(d.ct);
+  o.tt = R(d.tt);
   return o;
 }
 
@@ -111,19 +111,18 @@ __device__ inline GradT<R> lift(const GradT<double>& d) {
 // momentum (b1, b2, u3): f_i = -gamma d_i alpha + b1 d_i beta^1
 // - alpha / (2 gamma) d_i h^jk b_j b_k, i = 1, 2.
 template <class R>
-__device__ inline void geo_force(const CoeffsT<R>& m, const GradT<R>& d, const R& b1, const R& b2,
+__device__ inline void geo_force(const Grid& g, const CoeffsT<R>& m, const GradT<R>& d, const R& b1, const R& b2,
                                  const R& u3, R fr[2], double mass2) {
-  const R Q = R(mass2) + m.hu11 * b1 * b1 + m.hu22 * b2 * b2 + m.hu33 * u3 * u3 +
-              R(2.0) * m.hu13 * b1 * u3;
+  const R t11 = m.hu11 * b1 * b1, t22 = m.hu22 * b2 * b2, t13 = R(2.0) * m.hu13 * b1 * u3, t33 = m.hu33 * u3 * u3;
+  const R W = t22 + t13 + t33;
+  const R Q = R(mass2) + t11 + W;
   const R ig = rsqrt(Q);
   const R gb = Q * ig;
   const R h = R(0.5) * m.alpha * ig;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const R q = d.hu11[i] * b1 * b1 + d.hu22[i] * b2 * b2 + d.hu33[i] * u3 * u3 +
-                R(2.0) * d.hu13[i] * b1 * u3;
-    fr[i] = -(gb * d.alpha[i]) + b1 * d.beta1[i] - h * q;
-  }
+  const R q1 = d.l11[0] * t11 - d.z[0] * W - R(g.dxi) * t13;
+  const R q2 = d.l11[1] * t11 - d.z[1] * W - d.ct * t33 - d.tt * t22;
+  fr[0] = b1 * d.beta1[0] - gb * d.alpha[0] - h * q1;
+  fr[1] = b1 * d.beta1[1] - gb * d.alpha[1] - h * q2;
 }
 
 // coordinate velocity (v1, v2) = alpha h^ij u_j / gamma - beta^i
@@ -206,12 +205,13 @@ __device__ inline void adjoint_one(const Grid& g, const GatherPlanesT<double>& f
     const T6 B2 = interp_tan<1, 0>(g, fp.B[1], i1, dx1, i2, dx2, inv_B0);
     const T6 B3 = interp_tan<1, 1>(g, fp.B[2], i1, dx1, i2, dx2, inv_B0);
     const T6 al = f.c.alpha;
-    E[0] = al * D1 / f.s11;
+    const T6 k13 = f.c.hu13 * f.is11 * f.is11;
+    E[0] = al * f.is11 * D1;
     E[1] = al * f.s22 * D2;
-    E[2] = al * f.s33 * (f.k13 * D1 + D3);
-    B[0] = al * B1 / f.s11;
+    E[2] = al * f.s33 * (D3 - k13 * D1);
+    B[0] = al * f.is11 * B1;
     B[1] = al * f.s22 * B2;
-    B[2] = al * f.s33 * (f.k13 * B1 + B3);
+    B[2] = al * f.s33 * (B3 - k13 * B1);
     em_half(f, E, B, T6(0.25 * qm * g.dt), u1, u2, u3);
   }
 
@@ -224,7 +224,7 @@ __device__ inline void adjoint_one(const Grid& g, const GatherPlanesT<double>& f
     bool converged = false;
     for (int it = 0; it < g.n_iter; ++it) {
       double fr[2];
-      geo_force(fv.c, dv, 0.5 * (s1 + z1), 0.5 * (s2 + z2), w3, fr, ms);
+      geo_force(g, fv.c, dv, 0.5 * (s1 + z1), 0.5 * (s2 + z2), w3, fr, ms);
       const double n1 = s1 + g.dt * fr[0], n2 = s2 + g.dt * fr[1];
       converged = n1 == z1 && n2 == z2;
       z1 = n1;
@@ -236,7 +236,7 @@ __device__ inline void adjoint_one(const Grid& g, const GatherPlanesT<double>& f
       T6 t1 = u1, t2 = u2;
       for (int it = 0; it < g.n_iter; ++it) {
         T6 fr[2];
-        geo_force(f.c, d, T6(0.5) * (u1 + t1), T6(0.5) * (u2 + t2), u3, fr, ms);
+        geo_force(g, f.c, d, T6(0.5) * (u1 + t1), T6(0.5) * (u2 + t2), u3, fr, ms);
         t1 = u1 + T6(g.dt) * fr[0];
         t2 = u2 + T6(g.dt) * fr[1];
       }
@@ -246,14 +246,14 @@ __device__ inline void adjoint_one(const Grid& g, const GatherPlanesT<double>& f
       // tangent of the map with Z held fixed
       T6 b1 = T6(0.5) * (u1 + T6(z1)), b2 = T6(0.5) * (u2 + T6(z2));
       T6 fr[2];
-      geo_force(f.c, d, b1, b2, u3, fr, ms);
+      geo_force(g, f.c, d, b1, b2, u3, fr, ms);
       T6 n1 = u1 + T6(g.dt) * fr[0], n2 = u2 + T6(g.dt) * fr[1];
       // A = dt/2 df/dubar_{12} at the fixed point
       CoeffsT<T2> m2{T2(fv.c.alpha), T2(fv.c.beta1), T2(fv.c.hu11), T2(fv.c.hu22), T2(fv.c.hu33),
                      T2(fv.c.hu13)};
       const GradT<T2> d2 = lift<T2>(dv);
       T2 f2[2];
-      geo_force(m2, d2, seed<2>(0.5 * (s1 + z1), 0), seed<2>(0.5 * (s2 + z2), 1), T2(w3), f2, ms);
+      geo_force(g, m2, d2, seed<2>(0.5 * (s1 + z1), 0), seed<2>(0.5 * (s2 + z2), 1), T2(w3), f2, ms);
       const double A[2][2] = {{0.5 * g.dt * f2[0].d[0], 0.5 * g.dt * f2[0].d[1]},
                               {0.5 * g.dt * f2[1].d[0], 0.5 * g.dt * f2[1].d[1]}};
       n1.v = z1;

@@ -679,6 +679,7 @@ grpic_status grpic_create(const grpic_params* p, grpic_ctx** out) {
     g.dt = p->cfl / vmax;
   }
   c->prm.dt = g.dt;
+  g.inv_dt = 1.0 / g.dt;
   {
     // the polar cap of the axis update ends at theta(x2 = 1/2)
     double thc, td, dtd;
@@ -700,6 +701,11 @@ grpic_status grpic_create(const grpic_params* p, grpic_ctx** out) {
     g.axis_band = 4.0 * g.dth;
     g.band_hi = kPi - g.axis_band;
     if (g.r0 != 0.0 || g.h0 != 0.0) g.ser = 0;
+    // midpoints reach half a cell past the particle's cell: one cell beyond the
+    // axis bands (4 cells or 0.11 rad in double, 0.11 rad in single precision)
+    const double wide = std::ceil(0.11 / g.dth) + 1.0;
+    g.mid32 = (int)wide;
+    g.mid64 = g.ser == 2 ? 5 : (int)wide;
   }
   // single-precision push: cells whose inner edge lies below r = 3 M keep the
   // metric and its derivatives in FP64 (the horizon region, where lapse and

@@ -141,7 +141,8 @@ __device__ inline void boris(R& ux, R& uy, R& uz, const R E[3], const R B[3], R 
   uz = mz + (px * sy - py * sx) + k * E[2];
 }
 
-// EM half step: covariant -> tetrad (App. A), Boris, tetrad -> covariant.
+// EM half step: covariant -> tetrad (App. A), Boris, tetrad -> covariant:
+// u_hat1 = u^1 / sqrt(h^11), u_hat2 = u_2 / sqrt(h_22), u_hat3 = u_3 / sqrt(h_33).
 // Single precision takes only the change of the tetrad components back and
 // adds it to the covariant u, so u carries one rounding per half step instead
 // of those of a full round trip through the tetrad (which would dominate the
@@ -151,50 +152,51 @@ __device__ inline void boris(R& ux, R& uy, R& uz, const R E[3], const R B[3], R 
 template <class R>
 __device__ inline void em_half(const FrameT<R>& f, const R E[3], const R B[3], R k, R& u1, R& u2,
                                R& u3) {
+  const R k13 = f.c.hu13 * f.is11;
   if constexpr (sizeof(R) == 4) {
-    const R x = f.s11 * (u1 - f.k13 * u3);
-    const R y = u2 * rcp(f.s22);
-    const R z = u3 * rcp(f.s33);
+    const R x = f.is11 * (f.c.hu11 * u1 + f.c.hu13 * u3);
+    const R y = u2 * (f.c.hu22 * f.s22);
+    const R z = u3 * f.is33;
     R dx, dy, dz;
     boris_delta(x, y, z, E, B, k, dx, dy, dz);
-    u1 = u1 + (dx * rcp(f.s11) + f.k13 * f.s33 * dz);
+    const R d3 = f.s33 * dz;
+    u1 = u1 + f.is11 * (dx - k13 * d3);
     u2 = u2 + f.s22 * dy;
-    u3 = u3 + f.s33 * dz;
+    u3 = u3 + d3;
   } else {
-    R x = f.s11 * (u1 - f.k13 * u3);
-    R y = u2 / f.s22;
-    R z = u3 / f.s33;
+    R x = f.is11 * (f.c.hu11 * u1 + f.c.hu13 * u3);
+    R y = u2 * (f.c.hu22 * f.s22);
+    R z = u3 * f.is33;
     boris(x, y, z, E, B, k);
-    u1 = x / f.s11 + f.k13 * f.s33 * z;
-    u2 = f.s22 * y;
     u3 = f.s33 * z;
+    u1 = f.is11 * (x - k13 * u3);
+    u2 = f.s22 * y;
   }
 }
 
 // Implicit-midpoint geodesic momentum update at fixed x^n (eq.
-// discretized-geodesic-u); u_3 is untouched.
+// discretized-geodesic-u); u_3 is untouched.  With t_jk the terms h^jk b_j b_k
+// of gamma^2, the force's sum over the metric derivatives is one over the
+// logarithmic derivatives times those terms (GradT).
 template <class R>
 __device__ inline void geodesic_u(const Grid& g, const FrameT<R>& f, const GradT<R>& d, R& u1, R& u2,
                                   R u3, R mass2) {
   const CoeffsT<R>& m = f.c;
   const R s1 = u1, s2 = u2;
-  const R u33 = u3 * u3;
-  const R dt = (R)g.dt;
+  const R t33 = m.hu33 * u3 * u3, c13 = (R)2 * m.hu13 * u3, ha = (R)0.5 * m.alpha;
+  const R dt = (R)g.dt, dxi = (R)g.dxi;
   R t1 = s1, t2 = s2;
   for (int it = 0; it < g.n_iter; ++it) {
     const R b1 = (R)0.5 * (s1 + t1), b2 = (R)0.5 * (s2 + t2);
-    const R Q = mass2 + m.hu11 * b1 * b1 + m.hu22 * b2 * b2 + m.hu33 * u33 + (R)2 * m.hu13 * b1 * u3;
+    const R t11 = m.hu11 * b1 * b1, t22 = m.hu22 * b2 * b2, t13 = c13 * b1;
+    const R W = t22 + t13 + t33;
+    const R Q = mass2 + t11 + W;
     const R ig = rsqrt(Q);
-    const R gb = Q * ig;
-    const R h = (R)0.5 * m.alpha * ig;
-    R fr[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const R q = d.hu11[i] * b1 * b1 + d.hu22[i] * b2 * b2 + d.hu33[i] * u33 +
-                  (R)2 * d.hu13[i] * b1 * u3;
-      fr[i] = -gb * d.alpha[i] + b1 * d.beta1[i] - h * q;
-    }
-    const R n1 = s1 + dt * fr[0], n2 = s2 + dt * fr[1];
+    const R gb = Q * ig, h = ha * ig;
+    const R q1 = d.l11[0] * t11 - d.z[0] * W - dxi * t13;
+    const R q2 = d.l11[1] * t11 - d.z[1] * W - d.ct * t33 - d.tt * t22;
+    const R n1 = s1 + dt * (b1 * d.beta1[0] - gb * d.alpha[0] - h * q1);
+    const R n2 = s2 + dt * (b1 * d.beta1[1] - gb * d.alpha[1] - h * q2);
     // exact repeat: the fixed point of the map; or the optional convergence
     // test, evaluated in FP64
     bool fixed = n1 == t1 && n2 == t2;
@@ -255,11 +257,11 @@ __device__ inline void sincos_small(double x, double* s, double* c) {
 
 // exp(t) for |t| <= 0.03: Taylor series to t^8 (remainder below 1e-19 relative)
 __device__ inline double exp_short(double t) {
-  double p = fma(t, 1.0 / 40320.0, 1.0 / 5040.0);
-  p = fma(t, p, 1.0 / 720.0);
-  p = fma(t, p, 1.0 / 120.0);
-  p = fma(t, p, 1.0 / 24.0);
-  p = fma(t, p, 1.0 / 6.0);
+  double p = fma_k(t, 1.0 / 40320.0, 1.0 / 5040.0);
+  p = fma_k(t, p, 1.0 / 720.0);
+  p = fma_k(t, p, 1.0 / 120.0);
+  p = fma_k(t, p, 1.0 / 24.0);
+  p = fma_k(t, p, 1.0 / 6.0);
   p = fma(t, p, 0.5);
   p = fma(t, p, 1.0);
   return fma(t, p, 1.0);
@@ -269,10 +271,10 @@ __device__ inline double exp_short(double t) {
 // below 2e-17 relative)
 __device__ inline void sincos_short(double x, double* s, double* c) {
   const double z = x * x;
-  double ps = fma(z, -1.0 / 5040.0, 1.0 / 120.0);
-  ps = fma(z, ps, -1.0 / 6.0);
+  double ps = fma_k(z, -1.0 / 5040.0, 1.0 / 120.0);
+  ps = fma_k(z, ps, -1.0 / 6.0);
   *s = fma(x * z, ps, x);
-  double pc = fma(z, -1.0 / 720.0, 1.0 / 24.0);
+  double pc = fma_k(z, -1.0 / 720.0, 1.0 / 24.0);
   pc = fma(z, pc, -0.5);
   *c = fma(z, pc, 1.0);
 }
@@ -407,6 +409,78 @@ __device__ inline RSCT<float> rsc_near_f(const Grid& g, const Tables& t, int i1,
   return p;
 }
 
+// The tables' values at a cell's corner, read once per particle: positions in
+// the cells at least mid64 / mid32 from both axes (mid: every active lane of
+// the wavefront) need nothing else, and the iterations of the coordinate update
+// then neither read memory nor branch on the angle.
+template <class T>
+struct AnchorT {
+  T r, s, c;
+  bool mid;
+};
+
+template <int SER>
+__device__ inline AnchorT<double> anchor_at(const Grid& g, const Tables& t, int i1, int i2, double) {
+  AnchorT<double> a;
+  a.mid = false;
+  if (SER > 0) {
+    a.r = t.r[0][i1 + g.ng];
+    a.s = t.s[0][i2 + g.ng];
+    a.c = t.c[0][i2 + g.ng];
+    a.mid = __all((i2 >= g.mid64) & (i2 < g.n_th - g.mid64));
+  }
+  return a;
+}
+template <int SER>
+__device__ inline AnchorT<float> anchor_at(const Grid& g, const Tables& t, int i1, int i2, float) {
+  AnchorT<float> a;
+  a.mid = false;
+  if (SER > 0) {
+    a.r = t.rf[i1 + g.ng];
+    a.s = t.sf[i2 + g.ng];
+    a.c = t.cf[i2 + g.ng];
+    a.mid = __all((i2 >= g.mid32) & (i2 < g.n_th - g.mid32));
+  }
+  return a;
+}
+
+// r, sin, cos and the map factors at offsets (dx + h) from the corner of cell
+// (i1, i2): the anchor's form, or rsc_near / rsc_near_f.
+template <int SER>
+__device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<double>& an, int i1, double dx1, double h1,
+                             int i2, double dx2, double h2) {
+  if (SER == 0 || !an.mid) return rsc_near<SER>(g, t, i1, ((double)i1 + dx1) + h1, i2, ((double)i2 + dx2) + h2);
+  RSC p;
+  const double tr = (dx1 + h1) * g.dxi, x = (dx2 + h2) * g.dth;
+  double sp, cp;
+  if (SER == 2) sincos_short(x, &sp, &cp); else sincos_small(x, &sp, &cp);
+  p.r = an.r * (SER == 2 ? exp_short(tr) : exp_small(tr));
+  p.rd = g.dxi * p.r;
+  p.td = g.dth;
+  p.itd2 = g.inv_dth2;
+  p.dtd = 0.0;
+  p.s = fma(an.s, cp, an.c * sp);
+  p.c = fma(an.c, cp, -(an.s * sp));
+  return p;
+}
+template <int SER>
+__device__ inline RSCT<float> rsc_at(const Grid& g, const Tables& t, const AnchorT<float>& an, int i1, float dx1,
+                                     float h1, int i2, float dx2, float h2) {
+  const float f1 = dx1 + h1, f2 = dx2 + h2;
+  if (SER == 0 || !an.mid) return rsc_near_f<SER>(g, t, i1, f1, i2, f2);
+  RSCT<float> p;
+  float sp, cp;
+  sincos_small_f(f2 * (float)g.dth, &sp, &cp);
+  p.r = an.r * exp_small_f(f1 * (float)g.dxi);
+  p.rd = (float)g.dxi * p.r;
+  p.td = (float)g.dth;
+  p.itd2 = (float)g.inv_dth2;
+  p.dtd = 0.0f;
+  p.s = fmaf(an.s, cp, an.c * sp);
+  p.c = fmaf(an.c, cp, -(an.s * sp));
+  return p;
+}
+
 // Sort key of a slot's state: its cell i1 * n_th + i2, or n_cells for a slot
 // that the cell sort drops (empty, invalid, leaving, outside the grid).
 __device__ inline int cell_key(const Grid& g, uint8_t t, int i1, int i2) {
@@ -457,6 +531,43 @@ struct Move {
   int cell;            // sort key of the state after the push (cell_key)
 };
 
+// Implicit coordinate update (eq. discretized-geodesic-x): the displacement
+// (d1, d2) in cells and w3, the phi velocity alpha u^3 / gamma at the path
+// midpoint.  An iterate that repeats exactly is the fixed point of the map, so
+// stopping there gives the same result as running all n_iter iterations (and
+// with iter_tol > 0 the loop also ends once the FP64 change is below the
+// relative tolerance).  The first iterate (d = 0) uses the coefficients m at
+// x^n already in hand; w3 is that of the last evaluation if the iterate
+// repeats there, and of one more at the final midpoint otherwise.
+template <int SER, class R>
+__device__ inline void coordinate_update(const Grid& g, const Tables& tab, const AnchorT<R>& an, const CoeffsT<R>& m,
+                                         int i1, R dx1, int i2, R dx2, R u1, R u2, R u3, R mass2, R& d1, R& d2,
+                                         R& w3) {
+  const R dt = (R)g.dt, half = (R)0.5;
+  const R iu0 = m.alpha * rsqrt(mass2 + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
+                                (R)2 * m.hu13 * u1 * u3);
+  R n1 = dt * ((m.hu11 * u1 + m.hu13 * u3) * iu0 - m.beta1);
+  R n2 = dt * (m.hu22 * u2 * iu0);
+  w3 = (m.hu13 * u1 + m.hu33 * u3) * iu0;
+  d1 = (R)0;
+  d2 = (R)0;
+  for (int it = 1;; ++it) {
+    const bool repeat = n1 == d1 && n2 == d2;
+    bool last = it >= g.n_iter;
+    if (g.iter_tol > 0.0)
+      last = last || fabs((double)n1 - (double)d1) + fabs((double)n2 - (double)d2) <=
+                         g.iter_tol * (fabs((double)n1) + fabs((double)n2));
+    d1 = n1;
+    d2 = n2;
+    if (repeat) break;
+    const VelT<R> v = velocity_from(g, rsc_at<SER>(g, tab, an, i1, dx1, half * d1, i2, dx2, half * d2), u1, u2, u3, mass2);
+    w3 = v.w3;
+    if (last) break;
+    n1 = dt * v.v1;
+    n2 = dt * v.v2;
+  }
+}
+
 // FP64 particle update (Sec. 3.1 steps 1-11) of slot k; writes the new state
 // and returns the move for the deposit.
 template <int SER, bool kPrev = true>
@@ -491,10 +602,10 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   mv.xa = dx1;
   mv.ya = dx2;
 
-  const double x1 = (double)i1 + dx1, x2 = (double)i2 + dx2;
+  AnchorT<double> an = anchor_at<SER>(g, tab, i1, i2, 0.0);
   Frame f;
   Grad d;
-  frame_from(g, rsc_near<SER>(g, tab, i1, x1, i2, x2), &f, &d);
+  frame_from(g, rsc_at<SER>(g, tab, an, i1, dx1, 0.0, i2, dx2, 0.0), &f, &d);
   const double qm = species_sign(t);
   if (qm != 0.0) {
     // D^i, B^i at x^n -> tetrad components, scaled by the lapse
@@ -504,9 +615,9 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
     const double B1 = interp<0, 1>(g, fp.B[0], i1, dx1, i2, dx2);
     const double B2 = interp<1, 0>(g, fp.B[1], i1, dx1, i2, dx2);
     const double B3 = interp<1, 1>(g, fp.B[2], i1, dx1, i2, dx2);
-    const double al = f.c.alpha, ais11 = al * rcp(f.s11);
-    const double E[3] = {ais11 * D1, al * f.s22 * D2, al * f.s33 * (f.k13 * D1 + D3)};
-    const double B[3] = {ais11 * B1, al * f.s22 * B2, al * f.s33 * (f.k13 * B1 + B3)};
+    const double al = f.c.alpha, ais11 = al * f.is11, k13 = f.c.hu13 * f.is11 * f.is11;
+    const double E[3] = {ais11 * D1, al * f.s22 * D2, al * f.s33 * (D3 - k13 * D1)};
+    const double B[3] = {ais11 * B1, al * f.s22 * B2, al * f.s33 * (B3 - k13 * B1)};
     const double kb = 0.25 * qm * g.dt;
     em_half(f, E, B, kb, u1, u2, u3);
     geodesic_u(g, f, d, u1, u2, u3, 1.0);
@@ -515,46 +626,18 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
     geodesic_u(g, f, d, u1, u2, u3, mass2_of(t));  // EM stage skipped for q = 0
   }
 
-  // implicit coordinate update (eq. discretized-geodesic-x); an iterate that
-  // repeats exactly is the fixed point of the map, so stopping there gives the
-  // same result as running all n_iter iterations (and with iter_tol > 0 the
-  // loop also ends once the FP64 change is below the relative tolerance)
-  // The first iterate (d = 0) uses the coefficients at x^n already in hand.
-  double d1 = 0.0, d2 = 0.0;
-  Coeffs m = f.c;
-  // m^2 from the tag, taken here rather than at the top: the empty asm keeps
-  // the compiler from hoisting it, so that it is not live through the field
-  // gather and EM stages, where the FP64 update is at its register limit
+  // m^2 and the anchor, taken here again rather than kept from the top: the
+  // empty asm keeps the compiler from hoisting them, so that they are not live
+  // through the field gather and EM stages, where the FP64 update is at its
+  // register limit
   uint32_t tl = t;
-  asm volatile("" : "+v"(tl));
+  asm volatile("" : "+v"(tl), "+v"(i1), "+v"(i2));
+  an = anchor_at<SER>(g, tab, i1, i2, 0.0);
   const double ms = mass2_of((uint8_t)tl);
-  double iu0;
-  bool repeat = false;
-  for (int it = 0;;) {
-    iu0 = m.alpha * rsqrt(ms + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                          2.0 * m.hu13 * u1 * u3);
-    const double n1 = g.dt * ((m.hu11 * u1 + m.hu13 * u3) * iu0 - m.beta1);
-    const double n2 = g.dt * (m.hu22 * u2 * iu0);
-    repeat = n1 == d1 && n2 == d2;
-    bool fixed = repeat;
-    if (g.iter_tol > 0.0)
-      fixed = fixed || fabs(n1 - d1) + fabs(n2 - d2) <= g.iter_tol * (fabs(n1) + fabs(n2));
-    d1 = n1;
-    d2 = n2;
-    if (fixed || ++it >= g.n_iter) break;
-    m = coeffs_from(g, rsc_near<SER>(g, tab, i1, x1 + 0.5 * d1, i2, x2 + 0.5 * d2));
-  }
-  {
-    // phi update and the phi velocity at the path midpoint (the J^3 of the
-    // deposit); after an exact repeat the last coefficients are already there
-    if (!repeat) {
-      m = coeffs_from(g, rsc_near<SER>(g, tab, i1, x1 + 0.5 * d1, i2, x2 + 0.5 * d2));
-      iu0 = m.alpha * rsqrt(ms + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                            2.0 * m.hu13 * u1 * u3);
-    }
-    P.phi[k] += g.dt * (m.hu13 * u1 + m.hu33 * u3) * iu0;
-    mv.vphi = (m.hu13 * u1 + m.hu33 * u3) * iu0;
-  }
+  double d1, d2, w3;
+  coordinate_update<SER>(g, tab, an, f.c, i1, dx1, i2, dx2, u1, u2, u3, ms, d1, d2, w3);
+  P.phi[k] += g.dt * w3;
+  mv.vphi = w3;
   dx1 += d1;
   renormalize(i1, dx1);
   dx2 += d2;
@@ -628,30 +711,32 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
   mv.xa = dx1;
   mv.ya = dx2;
 
+  AnchorT<float> an = anchor_at<SER>(g, tab, i1, i2, 0.0f);
   FrameT<float> f;
   GradT<float> d;
   if (i1 < g.i_fp64) {
     // horizon region: metric and derivatives in FP64, then rounded
     Frame fd;
     Grad dd;
-    frame_from(g, rsc_near<SER>(g, tab, i1, (double)i1 + dx1, i2, (double)i2 + dx2), &fd, &dd);
+    const AnchorT<double> ad = anchor_at<SER>(g, tab, i1, i2, 0.0);
+    frame_from(g, rsc_at<SER>(g, tab, ad, i1, (double)dx1, 0.0, i2, (double)dx2, 0.0), &fd, &dd);
     f.c = CoeffsT<float>{(float)fd.c.alpha, (float)fd.c.beta1, (float)fd.c.hu11,
                          (float)fd.c.hu22, (float)fd.c.hu33, (float)fd.c.hu13};
-    f.s11 = (float)fd.s11;
+    f.is11 = (float)fd.is11;
     f.s22 = (float)fd.s22;
     f.s33 = (float)fd.s33;
-    f.k13 = (float)fd.k13;
+    f.is33 = (float)fd.is33;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       d.alpha[q] = (float)dd.alpha[q];
       d.beta1[q] = (float)dd.beta1[q];
-      d.hu11[q] = (float)dd.hu11[q];
-      d.hu22[q] = (float)dd.hu22[q];
-      d.hu33[q] = (float)dd.hu33[q];
-      d.hu13[q] = (float)dd.hu13[q];
+      d.l11[q] = (float)dd.l11[q];
+      d.z[q] = (float)dd.z[q];
     }
+    d.ct = (float)dd.ct;
+    d.tt = (float)dd.tt;
   } else {
-    frame_from(g, rsc_near_f<SER>(g, tab, i1, dx1, i2, dx2), &f, &d);
+    frame_from(g, rsc_at<SER>(g, tab, an, i1, dx1, 0.0f, i2, dx2, 0.0f), &f, &d);
   }
   const float qm = (float)species_sign(t);
   const float ms = (float)mass2_of(t);
@@ -662,9 +747,9 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     const float B1 = interp<0, 1>(g, fp.B[0], i1, dx1, i2, dx2);
     const float B2 = interp<1, 0>(g, fp.B[1], i1, dx1, i2, dx2);
     const float B3 = interp<1, 1>(g, fp.B[2], i1, dx1, i2, dx2);
-    const float al = f.c.alpha, ais11 = al * rcp(f.s11);
-    const float E[3] = {ais11 * D1, al * f.s22 * D2, al * f.s33 * (f.k13 * D1 + D3)};
-    const float B[3] = {ais11 * B1, al * f.s22 * B2, al * f.s33 * (f.k13 * B1 + B3)};
+    const float al = f.c.alpha, ais11 = al * f.is11, k13 = f.c.hu13 * f.is11 * f.is11;
+    const float E[3] = {ais11 * D1, al * f.s22 * D2, al * f.s33 * (D3 - k13 * D1)};
+    const float B[3] = {ais11 * B1, al * f.s22 * B2, al * f.s33 * (B3 - k13 * B1)};
     const float kb = 0.25f * qm * (float)g.dt;
     em_half(f, E, B, kb, u1, u2, u3);
     geodesic_u(g, f, d, u1, u2, u3, 1.0f);
@@ -673,36 +758,11 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     geodesic_u(g, f, d, u1, u2, u3, ms);  // EM stage skipped for q = 0
   }
 
-  // implicit coordinate update with the displacement (d1, d2) in cells
-  const float dt = (float)g.dt;
-  float d1 = 0.0f, d2 = 0.0f;
-  CoeffsT<float> m = f.c;
-  float iu0;
-  bool repeat = false;
-  for (int it = 0;;) {
-    iu0 = m.alpha * rsqrt(ms + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                          2.0f * m.hu13 * u1 * u3);
-    const float n1 = dt * ((m.hu11 * u1 + m.hu13 * u3) * iu0 - m.beta1);
-    const float n2 = dt * (m.hu22 * u2 * iu0);
-    repeat = n1 == d1 && n2 == d2;
-    bool fixed = repeat;
-    if (g.iter_tol > 0.0)
-      fixed = fixed || fabs((double)n1 - (double)d1) + fabs((double)n2 - (double)d2) <=
-                           g.iter_tol * (fabs((double)n1) + fabs((double)n2));
-    d1 = n1;
-    d2 = n2;
-    if (fixed || ++it >= g.n_iter) break;
-    m = coeffs_from(g, rsc_near_f<SER>(g, tab, i1, dx1 + 0.5f * d1, i2, dx2 + 0.5f * d2));
-  }
-  {
-    if (!repeat) {
-      m = coeffs_from(g, rsc_near_f<SER>(g, tab, i1, dx1 + 0.5f * d1, i2, dx2 + 0.5f * d2));
-      iu0 = m.alpha * rsqrt(ms + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                            2.0f * m.hu13 * u1 * u3);
-    }
-    mv.vphi = (m.hu13 * u1 + m.hu33 * u3) * iu0;
-    P.phi[k] += dt * mv.vphi;
-  }
+  float d1, d2;
+  asm volatile("" : "+v"(i1), "+v"(i2));  // (the anchor again, as in push_one)
+  an = anchor_at<SER>(g, tab, i1, i2, 0.0f);
+  coordinate_update<SER>(g, tab, an, f.c, i1, dx1, i2, dx2, u1, u2, u3, ms, d1, d2, mv.vphi);
+  P.phi[k] += (float)g.dt * mv.vphi;
   dx1 += d1;
   renormalize(i1, dx1);
   dx2 += d2;
@@ -812,21 +872,10 @@ struct ContribT {
 };
 
 // lapse-weighted phi velocity alpha u^3 / gamma at the path midpoint (ia + xm, ja + ym)
-template <int SER>
-__device__ inline double vphi_mid(const Grid& g, const Tables& tab, int ia, double xm, int ja,
-                                  double ym, double u1, double u2, double u3) {
-  const Coeffs m = coeffs_from(g, rsc_near<SER>(g, tab, ia, (double)ia + xm, ja, (double)ja + ym));
-  const double iu0 = m.alpha * rsqrt(1.0 + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                                     2.0 * m.hu13 * u1 * u3);
-  return (m.hu13 * u1 + m.hu33 * u3) * iu0;
-}
-template <int SER>
-__device__ inline float vphi_mid(const Grid& g, const Tables& tab, int ia, float xm, int ja,
-                                 float ym, float u1, float u2, float u3) {
-  const CoeffsT<float> m = coeffs_from(g, rsc_near_f<SER>(g, tab, ia, xm, ja, ym));
-  const float iu0 = m.alpha * rsqrt(1.0f + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                                    2.0f * m.hu13 * u1 * u3);
-  return (m.hu13 * u1 + m.hu33 * u3) * iu0;
+template <int SER, class T>
+__device__ inline T vphi_mid(const Grid& g, const Tables& tab, int ia, T xm, int ja, T ym, T u1, T u2, T u3) {
+  const AnchorT<T> an = anchor_at<SER>(g, tab, ia, ja, (T)0);
+  return velocity_from(g, rsc_at<SER>(g, tab, an, ia, xm, (T)0, ja, ym, (T)0), u1, u2, u3, (T)1).w3;
 }
 
 template <class T, int SER>
@@ -840,7 +889,7 @@ __device__ inline bool make_contrib(const Grid& g, const Tables& tab, const Move
       abs(di) > 1 || abs(dj) > 1)
     return false;
   const T q = mv.q;
-  const T qdt = q / (T)g.dt;
+  const T qdt = q * (T)g.inv_dt;
   const T one = (T)1, half = (T)0.5;
   const T xa = mv.xa, ya = mv.ya;
   const T xb = (T)di + mv.xb, yb = (T)dj + mv.yb;
