@@ -193,7 +193,7 @@ __device__ inline void adjoint_one(const Grid& g, const GatherPlanesT<double>& f
 
   FrameT<T6> f;
   GradT<T6> d;
-  frame_from(g, rsc_tan(g, x1, x2), &f, &d);
+  frame_from<true>(g, rsc_tan(g, x1, x2), &f, &d);
   const double qm = species_sign(t);
   const double ms = mass2_of(t);  // m^2 in gamma: 0 for a massless neutral particle
   T6 E[3], B[3];

@@ -25,6 +25,16 @@ namespace grpic {
 
 constexpr double kPi = 3.14159265358979323846;
 
+// Uniform values of the particle update in its own precision.  The single-
+// precision copy is made on the host: a conversion of a kernel argument is a
+// vector instruction at a quarter of the full rate in every wavefront.
+template <class R>
+struct UniT {
+  R a, a2, M, two_M;
+  R dxi, dth, inv_dth2;
+  R dt, inv_dt, charge_scale, small_angle;
+};
+
 // Everything a kernel needs to know about the grid and the run, by value.
 struct Grid {
   double a, M;
@@ -48,6 +58,10 @@ struct Grid {
   // cells at least this far from both axes take the push's table form of the
   // polar angle in double / single precision (outside the series' axis bands)
   int mid64, mid32;
+  // the gather's 32-bit byte offsets and 24-bit index product hold (planes
+  // below 4 GiB, rows and columns below 2^24)
+  int narrow;
+  UniT<float> uf;
   int64_t plane;          // reals per plane
 };
 
@@ -72,6 +86,20 @@ struct Tables {
   const float* __restrict__ sf;
   const float* __restrict__ cf;
 };
+
+template <class R>
+__host__ __device__ inline UniT<R> uni(const Grid& g) {
+  if constexpr (sizeof(R) == 4) return g.uf;
+  else return {R(g.a), R(g.a2), R(g.M), R(g.two_M), R(g.dxi), R(g.dth), R(g.inv_dth2),
+               R(g.dt), R(g.inv_dt), R(g.charge_scale), R(g.small_angle)};
+}
+
+// Element k of a table or array by a 32-bit byte offset from a uniform base
+// (k sizeof(T) below 2^32): one address register, no 64-bit vector arithmetic.
+template <class T>
+__device__ inline T& elem(T* __restrict__ p, uint32_t k) {
+  return *(T*)((char*)p + (size_t)(uint32_t)(k * (uint32_t)sizeof(T)));
+}
 
 // Pusher coefficients at a point: lapse, shift and inverse spatial metric.
 template <class R>
@@ -258,12 +286,13 @@ __host__ __device__ inline Coeffs coeffs_at(const Grid& g, double x1, double x2)
 
 // Coefficients, tetrad factors and first derivatives at a point.  Three
 // inverse square roots (of Sigma, S2 and A) and one reciprocal give them all.
-template <class R>
+// kMap: the general map (tt is 0 on the logarithmic-r, uniform-theta grid).
+template <bool kMap, class R>
 __host__ __device__ inline void frame_from(const Grid& g, RSCT<R> p, FrameT<R>* f, GradT<R>* d) {
-  const R r = p.r, s = p.s, c = p.c;
-  const R a = (R)g.a, M = (R)g.M, dxi = (R)g.dxi, T = p.td, Rr = p.rd;
-  const R a2 = sizeof(R) == 8 ? (R)g.a2 : a * a, r2 = r * r;
-  const R tMr = sizeof(R) == 8 ? (R)g.two_M * r : (R)2 * M * r;
+  const R r = p.r, s = p.s, c = p.c, T = p.td, Rr = p.rd;
+  const UniT<R> U = uni<R>(g);
+  const R a = U.a, M = U.M, dxi = U.dxi, a2 = U.a2, r2 = r * r;
+  const R tMr = U.two_M * r;
   const R Sig = r2 + a2 * c * c;
   const R S2 = Sig + tMr;
   const R ra = r2 + a2;
@@ -306,7 +335,7 @@ __host__ __device__ inline void frame_from(const Grid& g, RSCT<R> p, FrameT<R>* 
   d->z[0] = Rr * dls;
   d->z[1] = Tst * iSig;
   d->ct = (R)2 * T * c * s * is2;
-  d->tt = (R)2 * p.dtd * T * p.itd2;
+  d->tt = kMap ? (R)2 * p.dtd * T * p.itd2 : (R)0;
 }
 
 // Coordinate velocity of a particle at a point: v1 = alpha u^1 / gamma -
@@ -329,8 +358,9 @@ struct VelT {
 template <class R>
 __device__ inline VelT<R> velocity_from(const Grid& g, RSCT<R> p, R u1, R u2, R u3, R mass2) {
   const R r = p.r, s = p.s, c = p.c, Rr = p.rd;
-  const R a = (R)g.a, a2 = sizeof(R) == 8 ? (R)g.a2 : a * a, r2 = r * r;
-  const R tMr = (sizeof(R) == 8 ? (R)g.two_M : (R)(2.0 * g.M)) * r;
+  const UniT<R> U = uni<R>(g);
+  const R a = U.a, a2 = U.a2, r2 = r * r;
+  const R tMr = U.two_M * r;
   const R Sig = r2 + a2 * c * c;
   const R S2 = Sig + tMr;
   const R ra = r2 + a2;
@@ -349,10 +379,6 @@ __device__ inline VelT<R> velocity_from(const Grid& g, RSCT<R> p, R u1, R u2, R 
   v.v2 = p.itd2 * u2 * gi;
   v.w3 = (a * p1 + t3) * gi;
   return v;
-}
-
-__host__ __device__ inline void frame_at(const Grid& g, double x1, double x2, Frame* f, Grad* d) {
-  frame_from(g, rsc_direct(g, x1, x2), f, d);
 }
 
 // Geometry at a grid location for the field solver (theta not clamped).

@@ -706,6 +706,11 @@ grpic_status grpic_create(const grpic_params* p, grpic_ctx** out) {
     const double wide = std::ceil(0.11 / g.dth) + 1.0;
     g.mid32 = (int)wide;
     g.mid64 = g.ser == 2 ? 5 : (int)wide;
+    const int64_t bytes = g.plane * (c->f32 ? 4 : 8);
+    g.narrow = bytes < ((int64_t)1 << 32) && p->n_r + 2 * p->n_ghost < (1 << 24) && g.ld < (1 << 24);
+    const UniT<double> u = uni<double>(g);
+    g.uf = UniT<float>{(float)u.a, (float)u.a * (float)u.a, (float)u.M, (float)u.two_M, (float)u.dxi, (float)u.dth,
+                       (float)u.inv_dth2, (float)u.dt, (float)u.inv_dt, (float)u.charge_scale, (float)u.small_angle};
   }
   // single-precision push: cells whose inner edge lies below r = 3 M keep the
   // metric and its derivatives in FP64 (the horizon region, where lapse and

@@ -72,33 +72,54 @@ struct GatherPlanesT {
   const T* __restrict__ B[3];
 };
 
-__device__ inline double species_sign(uint8_t t) {
+template <class T = double>
+__device__ inline T species_sign(uint8_t t) {
   const int s = t & kSpecies;
-  return s == 1 ? 1.0 : (s == 2 ? -1.0 : 0.0);
+  return s == 1 ? (T)1 : (s == 2 ? (T)-1 : (T)0);
 }
 
-// First-order interpolation in code coordinates of a plane staggered by half a
-// cell in x1 (H1) and/or x2 (H2).
-template <int H1, int H2, class T>
-__device__ inline T interp(const Grid& g, const T* __restrict__ F, int i1, T dx1, int i2, T dx2) {
-  int k1 = i1, k2 = i2;
-  T w1 = dx1, w2 = dx2;
+// The arrays from slot k0 on (a block's first slot: uniform), so that a lane
+// reaches its slot with a 32-bit index.
+template <class T>
+__device__ inline ParticleArraysT<T> from_slot(const ParticleArraysT<T>& P, int64_t k0) {
+  return ParticleArraysT<T>{P.i1 + k0, P.i2 + k0, P.dx1 + k0, P.dx2 + k0, P.u1 + k0, P.u2 + k0, P.u3 + k0,
+                            P.w + k0, P.phi + k0, P.i1p + k0, P.i2p + k0, P.dx1p + k0, P.dx2p + k0, P.tag + k0, P.n - k0};
+}
+
+// First-order interpolation in code coordinates of the six field components
+// (D^1, D^2, D^3, B^1, B^2, B^3) at offsets (dx1, dx2) in cell (i1, i2); a
+// component staggered by half a cell starts at the cell's corner or one row or
+// column before it.  O: uint32_t byte offsets where g.narrow says they hold (the
+// planes' bases and the second row's are then scalar), int64_t otherwise.
+template <class O, class T>
+__device__ inline void gather_off(const Grid& g, const GatherPlanesT<T>& fp, int i1, T dx1, int i2, T dx2, T F[6]) {
   const T half = (T)0.5;
-  if (H1) {
-    const bool up = dx1 >= half;
-    k1 = up ? i1 : i1 - 1;
-    w1 = up ? dx1 - half : dx1 + half;
-  }
-  if (H2) {
-    const bool up = dx2 >= half;
-    k2 = up ? i2 : i2 - 1;
-    w2 = up ? dx2 - half : dx2 + half;
-  }
-  const T* p = F + ix(g, k1, k2);
-  const T f00 = p[0], f01 = p[1], f10 = p[g.ld], f11 = p[g.ld + 1];
-  const T a0 = f00 + w2 * (f01 - f00);
-  const T a1 = f10 + w2 * (f11 - f10);
-  return a0 + w1 * (a1 - a0);
+  const bool up1 = dx1 >= half, up2 = dx2 >= half;
+  const T h1 = up1 ? dx1 - half : dx1 + half, h2 = up2 ? dx2 - half : dx2 + half;
+  O o;
+  if constexpr (sizeof(O) == 4) o = ((O)__umul24((unsigned)(i1 + g.ng), (unsigned)g.ld) + (O)(i2 + g.ng)) * (O)sizeof(T);
+  else o = (O)ix(g, i1, i2) * (O)sizeof(T);
+  const O row = (O)g.ld * (O)sizeof(T);
+  const O oa = up1 ? o : o - row, ob = up2 ? o : o - (O)sizeof(T), oab = up2 ? oa : oa - (O)sizeof(T);
+  auto at = [&](const T* __restrict__ p, O off, T w1, T w2) {
+    const T* a = (const T*)((const char*)p + (size_t)off);
+    const T* b = (const T*)((const char*)p + (size_t)row + (size_t)off);
+    const T f00 = a[0], f01 = a[1], f10 = b[0], f11 = b[1];
+    const T a0 = f00 + w2 * (f01 - f00);
+    const T a1 = f10 + w2 * (f11 - f10);
+    return a0 + w1 * (a1 - a0);
+  };
+  F[0] = at(fp.D[0], oa, h1, dx2);
+  F[1] = at(fp.D[1], ob, dx1, h2);
+  F[2] = at(fp.D[2], o, dx1, dx2);
+  F[3] = at(fp.B[0], ob, dx1, h2);
+  F[4] = at(fp.B[1], oa, h1, dx2);
+  F[5] = at(fp.B[2], oab, h1, h2);
+}
+template <class T>
+__device__ inline void gather(const Grid& g, const GatherPlanesT<T>& fp, int i1, T dx1, int i2, T dx2, T F[6]) {
+  if (g.narrow) gather_off<uint32_t>(g, fp, i1, dx1, i2, dx2, F);
+  else gather_off<int64_t>(g, fp, i1, dx1, i2, dx2, F);
 }
 
 // Relativistic Boris step for duration tau in an orthonormal frame: u_minus
@@ -178,13 +199,15 @@ __device__ inline void em_half(const FrameT<R>& f, const R E[3], const R B[3], R
 // discretized-geodesic-u); u_3 is untouched.  With t_jk the terms h^jk b_j b_k
 // of gamma^2, the force's sum over the metric derivatives is one over the
 // logarithmic derivatives times those terms (GradT).
-template <class R>
+// kMap: the general map (GradT::tt is not 0).
+template <bool kMap, class R>
 __device__ inline void geodesic_u(const Grid& g, const FrameT<R>& f, const GradT<R>& d, R& u1, R& u2,
                                   R u3, R mass2) {
   const CoeffsT<R>& m = f.c;
   const R s1 = u1, s2 = u2;
   const R t33 = m.hu33 * u3 * u3, c13 = (R)2 * m.hu13 * u3, ha = (R)0.5 * m.alpha;
-  const R dt = (R)g.dt, dxi = (R)g.dxi;
+  const R ct33 = d.ct * t33;
+  const R dt = uni<R>(g).dt, dxi = uni<R>(g).dxi;
   R t1 = s1, t2 = s2;
   for (int it = 0; it < g.n_iter; ++it) {
     const R b1 = (R)0.5 * (s1 + t1), b2 = (R)0.5 * (s2 + t2);
@@ -194,7 +217,8 @@ __device__ inline void geodesic_u(const Grid& g, const FrameT<R>& f, const GradT
     const R ig = rsqrt(Q);
     const R gb = Q * ig, h = ha * ig;
     const R q1 = d.l11[0] * t11 - d.z[0] * W - dxi * t13;
-    const R q2 = d.l11[1] * t11 - d.z[1] * W - d.ct * t33 - d.tt * t22;
+    R q2 = d.l11[1] * t11 - d.z[1] * W - ct33;
+    if (kMap) q2 = q2 - d.tt * t22;
     const R n1 = s1 + dt * (b1 * d.beta1[0] - gb * d.alpha[0] - h * q1);
     const R n2 = s2 + dt * (b1 * d.beta1[1] - gb * d.alpha[1] - h * q2);
     // exact repeat: the fixed point of the map; or the optional convergence
@@ -362,17 +386,16 @@ template <int SER>
 __device__ inline RSCT<float> rsc_near_f(const Grid& g, const Tables& t, int i1, float f1, int i2,
                                         float f2) {
   RSCT<float> p;
-  const float dth = (float)g.dth, eps = (float)g.small_angle;
-  const float e = SER > 0 ? t.rf[i1 + g.ng] * exp_small_f(f1 * (float)g.dxi)
-                          : t.rf[i1 + g.ng] * expf(f1 * (float)g.dxi);
+  const float dth = g.uf.dth, eps = g.uf.small_angle;
+  const float e = elem(t.rf, (uint32_t)(i1 + g.ng)) * (SER > 0 ? exp_small_f(f1 * g.uf.dxi) : expf(f1 * g.uf.dxi));
   p.r = SER > 0 ? e : (float)g.r0 + e;
-  p.rd = (float)g.dxi * e;
+  p.rd = g.uf.dxi * e;
   const bool upper = 2 * i2 >= g.n_th;
   const float eta = upper ? ((float)(g.n_th - i2) - f2) * dth : ((float)i2 + f2) * dth;
   float ang = eta;
   if (SER > 0) {
     p.td = dth;
-    p.itd2 = (float)g.inv_dth2;
+    p.itd2 = g.uf.inv_dth2;
     p.dtd = 0.0f;
   } else {
     // past the axis (a midpoint of the coordinate iteration) the map is
@@ -424,9 +447,9 @@ __device__ inline AnchorT<double> anchor_at(const Grid& g, const Tables& t, int 
   AnchorT<double> a;
   a.mid = false;
   if (SER > 0) {
-    a.r = t.r[0][i1 + g.ng];
-    a.s = t.s[0][i2 + g.ng];
-    a.c = t.c[0][i2 + g.ng];
+    a.r = elem(t.r[0], (uint32_t)(i1 + g.ng));
+    a.s = elem(t.s[0], (uint32_t)(i2 + g.ng));
+    a.c = elem(t.c[0], (uint32_t)(i2 + g.ng));
     a.mid = __all((i2 >= g.mid64) & (i2 < g.n_th - g.mid64));
   }
   return a;
@@ -436,22 +459,22 @@ __device__ inline AnchorT<float> anchor_at(const Grid& g, const Tables& t, int i
   AnchorT<float> a;
   a.mid = false;
   if (SER > 0) {
-    a.r = t.rf[i1 + g.ng];
-    a.s = t.sf[i2 + g.ng];
-    a.c = t.cf[i2 + g.ng];
+    a.r = elem(t.rf, (uint32_t)(i1 + g.ng));
+    a.s = elem(t.sf, (uint32_t)(i2 + g.ng));
+    a.c = elem(t.cf, (uint32_t)(i2 + g.ng));
     a.mid = __all((i2 >= g.mid32) & (i2 < g.n_th - g.mid32));
   }
   return a;
 }
 
-// r, sin, cos and the map factors at offsets (dx + h) from the corner of cell
-// (i1, i2): the anchor's form, or rsc_near / rsc_near_f.
+// r, sin, cos and the map factors at offsets (f1, f2) from the corner of cell
+// (i1, i2), position (x1, x2): the anchor's form, or rsc_near / rsc_near_f.
 template <int SER>
-__device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<double>& an, int i1, double dx1, double h1,
-                             int i2, double dx2, double h2) {
-  if (SER == 0 || !an.mid) return rsc_near<SER>(g, t, i1, ((double)i1 + dx1) + h1, i2, ((double)i2 + dx2) + h2);
+__device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<double>& an, int i1, double x1, double f1,
+                             int i2, double x2, double f2) {
+  if (SER == 0 || !an.mid) return rsc_near<SER>(g, t, i1, x1, i2, x2);
   RSC p;
-  const double tr = (dx1 + h1) * g.dxi, x = (dx2 + h2) * g.dth;
+  const double tr = f1 * g.dxi, x = f2 * g.dth;
   double sp, cp;
   if (SER == 2) sincos_short(x, &sp, &cp); else sincos_small(x, &sp, &cp);
   p.r = an.r * (SER == 2 ? exp_short(tr) : exp_small(tr));
@@ -464,17 +487,16 @@ __device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<doubl
   return p;
 }
 template <int SER>
-__device__ inline RSCT<float> rsc_at(const Grid& g, const Tables& t, const AnchorT<float>& an, int i1, float dx1,
-                                     float h1, int i2, float dx2, float h2) {
-  const float f1 = dx1 + h1, f2 = dx2 + h2;
+__device__ inline RSCT<float> rsc_at(const Grid& g, const Tables& t, const AnchorT<float>& an, int i1, double,
+                                     float f1, int i2, double, float f2) {
   if (SER == 0 || !an.mid) return rsc_near_f<SER>(g, t, i1, f1, i2, f2);
   RSCT<float> p;
   float sp, cp;
-  sincos_small_f(f2 * (float)g.dth, &sp, &cp);
-  p.r = an.r * exp_small_f(f1 * (float)g.dxi);
-  p.rd = (float)g.dxi * p.r;
-  p.td = (float)g.dth;
-  p.itd2 = (float)g.inv_dth2;
+  sincos_small_f(f2 * g.uf.dth, &sp, &cp);
+  p.r = an.r * exp_small_f(f1 * g.uf.dxi);
+  p.rd = g.uf.dxi * p.r;
+  p.td = g.uf.dth;
+  p.itd2 = g.uf.inv_dth2;
   p.dtd = 0.0f;
   p.s = fmaf(an.s, cp, an.c * sp);
   p.c = fmaf(an.c, cp, -(an.s * sp));
@@ -501,16 +523,16 @@ struct StateT {
 };
 
 template <class T>
-__device__ inline StateT<T> load_state(const ParticleArraysT<T>& P, int64_t k) {
+__device__ inline StateT<T> load_state(const ParticleArraysT<T>& P, uint32_t k) {
   StateT<T> s;
-  s.t = P.tag[k];
-  s.i1 = P.i1[k];
-  s.i2 = P.i2[k];
-  s.dx1 = P.dx1[k];
-  s.dx2 = P.dx2[k];
-  s.u1 = P.u1[k];
-  s.u2 = P.u2[k];
-  s.u3 = P.u3[k];
+  s.t = elem(P.tag, k);
+  s.i1 = elem(P.i1, k);
+  s.i2 = elem(P.i2, k);
+  s.dx1 = elem(P.dx1, k);
+  s.dx2 = elem(P.dx2, k);
+  s.u1 = elem(P.u1, k);
+  s.u2 = elem(P.u2, k);
+  s.u3 = elem(P.u3, k);
   // (the empty asm keeps the compiler from moving a load down to its first use)
   uint32_t t = s.t;
   asm volatile("" : "+v"(t), "+v"(s.i1), "+v"(s.i2), "+v"(s.dx1), "+v"(s.dx2), "+v"(s.u1), "+v"(s.u2), "+v"(s.u3));
@@ -543,7 +565,7 @@ template <int SER, class R>
 __device__ inline void coordinate_update(const Grid& g, const Tables& tab, const AnchorT<R>& an, const CoeffsT<R>& m,
                                          int i1, R dx1, int i2, R dx2, R u1, R u2, R u3, R mass2, R& d1, R& d2,
                                          R& w3) {
-  const R dt = (R)g.dt, half = (R)0.5;
+  const R dt = uni<R>(g).dt, half = (R)0.5;
   const R iu0 = m.alpha * rsqrt(mass2 + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
                                 (R)2 * m.hu13 * u1 * u3);
   R n1 = dt * ((m.hu11 * u1 + m.hu13 * u3) * iu0 - m.beta1);
@@ -560,7 +582,11 @@ __device__ inline void coordinate_update(const Grid& g, const Tables& tab, const
     d1 = n1;
     d2 = n2;
     if (repeat) break;
-    const VelT<R> v = velocity_from(g, rsc_at<SER>(g, tab, an, i1, dx1, half * d1, i2, dx2, half * d2), u1, u2, u3, mass2);
+    const VelT<R> v = velocity_from(g,
+                                    rsc_at<SER>(g, tab, an, i1, ((double)i1 + (double)dx1) + 0.5 * (double)d1,
+                                                dx1 + half * d1, i2, ((double)i2 + (double)dx2) + 0.5 * (double)d2,
+                                                dx2 + half * d2),
+                                    u1, u2, u3, mass2);
     w3 = v.w3;
     if (last) break;
     n1 = dt * v.v1;
@@ -568,34 +594,35 @@ __device__ inline void coordinate_update(const Grid& g, const Tables& tab, const
   }
 }
 
-// FP64 particle update (Sec. 3.1 steps 1-11) of slot k; writes the new state
+// FP64 particle update (Sec. 3.1 steps 1-11) of slot k of the block's arrays
+// (from_slot); writes the new state
 // and returns the move for the deposit.
 template <int SER, bool kPrev = true>
 __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const GatherPlanesT<double>& fp,
-                                        const ParticleArrays& P, int64_t k) {
+                                        const ParticleArrays& P, uint32_t k) {
   Move<double> mv;
   mv.dep = false;
   mv.cell = g.n_r * g.n_th;
-  if (k >= P.n) return mv;
+  if ((int64_t)k >= P.n) return mv;
   const StateT<double> st = load_state(P, k);
   uint8_t t = st.t;
   if (!is_live(t)) return mv;
   if (t & kLeaving) {
-    P.tag[k] = 0;
+    elem(P.tag, k) = 0;
     return mv;
   }
   int i1 = st.i1, i2 = st.i2;
   double dx1 = st.dx1, dx2 = st.dx2;
   if (!in_grid(g, i1, dx1, i2, dx2)) {  // corrupt input: drop, never index with it
-    P.tag[k] = kInvalid;
+    elem(P.tag, k) = kInvalid;
     return mv;
   }
   double u1 = st.u1, u2 = st.u2, u3 = st.u3;
   if (kPrev) {  // the previous position, for a separate deposit
-    P.i1p[k] = i1;
-    P.i2p[k] = i2;
-    P.dx1p[k] = dx1;
-    P.dx2p[k] = dx2;
+    elem(P.i1p, k) = i1;
+    elem(P.i2p, k) = i2;
+    elem(P.dx1p, k) = dx1;
+    elem(P.dx2p, k) = dx2;
   }
   mv.ia = i1;
   mv.ja = i2;
@@ -605,25 +632,21 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   AnchorT<double> an = anchor_at<SER>(g, tab, i1, i2, 0.0);
   Frame f;
   Grad d;
-  frame_from(g, rsc_at<SER>(g, tab, an, i1, dx1, 0.0, i2, dx2, 0.0), &f, &d);
+  frame_from<SER == 0>(g, rsc_at<SER>(g, tab, an, i1, (double)i1 + dx1, dx1, i2, (double)i2 + dx2, dx2), &f, &d);
   const double qm = species_sign(t);
   if (qm != 0.0) {
     // D^i, B^i at x^n -> tetrad components, scaled by the lapse
-    const double D1 = interp<1, 0>(g, fp.D[0], i1, dx1, i2, dx2);
-    const double D2 = interp<0, 1>(g, fp.D[1], i1, dx1, i2, dx2);
-    const double D3 = interp<0, 0>(g, fp.D[2], i1, dx1, i2, dx2);
-    const double B1 = interp<0, 1>(g, fp.B[0], i1, dx1, i2, dx2);
-    const double B2 = interp<1, 0>(g, fp.B[1], i1, dx1, i2, dx2);
-    const double B3 = interp<1, 1>(g, fp.B[2], i1, dx1, i2, dx2);
+    double F[6];
+    gather(g, fp, i1, dx1, i2, dx2, F);
     const double al = f.c.alpha, ais11 = al * f.is11, k13 = f.c.hu13 * f.is11 * f.is11;
-    const double E[3] = {ais11 * D1, al * f.s22 * D2, al * f.s33 * (D3 - k13 * D1)};
-    const double B[3] = {ais11 * B1, al * f.s22 * B2, al * f.s33 * (B3 - k13 * B1)};
+    const double E[3] = {ais11 * F[0], al * f.s22 * F[1], al * f.s33 * (F[2] - k13 * F[0])};
+    const double B[3] = {ais11 * F[3], al * f.s22 * F[4], al * f.s33 * (F[5] - k13 * F[3])};
     const double kb = 0.25 * qm * g.dt;
     em_half(f, E, B, kb, u1, u2, u3);
-    geodesic_u(g, f, d, u1, u2, u3, 1.0);
+    geodesic_u<SER == 0>(g, f, d, u1, u2, u3, 1.0);
     em_half(f, E, B, kb, u1, u2, u3);
   } else {
-    geodesic_u(g, f, d, u1, u2, u3, mass2_of(t));  // EM stage skipped for q = 0
+    geodesic_u<SER == 0>(g, f, d, u1, u2, u3, mass2_of(t));  // EM stage skipped for q = 0
   }
 
   // m^2 and the anchor, taken here again rather than kept from the top: the
@@ -634,9 +657,11 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   asm volatile("" : "+v"(tl), "+v"(i1), "+v"(i2));
   an = anchor_at<SER>(g, tab, i1, i2, 0.0);
   const double ms = mass2_of((uint8_t)tl);
+  // the weight and phi, needed after the iterations: in flight during them
+  const double wt = elem(P.w, k), ph = elem(P.phi, k);
   double d1, d2, w3;
   coordinate_update<SER>(g, tab, an, f.c, i1, dx1, i2, dx2, u1, u2, u3, ms, d1, d2, w3);
-  P.phi[k] += g.dt * w3;
+  elem(P.phi, k) = ph + g.dt * w3;
   mv.vphi = w3;
   dx1 += d1;
   renormalize(i1, dx1);
@@ -657,20 +682,20 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   if (i1 < 0 || i1 >= g.n_r) t |= kLeaving;
   // a non-finite or more-than-one-cell move cannot be deposited: drop it
   if (!(fabs(d1) < 1.0 && fabs(d2) < 1.0)) t = kInvalid;
-  P.i1[k] = i1;
-  P.i2[k] = i2;
-  P.dx1[k] = dx1;
-  P.dx2[k] = dx2;
-  P.u1[k] = u1;
-  P.u2[k] = u2;
-  P.u3[k] = u3;
-  P.tag[k] = t;
+  elem(P.i1, k) = i1;
+  elem(P.i2, k) = i2;
+  elem(P.dx1, k) = dx1;
+  elem(P.dx2, k) = dx2;
+  elem(P.u1, k) = u1;
+  elem(P.u2, k) = u2;
+  elem(P.u3, k) = u3;
+  elem(P.tag, k) = t;
   mv.dep = is_live(t) && qm != 0.0;
   mv.ib = i1;
   mv.jb = i2;
   mv.xb = dx1;
   mv.yb = dx2;
-  mv.q = (qm * g.charge_scale) * P.w[k];
+  mv.q = (qm * g.charge_scale) * wt;
   mv.u1 = u1;
   mv.u2 = u2;
   mv.u3 = u3;
@@ -681,30 +706,30 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
 // Single-precision form of the same update (see the file comment).
 template <int SER, bool kPrev = true>
 __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, const GatherPlanesT<float>& fp,
-                                           const ParticleArraysT<float>& P, int64_t k) {
+                                           const ParticleArraysT<float>& P, uint32_t k) {
   Move<float> mv;
   mv.dep = false;
   mv.cell = g.n_r * g.n_th;
-  if (k >= P.n) return mv;
+  if ((int64_t)k >= P.n) return mv;
   const StateT<float> st = load_state(P, k);
   uint8_t t = st.t;
   if (!is_live(t)) return mv;
   if (t & kLeaving) {
-    P.tag[k] = 0;
+    elem(P.tag, k) = 0;
     return mv;
   }
   int i1 = st.i1, i2 = st.i2;
   float dx1 = st.dx1, dx2 = st.dx2;
   if (!in_grid(g, i1, dx1, i2, dx2)) {
-    P.tag[k] = kInvalid;
+    elem(P.tag, k) = kInvalid;
     return mv;
   }
   float u1 = st.u1, u2 = st.u2, u3 = st.u3;
   if (kPrev) {  // the previous position, for a separate deposit
-    P.i1p[k] = i1;
-    P.i2p[k] = i2;
-    P.dx1p[k] = dx1;
-    P.dx2p[k] = dx2;
+    elem(P.i1p, k) = i1;
+    elem(P.i2p, k) = i2;
+    elem(P.dx1p, k) = dx1;
+    elem(P.dx2p, k) = dx2;
   }
   mv.ia = i1;
   mv.ja = i2;
@@ -719,7 +744,8 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     Frame fd;
     Grad dd;
     const AnchorT<double> ad = anchor_at<SER>(g, tab, i1, i2, 0.0);
-    frame_from(g, rsc_at<SER>(g, tab, ad, i1, (double)dx1, 0.0, i2, (double)dx2, 0.0), &fd, &dd);
+    frame_from<SER == 0>(g, rsc_at<SER>(g, tab, ad, i1, (double)i1 + dx1, (double)dx1, i2, (double)i2 + dx2, (double)dx2),
+                         &fd, &dd);
     f.c = CoeffsT<float>{(float)fd.c.alpha, (float)fd.c.beta1, (float)fd.c.hu11,
                          (float)fd.c.hu22, (float)fd.c.hu33, (float)fd.c.hu13};
     f.is11 = (float)fd.is11;
@@ -736,33 +762,31 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     d.ct = (float)dd.ct;
     d.tt = (float)dd.tt;
   } else {
-    frame_from(g, rsc_at<SER>(g, tab, an, i1, dx1, 0.0f, i2, dx2, 0.0f), &f, &d);
+    frame_from<SER == 0>(g, rsc_at<SER>(g, tab, an, i1, 0.0, dx1, i2, 0.0, dx2), &f, &d);
   }
-  const float qm = (float)species_sign(t);
+  const float qm = species_sign<float>(t);
   const float ms = (float)mass2_of(t);
   if (qm != 0.0f) {
-    const float D1 = interp<1, 0>(g, fp.D[0], i1, dx1, i2, dx2);
-    const float D2 = interp<0, 1>(g, fp.D[1], i1, dx1, i2, dx2);
-    const float D3 = interp<0, 0>(g, fp.D[2], i1, dx1, i2, dx2);
-    const float B1 = interp<0, 1>(g, fp.B[0], i1, dx1, i2, dx2);
-    const float B2 = interp<1, 0>(g, fp.B[1], i1, dx1, i2, dx2);
-    const float B3 = interp<1, 1>(g, fp.B[2], i1, dx1, i2, dx2);
+    float F[6];
+    gather(g, fp, i1, dx1, i2, dx2, F);
     const float al = f.c.alpha, ais11 = al * f.is11, k13 = f.c.hu13 * f.is11 * f.is11;
-    const float E[3] = {ais11 * D1, al * f.s22 * D2, al * f.s33 * (D3 - k13 * D1)};
-    const float B[3] = {ais11 * B1, al * f.s22 * B2, al * f.s33 * (B3 - k13 * B1)};
-    const float kb = 0.25f * qm * (float)g.dt;
+    const float E[3] = {ais11 * F[0], al * f.s22 * F[1], al * f.s33 * (F[2] - k13 * F[0])};
+    const float B[3] = {ais11 * F[3], al * f.s22 * F[4], al * f.s33 * (F[5] - k13 * F[3])};
+    const float kb = 0.25f * qm * g.uf.dt;
     em_half(f, E, B, kb, u1, u2, u3);
-    geodesic_u(g, f, d, u1, u2, u3, 1.0f);
+    geodesic_u<SER == 0>(g, f, d, u1, u2, u3, 1.0f);
     em_half(f, E, B, kb, u1, u2, u3);
   } else {
-    geodesic_u(g, f, d, u1, u2, u3, ms);  // EM stage skipped for q = 0
+    geodesic_u<SER == 0>(g, f, d, u1, u2, u3, ms);  // EM stage skipped for q = 0
   }
 
+  // the weight and phi, needed after the iterations: in flight during them
+  const float wt = elem(P.w, k), ph = elem(P.phi, k);
   float d1, d2;
   asm volatile("" : "+v"(i1), "+v"(i2));  // (the anchor again, as in push_one)
   an = anchor_at<SER>(g, tab, i1, i2, 0.0f);
   coordinate_update<SER>(g, tab, an, f.c, i1, dx1, i2, dx2, u1, u2, u3, ms, d1, d2, mv.vphi);
-  P.phi[k] += (float)g.dt * mv.vphi;
+  elem(P.phi, k) = ph + g.uf.dt * mv.vphi;
   dx1 += d1;
   renormalize(i1, dx1);
   dx2 += d2;
@@ -781,20 +805,20 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
   }
   if (i1 < 0 || i1 >= g.n_r) t |= kLeaving;
   if (!(fabsf(d1) < 1.0f && fabsf(d2) < 1.0f)) t = kInvalid;
-  P.i1[k] = i1;
-  P.i2[k] = i2;
-  P.dx1[k] = dx1;
-  P.dx2[k] = dx2;
-  P.u1[k] = u1;
-  P.u2[k] = u2;
-  P.u3[k] = u3;
-  P.tag[k] = t;
+  elem(P.i1, k) = i1;
+  elem(P.i2, k) = i2;
+  elem(P.dx1, k) = dx1;
+  elem(P.dx2, k) = dx2;
+  elem(P.u1, k) = u1;
+  elem(P.u2, k) = u2;
+  elem(P.u3, k) = u3;
+  elem(P.tag, k) = t;
   mv.dep = is_live(t) && qm != 0.0f;
   mv.ib = i1;
   mv.jb = i2;
   mv.xb = dx1;
   mv.yb = dx2;
-  mv.q = (float)(species_sign(t) * g.charge_scale) * P.w[k];
+  mv.q = (qm * g.uf.charge_scale) * wt;
   mv.u1 = u1;
   mv.u2 = u2;
   mv.u3 = u3;
@@ -804,29 +828,29 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
 
 // The move of slot k as stored by the push (previous and current position).
 template <class T>
-__device__ inline Move<T> load_move(const Grid& g, const ParticleArraysT<T>& P, int64_t k) {
+__device__ inline Move<T> load_move(const Grid& g, const ParticleArraysT<T>& P, uint32_t k) {
   Move<T> mv;
   mv.dep = false;
   mv.mid = false;
   mv.cell = g.n_r * g.n_th;
-  if (k >= P.n) return mv;
-  const uint8_t t = P.tag[k];
+  if ((int64_t)k >= P.n) return mv;
+  const uint8_t t = elem(P.tag, k);
   if (!is_live(t)) return mv;
-  const double sg = species_sign(t);
-  if (sg == 0.0) return mv;
+  const T sg = species_sign<T>(t);
+  if (sg == (T)0) return mv;
   mv.dep = true;
-  mv.q = (T)(sg * g.charge_scale) * P.w[k];
-  mv.ia = P.i1p[k];
-  mv.ja = P.i2p[k];
-  mv.xa = P.dx1p[k];
-  mv.ya = P.dx2p[k];
-  mv.ib = P.i1[k];
-  mv.jb = P.i2[k];
-  mv.xb = P.dx1[k];
-  mv.yb = P.dx2[k];
-  mv.u1 = P.u1[k];
-  mv.u2 = P.u2[k];
-  mv.u3 = P.u3[k];
+  mv.q = (sg * uni<T>(g).charge_scale) * elem(P.w, k);
+  mv.ia = elem(P.i1p, k);
+  mv.ja = elem(P.i2p, k);
+  mv.xa = elem(P.dx1p, k);
+  mv.ya = elem(P.dx2p, k);
+  mv.ib = elem(P.i1, k);
+  mv.jb = elem(P.i2, k);
+  mv.xb = elem(P.dx1, k);
+  mv.yb = elem(P.dx2, k);
+  mv.u1 = elem(P.u1, k);
+  mv.u2 = elem(P.u2, k);
+  mv.u3 = elem(P.u3, k);
   return mv;
 }
 
@@ -875,7 +899,8 @@ struct ContribT {
 template <int SER, class T>
 __device__ inline T vphi_mid(const Grid& g, const Tables& tab, int ia, T xm, int ja, T ym, T u1, T u2, T u3) {
   const AnchorT<T> an = anchor_at<SER>(g, tab, ia, ja, (T)0);
-  return velocity_from(g, rsc_at<SER>(g, tab, an, ia, xm, (T)0, ja, ym, (T)0), u1, u2, u3, (T)1).w3;
+  return velocity_from(g, rsc_at<SER>(g, tab, an, ia, (double)ia + (double)xm, xm, ja, (double)ja + (double)ym, ym), u1,
+                       u2, u3, (T)1).w3;
 }
 
 template <class T, int SER>
@@ -889,7 +914,7 @@ __device__ inline bool make_contrib(const Grid& g, const Tables& tab, const Move
       abs(di) > 1 || abs(dj) > 1)
     return false;
   const T q = mv.q;
-  const T qdt = q * (T)g.inv_dt;
+  const T qdt = q * uni<T>(g).inv_dt;
   const T one = (T)1, half = (T)0.5;
   const T xa = mv.xa, ya = mv.ya;
   const T xb = (T)di + mv.xb, yb = (T)dj + mv.yb;
@@ -1259,7 +1284,7 @@ static_assert((1 << (push_rank_bits<double>() - 1)) >= dep_block<double>(), "ran
 // stored by the fused pass).  The table was cleared at the start of the
 // kernel and a block barrier (the deposit's) has passed since.
 template <class T>
-__device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, int64_t k, int cell,
+__device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, uint32_t k, int cell,
                                   int* __restrict__ counts) {
   constexpr int kBits = push_rank_bits<T>();
   RankTable<kBits>& rt = block_rank_table<kBits>();
@@ -1267,7 +1292,7 @@ __device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, int64_t 
   if (cell < g.n_r * g.n_th) entry = rank_insert(rt, cell, local);
   __syncthreads();
   rank_claim<kBits, dep_block<T>()>(rt, counts);
-  if (entry >= 0) i1p[k] = rt.n[entry] + local;
+  if (entry >= 0) elem(i1p, k) = rt.n[entry] + local;
 }
 
 // ------------------------------------------------------------------ kernels
@@ -1276,24 +1301,25 @@ __device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, int64_t 
 // and the fourth wavefront hides more than the compiler's own choice (~160
 // VGPRs, 3 wavefronts, a 10-15 % slower pass); a fifth (96 VGPRs) spills
 // 148 B per lane and runs about 30 % slower.
+constexpr int kPushBlock = 256;
 #define GRPIC_FP64_PUSH_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4)))
 
 template <int SER>
-__global__ void __launch_bounds__(256) GRPIC_FP64_PUSH_OCCUPANCY
+__global__ void __launch_bounds__(kPushBlock) GRPIC_FP64_PUSH_OCCUPANCY
 push_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P) {
-  (void)push_one<SER>(g, tab, fp, P, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  (void)push_one<SER>(g, tab, fp, from_slot(P, (int64_t)blockIdx.x * kPushBlock), threadIdx.x);
 }
 
 template <int SER>
-__global__ void __launch_bounds__(256) push_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
+__global__ void __launch_bounds__(kPushBlock) push_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
                                                        ParticleArraysT<float> P) {
-  (void)push_one_f32<SER>(g, tab, fp, P, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  (void)push_one_f32<SER>(g, tab, fp, from_slot(P, (int64_t)blockIdx.x * kPushBlock), threadIdx.x);
 }
 
 template <class T, int SER>
 __global__ void __launch_bounds__(dep_block<T>()) deposit_kernel(Grid g, Tables tab, ParticleArraysT<T> P,
                                                             CurrentPlanesT<T> cp) {
-  const Move<T> mv = load_move(g, P, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+  const Move<T> mv = load_move(g, from_slot(P, (int64_t)blockIdx.x * dep_block<T>()), threadIdx.x);
   ContribT<T> c;
   const bool act = make_contrib<T, SER>(g, tab, mv, c);
   deposit_block(g, cp, act, c);
@@ -1306,13 +1332,13 @@ __global__ void __launch_bounds__(dep_block<T>()) deposit_kernel(Grid g, Tables 
 template <int SER, bool kRank>
 __global__ void __launch_bounds__(dep_block<double>()) GRPIC_FP64_PUSH_OCCUPANCY
 push_deposit_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp, int* counts) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * dep_block<double>());
   if constexpr (kRank) rank_clear(block_rank_table<push_rank_bits<double>()>());
-  const Move<double> mv = push_one<SER, false>(g, tab, fp, P, k);
+  const Move<double> mv = push_one<SER, false>(g, tab, fp, Q, threadIdx.x);
   ContribT<double> c;
   const bool act = make_contrib<double, SER>(g, tab, mv, c);
   deposit_block(g, cp, act, c);
-  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, P.i1p, k, mv.cell, counts);
+  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 // library path in FP64 (coarse grids and the general quasi-spherical map):
@@ -1322,32 +1348,32 @@ template <bool kRank>
 __global__ void __launch_bounds__(dep_block<double>()) __attribute__((amdgpu_waves_per_eu(3)))
 push_deposit_kernel_lib(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp,
                         int* counts) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * dep_block<double>());
   if constexpr (kRank) rank_clear(block_rank_table<push_rank_bits<double>()>());
-  const Move<double> mv = push_one<0, false>(g, tab, fp, P, k);
+  const Move<double> mv = push_one<0, false>(g, tab, fp, Q, threadIdx.x);
   ContribT<double> c;
   const bool act = make_contrib<double, 0>(g, tab, mv, c);
   deposit_block(g, cp, act, c);
-  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, P.i1p, k, mv.cell, counts);
+  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 template <int SER, bool kRank>
 __device__ inline void push_deposit_f32(const Grid& g, const Tables& tab, const GatherPlanesT<float>& fp,
                                         const ParticleArraysT<float>& P, const CurrentPlanesT<float>& cp,
                                         int* counts) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const ParticleArraysT<float> Q = from_slot(P, (int64_t)blockIdx.x * dep_block<float>());
   if constexpr (kRank) rank_clear(block_rank_table<push_rank_bits<float>()>());
-  const Move<float> mv = push_one_f32<SER, false>(g, tab, fp, P, k);
+  const Move<float> mv = push_one_f32<SER, false>(g, tab, fp, Q, threadIdx.x);
   ContribT<float> c;
   const bool act = make_contrib<float, SER>(g, tab, mv, c);
   deposit_block(g, cp, act, c);
-  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, P.i1p, k, mv.cell, counts);
+  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
-// series paths: 5 wavefronts per SIMD (96 VGPRs: the compiler's own
-// allocation without the rank pass; the rank pass would take it past 96)
+// series paths: 6 wavefronts per SIMD (80 VGPRs; the compiler's own allocation
+// takes a few more and 5 wavefronts, 1 to 2 % slower at 2048^2 with 16 per cell)
 template <int SER, bool kRank>
-__global__ void __launch_bounds__(dep_block<float>()) __attribute__((amdgpu_waves_per_eu(5))) push_deposit_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
+__global__ void __launch_bounds__(dep_block<float>()) __attribute__((amdgpu_waves_per_eu(6))) push_deposit_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
                                                                      ParticleArraysT<float> P,
                                                                      CurrentPlanesT<float> cp, int* counts) {
   push_deposit_f32<SER, kRank>(g, tab, fp, P, cp, counts);
