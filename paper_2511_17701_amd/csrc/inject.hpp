@@ -22,18 +22,31 @@ struct InjectArgs {
   int64_t first_free;
 };
 
-// Sum of the weights of the live, not leaving e+ and e- per cell.
+// Sum of the weights of the live, not leaving e+ and e- per cell.  Slots of
+// one cell in consecutive lanes (cell-sorted sets) are summed across the
+// wavefront first and their first lane adds: one FP64 atomic per slot on a
+// cell's counter, the former design, queued there (2.00 ms for 4.0e7 slots at
+// 24 per cell; with the run sums 0.21 ms).
 template <class T>
 __global__ void __launch_bounds__(256) inject_weights_kernel(Grid g, ParticleArraysT<T> P,
                                                              double* __restrict__ wsum) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= P.n) return;
-  const uint8_t t = P.tag[k];
-  const int s = t & 3;
-  if (t == 0 || (t & kLeaving) || (s != 1 && s != 2)) return;
-  const int i1 = P.i1[k], i2 = P.i2[k];
-  if (i1 < 0 || i1 >= g.n_r || i2 < 0 || i2 >= g.n_th) return;
-  atomicAdd(wsum + (int64_t)i1 * g.n_th + i2, (double)P.w[k]);
+  const ParticleArraysT<T> B = from_slot(P, (int64_t)blockIdx.x * 256);
+  const uint32_t k = threadIdx.x;
+  bool act = false;
+  int i1 = 0, i2 = 0;
+  double w = 0.0;
+  if ((int64_t)k < B.n) {
+    const uint8_t t = elem(B.tag, k);
+    i1 = elem(B.i1, k);
+    i2 = elem(B.i2, k);
+    w = (double)elem(B.w, k);
+    const int s = t & kSpecies;
+    act = t != 0 && !(t & kLeaving) && (s == 1 || s == 2) && i1 >= 0 && i1 < g.n_r && i2 >= 0 && i2 < g.n_th;
+  }
+  const int64_t c = (int64_t)i1 * g.n_th + i2;
+  const Runs r = runs_of(act ? (int)c : -1);
+  const double sum = run_sum(act ? w : 0.0, r);
+  if (act && r.head) atomicAdd(wsum + c, sum);
 }
 
 // Pairs injected by each cell: n_pairs where B_i B^i > 0 and
