@@ -335,7 +335,7 @@ template <bool kRank>
 void launch_push_deposit(grpic_ctx* c, const grpic_fields* F, const grpic_particles* P, int* counts,
                          hipStream_t s) {
   if (c->f32) {
-    constexpr int kBk = dep_block<float>();
+    constexpr int kBk = kDepBlock;
     const dim3 grid((unsigned)((P->n + kBk - 1) / kBk));
     GatherPlanesT<float> gp;
     for (int k = 0; k < 3; ++k) {
@@ -350,7 +350,7 @@ void launch_push_deposit(grpic_ctx* c, const grpic_fields* F, const grpic_partic
       default: hipLaunchKernelGGL((push_deposit_kernel_f32_lib<kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
     }
   } else {
-    constexpr int kBk = dep_block<double>();
+    constexpr int kBk = kDepBlock;
     const dim3 grid((unsigned)((P->n + kBk - 1) / kBk));
     GatherPlanesT<double> gp;
     for (int k = 0; k < 3; ++k) {
@@ -378,7 +378,7 @@ grpic_status push_deposit_impl(grpic_ctx* c, const grpic_fields* F, const grpic_
 template <class T>
 grpic_status deposit_impl(grpic_ctx* c, const grpic_particles* P, const grpic_fields* F, hipStream_t s) {
   CurrentPlanesT<T> cp{{(T*)F->J[0], (T*)F->J[1], (T*)F->J[2]}};
-  constexpr int kBk = dep_block<T>();
+  constexpr int kBk = kDepBlock;
   const dim3 grid((unsigned)((P->n + kBk - 1) / kBk));
   switch (c->g.ser) {
     case 2: hipLaunchKernelGGL((deposit_kernel<T, 2>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
@@ -572,7 +572,9 @@ grpic_status diagnostics_impl(grpic_ctx* c, const grpic_fields* F, const grpic_p
   hipLaunchKernelGGL(fill_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, Q, 0.0);
   LAUNCH_CHECK("fill");
   if (P->n > 0) {
-    hipLaunchKernelGGL(charge_kernel<T>, dim3(blocks(P->n)), dim3(kB), 0, s, g, arrays<T>(P), Q);
+    constexpr int64_t kSlots = kChargeBlock * kChargeChunks;
+    hipLaunchKernelGGL(charge_kernel<T>, dim3((unsigned)((P->n + kSlots - 1) / kSlots)), dim3(kChargeBlock), 0, s, g,
+                       arrays<T>(P), Q);
     LAUNCH_CHECK("charge");
   }
   {

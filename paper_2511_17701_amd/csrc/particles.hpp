@@ -248,14 +248,14 @@ __device__ inline void renormalize(int& i, R& dx) {
 
 // exp(t) for |t| <= 0.11: Taylor series to t^11 (remainder below 1e-20 relative)
 __device__ inline double exp_small(double t) {
-  double p = fma(t, 1.0 / 39916800.0, 1.0 / 3628800.0);
-  p = fma(t, p, 1.0 / 362880.0);
-  p = fma(t, p, 1.0 / 40320.0);
-  p = fma(t, p, 1.0 / 5040.0);
-  p = fma(t, p, 1.0 / 720.0);
-  p = fma(t, p, 1.0 / 120.0);
-  p = fma(t, p, 1.0 / 24.0);
-  p = fma(t, p, 1.0 / 6.0);
+  double p = fma_k(t, 1.0 / 39916800.0, 1.0 / 3628800.0);
+  p = fma_k(t, p, 1.0 / 362880.0);
+  p = fma_k(t, p, 1.0 / 40320.0);
+  p = fma_k(t, p, 1.0 / 5040.0);
+  p = fma_k(t, p, 1.0 / 720.0);
+  p = fma_k(t, p, 1.0 / 120.0);
+  p = fma_k(t, p, 1.0 / 24.0);
+  p = fma_k(t, p, 1.0 / 6.0);
   p = fma(t, p, 0.5);
   p = fma(t, p, 1.0);
   return fma(t, p, 1.0);
@@ -264,17 +264,17 @@ __device__ inline double exp_small(double t) {
 // sin and cos for |x| <= 0.11: Taylor series to x^13 and x^14
 __device__ inline void sincos_small(double x, double* s, double* c) {
   const double z = x * x;
-  double ps = fma(z, 1.0 / 6227020800.0, -1.0 / 39916800.0);
-  ps = fma(z, ps, 1.0 / 362880.0);
-  ps = fma(z, ps, -1.0 / 5040.0);
-  ps = fma(z, ps, 1.0 / 120.0);
-  ps = fma(z, ps, -1.0 / 6.0);
+  double ps = fma_k(z, 1.0 / 6227020800.0, -1.0 / 39916800.0);
+  ps = fma_k(z, ps, 1.0 / 362880.0);
+  ps = fma_k(z, ps, -1.0 / 5040.0);
+  ps = fma_k(z, ps, 1.0 / 120.0);
+  ps = fma_k(z, ps, -1.0 / 6.0);
   *s = fma(x * z, ps, x);
-  double pc = fma(z, -1.0 / 87178291200.0, 1.0 / 479001600.0);
-  pc = fma(z, pc, -1.0 / 3628800.0);
-  pc = fma(z, pc, 1.0 / 40320.0);
-  pc = fma(z, pc, -1.0 / 720.0);
-  pc = fma(z, pc, 1.0 / 24.0);
+  double pc = fma_k(z, -1.0 / 87178291200.0, 1.0 / 479001600.0);
+  pc = fma_k(z, pc, -1.0 / 3628800.0);
+  pc = fma_k(z, pc, 1.0 / 40320.0);
+  pc = fma_k(z, pc, -1.0 / 720.0);
+  pc = fma_k(z, pc, 1.0 / 24.0);
   pc = fma(z, pc, -0.5);
   *c = fma(z, pc, 1.0);
 }
@@ -869,15 +869,12 @@ __device__ inline void atomic_add(float* p, float v) { unsafeAtomicAdd(p, v); }
 // deposits J^1 and J^2 (normalised by 1/dt) on the edges of the cell it lies
 // in, with first-order weights at the segment midpoint; J^3 = q alpha u^3 /
 // gamma goes to the four nodes around the path midpoint.
-// Particles per block of the deposit passes and the LDS tile of kTI rows x
-// dep_tj<T>() columns: in single precision 64 (one wavefront, whose barriers
-// cost nothing), in double precision 128; the tile holds the footprints of
-// cells up to 2 rows and 6 columns from the anchor
-template <class T>
-constexpr int dep_block() { return sizeof(T) == 4 ? 64 : 128; }
-template <class T>
-constexpr int dep_tj() { return 16; }
-constexpr int kTI = 8;
+// Particles per block of the deposit passes (two wavefronts) and the LDS tile
+// of kTI rows x kTJ columns around the block's anchor cell, which holds the
+// footprints of cells up to 2 rows and 6 columns from it.  Blocks of 64 in
+// single precision: +1.6 % (2048^2, 16 per cell).
+constexpr int kDepBlock = 128;
+constexpr int kTI = 8, kTJ = 16;
 constexpr int kDepRep = 2;  // copies of the deposit tile
 
 // lapse-weighted phi velocity alpha u^3 / gamma at the path midpoint (ia + xm, ja + ym)
@@ -1032,41 +1029,25 @@ __device__ inline void lds_barrier() {
 }
 
 // The cell a block's tile is laid around: that of a live particle in the
-// middle of the block's slots (cell-sorted: near the middle of its cells).
-// Every thread of the block calls this; false if the block has no live one.
+// middle of the block's slots (cell-sorted: near the middle of its cells), the
+// second wavefront's first or else the first one's last.  Every thread of the
+// block (two wavefronts) calls this; false if the block has no live particle.
 // It passes a block barrier.
-template <int kBlk>
 __device__ inline bool block_anchor(bool act, int ia, int ja, int& ai, int& aj) {
-  constexpr int kWaves = kBlk / 64;
+  __shared__ int cell[2][2];
   const unsigned long long live = __ballot(act);
-  const int wv = kWaves == 1 ? 0 : (int)threadIdx.x >> 6;
-  // one wavefront: its first live lane from 32 on, else its last one before;
-  // several: the last live lane of those before the block's middle, the first
-  // of those after it
-  const unsigned long long high = live & ~0xffffffffull;
-  const bool first = kWaves == 1 ? high != 0 : wv >= kWaves / 2;
-  const unsigned long long from = kWaves == 1 && first ? high : live;
-  const int lane = first ? __ffsll((long long)from) - 1 : 63 - __clzll((long long)from);
+  const int wv = (int)threadIdx.x >> 6;
+  const int lane = wv ? __ffsll((long long)live) - 1 : 63 - __clzll((long long)live);
   const int wi = __builtin_amdgcn_readlane(ia, lane & 63), wj = __builtin_amdgcn_readlane(ja, lane & 63);
-  if constexpr (kWaves == 1) {
-    lds_barrier();
-    ai = wi;
-    aj = wj;
-    return live != 0;
-  } else {
-    static_assert(kWaves == 2, "the anchor is one of two wavefronts'");
-    __shared__ int cell[2][2];
-    if ((threadIdx.x & 63) == 0) {
-      cell[wv][0] = live ? wi : INT_MIN;
-      cell[wv][1] = wj;
-    }
-    lds_barrier();
-    int s = 1;
-    if (__builtin_amdgcn_readfirstlane(cell[1][0]) == INT_MIN) s = 0;
-    ai = __builtin_amdgcn_readfirstlane(cell[s][0]);
-    aj = __builtin_amdgcn_readfirstlane(cell[s][1]);
-    return ai != INT_MIN;
+  if ((threadIdx.x & 63) == 0) {
+    cell[wv][0] = live ? wi : INT_MIN;
+    cell[wv][1] = wj;
   }
+  lds_barrier();
+  const int s = __builtin_amdgcn_readfirstlane(cell[1][0]) != INT_MIN;
+  ai = __builtin_amdgcn_readfirstlane(cell[s][0]);
+  aj = __builtin_amdgcn_readfirstlane(cell[s][1]);
+  return ai != INT_MIN;
 }
 
 // Block-level deposit: the lanes add their contributions (12 values, 8 when a
@@ -1074,7 +1055,11 @@ __device__ inline bool block_anchor(bool act, int ia, int ja, int& ai, int& aj) 
 // block's anchor cell, in kDepRep copies between which the adding lanes
 // alternate (a cell's run of lanes then hits one address with half of its
 // lanes per copy); the tile is then added to the planes with one global atomic
-// per touched node.  Before the LDS atomics the two lanes of an aligned pair
+// per touched node.  The tile is in double precision in both forms: on gfx950 an
+// LDS add of 64 floats takes 194 cycles of the CU even without conflicts, one
+// of 64 doubles 9 (21, 93 and 193 with 2, 8 and 64 lanes on one address), and
+// the float adds bound the single-precision pass (2048^2, 16 per cell, ten
+// steps with the filter and a sort: 30.0 ms, with double adds 26.0).  Before the LDS atomics the two lanes of an aligned pair
 // that share their nodes are summed by DPP swaps, and only the first adds
 // (cell-sorted particles put runs of one cell in consecutive lanes).  A
 // particle whose footprint leaves the tile (its block's cells wrap from the end
@@ -1089,18 +1074,16 @@ __device__ inline bool block_anchor(bool act, int ia, int ja, int& ai, int& aj) 
 template <class T, int SER>
 __device__ inline void deposit_block(const Grid& g, const Tables& tab, const CurrentPlanesT<T>& cp, const Move<T>& mv,
                                      bool act) {
-  constexpr int kBlk = dep_block<T>(), kTJ = dep_tj<T>(), kPlane = kTI * kTJ;
-  __shared__ __align__(16) T tile[kDepRep][3][kPlane];
+  constexpr int kBlk = kDepBlock, kPlane = kTI * kTJ;
+  __shared__ __align__(16) double tile[kDepRep][3][kPlane];
   {  // zero the tile (16-byte stores)
-    constexpr int kVec = 16 / sizeof(T);
-    using V = typename std::conditional<sizeof(T) == 8, double2, float4>::type;
-    V* fv = reinterpret_cast<V*>(&tile[0][0][0]);
-    static_assert(kDepRep * 3 * kPlane % (kVec * kBlk) == 0, "whole stores per thread");
+    double2* fv = reinterpret_cast<double2*>(&tile[0][0][0]);
+    static_assert(kDepRep * 3 * kPlane % (2 * kBlk) == 0, "whole stores per thread");
 #pragma unroll
-    for (int e = 0; e < kDepRep * 3 * kPlane / kVec; e += kBlk) fv[e + (int)threadIdx.x] = V{};
+    for (int e = 0; e < kDepRep * 3 * kPlane / 2; e += kBlk) fv[e + (int)threadIdx.x] = double2{};
   }
   int ai, aj;
-  if (!block_anchor<kBlk>(act, mv.ia, mv.ja, ai, aj)) return;  // no live charged particle in this block (uniform)
+  if (!block_anchor(act, mv.ia, mv.ja, ai, aj)) return;  // no live charged particle in this block (uniform)
   const int i0 = ai - (kTI / 2 - 1), j0 = aj - (kTJ / 2 - 1);  // the tile's first row and column
   if (act) {
     const ContribT<T> c = make_contrib<T, SER>(g, tab, mv);
@@ -1127,26 +1110,26 @@ __device__ inline void deposit_block(const Grid& g, const Tables& tab, const Cur
     const bool own_a = !(fa & second), own_m = !(fm & second);
     const int row = mv.ia - 1 - i0, col = mv.ja - 1 - j0;  // the footprint's first row and column
     if ((unsigned)row <= (unsigned)(kTI - 4) && (unsigned)col <= (unsigned)(kTJ - 4)) {
-      T* t = &tile[(threadIdx.x >> 1) % kDepRep][0][0] + (row + 1) * kTJ + (col + 1);
+      double* t = &tile[(threadIdx.x >> 1) % kDepRep][0][0] + (row + 1) * kTJ + (col + 1);
       if (own_a) {
-        atomicAdd(t, a[0]);
-        atomicAdd(t + 1, a[1]);
-        atomicAdd(t + kPlane, a[2]);
-        atomicAdd(t + kPlane + kTJ, a[3]);
+        atomicAdd(t, (double)a[0]);
+        atomicAdd(t + 1, (double)a[1]);
+        atomicAdd(t + kPlane, (double)a[2]);
+        atomicAdd(t + kPlane + kTJ, (double)a[3]);
       }
       if (!stay) {
-        T* p = t + c.di * kTJ + c.dj;
-        atomicAdd(p, c.j1[2]);
-        atomicAdd(p + 1, c.j1[3]);
-        atomicAdd(p + kPlane, c.j2[2]);
-        atomicAdd(p + kPlane + kTJ, c.j2[3]);
+        double* p = t + c.di * kTJ + c.dj;
+        atomicAdd(p, (double)c.j1[2]);
+        atomicAdd(p + 1, (double)c.j1[3]);
+        atomicAdd(p + kPlane, (double)c.j2[2]);
+        atomicAdd(p + kPlane + kTJ, (double)c.j2[3]);
       }
       if (own_m) {
-        T* p = t + 2 * kPlane + corner;
-        atomicAdd(p, m[0]);
-        atomicAdd(p + 1, m[1]);
-        atomicAdd(p + kTJ, m[2]);
-        atomicAdd(p + kTJ + 1, m[3]);
+        double* p = t + 2 * kPlane + corner;
+        atomicAdd(p, (double)m[0]);
+        atomicAdd(p + 1, (double)m[1]);
+        atomicAdd(p + kTJ, (double)m[2]);
+        atomicAdd(p + kTJ + 1, (double)m[3]);
       }
     } else {
       const int64_t o = ix(g, mv.ia, mv.ja), ld = g.ld;
@@ -1181,10 +1164,10 @@ __device__ inline void deposit_block(const Grid& g, const Tables& tab, const Cur
   for (int comp = 0; comp < 3; ++comp) {
 #pragma unroll
     for (int e = 0; e < kPlane; e += kBlk) {
-      T val = tile[0][comp][e + threadIdx.x];
+      double val = tile[0][comp][e + threadIdx.x];
 #pragma unroll
       for (int r = 1; r < kDepRep; ++r) val += tile[r][comp][e + threadIdx.x];
-      if (val != (T)0) atomic_add(cp.J[comp] + (base + (int64_t)(e / kTJ) * g.ld) + off, val);
+      if (val != 0.0) atomic_add(cp.J[comp] + (base + (int64_t)(e / kTJ) * g.ld) + off, (T)val);
     }
   }
 }
@@ -1252,26 +1235,22 @@ __device__ inline void rank_claim(RankTable<kBits>& rt, int* __restrict__ counts
   __syncthreads();
 }
 
-// Table bits for the dep_block<T>() slots of a fused block: twice as many
-// cells as slots.
-template <class T>
-constexpr int push_rank_bits() { return sizeof(T) == 4 ? 7 : 8; }
-static_assert((1 << (push_rank_bits<float>() - 1)) >= dep_block<float>(), "rank table too small");
-static_assert((1 << (push_rank_bits<double>() - 1)) >= dep_block<double>(), "rank table too small");
+// Table bits for the slots of a fused block: twice as many cells as slots.
+constexpr int kPushRankBits = 8;
+static_assert((1 << (kPushRankBits - 1)) >= kDepBlock, "rank table too small");
 
 // The rank pass of the sort inside a fused push + deposit block: slot k's key
 // after the push is `cell`; its rank goes to i1p (the previous position is not
 // stored by the fused pass).  The table was cleared at the start of the
 // kernel and a block barrier (the deposit's) has passed since.
-template <class T>
 __device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, uint32_t k, int cell,
                                   int* __restrict__ counts) {
-  constexpr int kBits = push_rank_bits<T>();
+  constexpr int kBits = kPushRankBits;
   RankTable<kBits>& rt = block_rank_table<kBits>();
   int local = 0, entry = -1;
   if (cell < g.n_r * g.n_th) entry = rank_insert(rt, cell, local);
   __syncthreads();
-  rank_claim<kBits, dep_block<T>()>(rt, counts);
+  rank_claim<kBits, kDepBlock>(rt, counts);
   if (entry >= 0) elem(i1p, k) = rt.n[entry] + local;
 }
 
@@ -1297,9 +1276,9 @@ __global__ void __launch_bounds__(kPushBlock) push_kernel_f32(Grid g, Tables tab
 }
 
 template <class T, int SER>
-__global__ void __launch_bounds__(dep_block<T>()) deposit_kernel(Grid g, Tables tab, ParticleArraysT<T> P,
+__global__ void __launch_bounds__(kDepBlock) deposit_kernel(Grid g, Tables tab, ParticleArraysT<T> P,
                                                             CurrentPlanesT<T> cp) {
-  const Move<T> mv = load_move(g, from_slot(P, (int64_t)blockIdx.x * dep_block<T>()), threadIdx.x);
+  const Move<T> mv = load_move(g, from_slot(P, (int64_t)blockIdx.x * kDepBlock), threadIdx.x);
   deposit_block<T, SER>(g, tab, cp, mv, mv.dep && move_in_range(g, mv));
 }
 
@@ -1308,44 +1287,44 @@ __global__ void __launch_bounds__(dep_block<T>()) deposit_kernel(Grid g, Tables 
 // stored.  kRank: the pass also ranks the slots by their cell after the push
 // for the cell sort (rank_fused; counts: the sort's zeroed cell counters).
 template <int SER, bool kRank>
-__global__ void __launch_bounds__(dep_block<double>()) GRPIC_FP64_PUSH_OCCUPANCY
+__global__ void __launch_bounds__(kDepBlock) GRPIC_FP64_PUSH_OCCUPANCY
 push_deposit_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp, int* counts) {
-  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * dep_block<double>());
-  if constexpr (kRank) rank_clear(block_rank_table<push_rank_bits<double>()>());
+  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * kDepBlock);
+  if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<double> mv = push_one<SER, false>(g, tab, fp, Q, threadIdx.x);
   deposit_block<double, SER>(g, tab, cp, mv, mv.dep);
-  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, Q.i1p, threadIdx.x, mv.cell, counts);
+  if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 // library path in FP64 (coarse grids and the general quasi-spherical map):
 // the library exp and sincos and the map factors need more registers than the
 // series paths; three wavefronts per SIMD leave room for them without spills
 template <bool kRank>
-__global__ void __launch_bounds__(dep_block<double>()) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(3)))
 push_deposit_kernel_lib(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp,
                         int* counts) {
-  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * dep_block<double>());
-  if constexpr (kRank) rank_clear(block_rank_table<push_rank_bits<double>()>());
+  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * kDepBlock);
+  if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<double> mv = push_one<0, false>(g, tab, fp, Q, threadIdx.x);
   deposit_block<double, 0>(g, tab, cp, mv, mv.dep);
-  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, Q.i1p, threadIdx.x, mv.cell, counts);
+  if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 template <int SER, bool kRank>
 __device__ inline void push_deposit_f32(const Grid& g, const Tables& tab, const GatherPlanesT<float>& fp,
                                         const ParticleArraysT<float>& P, const CurrentPlanesT<float>& cp,
                                         int* counts) {
-  const ParticleArraysT<float> Q = from_slot(P, (int64_t)blockIdx.x * dep_block<float>());
-  if constexpr (kRank) rank_clear(block_rank_table<push_rank_bits<float>()>());
+  const ParticleArraysT<float> Q = from_slot(P, (int64_t)blockIdx.x * kDepBlock);
+  if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<float> mv = push_one_f32<SER, false>(g, tab, fp, Q, threadIdx.x);
   deposit_block<float, SER>(g, tab, cp, mv, mv.dep);
-  if constexpr (kRank) rank_fused<decltype(mv.u1)>(g, Q.i1p, threadIdx.x, mv.cell, counts);
+  if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 // series paths: 6 wavefronts per SIMD (80 VGPRs; the compiler's own allocation
 // takes a few more and 5 wavefronts, 1 to 2 % slower at 2048^2 with 16 per cell)
 template <int SER, bool kRank>
-__global__ void __launch_bounds__(dep_block<float>()) __attribute__((amdgpu_waves_per_eu(6))) push_deposit_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
+__global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(6))) push_deposit_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
                                                                      ParticleArraysT<float> P,
                                                                      CurrentPlanesT<float> cp, int* counts) {
   push_deposit_f32<SER, kRank>(g, tab, fp, P, cp, counts);
@@ -1355,7 +1334,7 @@ __global__ void __launch_bounds__(dep_block<float>()) __attribute__((amdgpu_wave
 // wavefronts per SIMD (a few spilled registers), 11 % faster than the 4 that
 // its 100 VGPRs would give
 template <bool kRank>
-__global__ void __launch_bounds__(dep_block<float>()) __attribute__((amdgpu_waves_per_eu(5)))
+__global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(5)))
 push_deposit_kernel_f32_lib(Grid g, Tables tab, GatherPlanesT<float> fp, ParticleArraysT<float> P,
                             CurrentPlanesT<float> cp, int* counts) {
   push_deposit_f32<0, kRank>(g, tab, fp, P, cp, counts);
