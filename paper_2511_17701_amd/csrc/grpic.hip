@@ -300,8 +300,16 @@ grpic_status monopole_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipSt
   return GRPIC_OK;
 }
 
+template <int SER>
+void launch_push(grpic_ctx* c, const GatherPlanesT<double>& gp, const grpic_particles* P, dim3 grid, hipStream_t s) {
+  if (c->g.n_iter > kCycleIter)
+    hipLaunchKernelGGL((push_kernel<SER, true>), grid, dim3(kPushBlock), 0, s, c->g, c->tab, gp, arrays<double>(P));
+  else
+    hipLaunchKernelGGL((push_kernel<SER, false>), grid, dim3(kPushBlock), 0, s, c->g, c->tab, gp, arrays<double>(P));
+}
+
 grpic_status push_impl(grpic_ctx* c, const grpic_fields* F, const grpic_particles* P, hipStream_t s) {
-  const dim3 grid(blocks(P->n));
+  const dim3 grid((unsigned)((P->n + kPushBlock - 1) / kPushBlock));
   if (c->f32) {
     GatherPlanesT<float> gp;
     for (int k = 0; k < 3; ++k) {
@@ -309,9 +317,9 @@ grpic_status push_impl(grpic_ctx* c, const grpic_fields* F, const grpic_particle
       gp.B[k] = (const float*)F->B0[k];
     }
     switch (c->g.ser) {
-      case 2: hipLaunchKernelGGL((push_kernel_f32<2>), grid, dim3(kB), 0, s, c->g, c->tab, gp, arrays<float>(P)); break;
-      case 1: hipLaunchKernelGGL((push_kernel_f32<1>), grid, dim3(kB), 0, s, c->g, c->tab, gp, arrays<float>(P)); break;
-      default: hipLaunchKernelGGL((push_kernel_f32<0>), grid, dim3(kB), 0, s, c->g, c->tab, gp, arrays<float>(P)); break;
+      case 2: hipLaunchKernelGGL((push_kernel_f32<2>), grid, dim3(kPushBlock), 0, s, c->g, c->tab, gp, arrays<float>(P)); break;
+      case 1: hipLaunchKernelGGL((push_kernel_f32<1>), grid, dim3(kPushBlock), 0, s, c->g, c->tab, gp, arrays<float>(P)); break;
+      default: hipLaunchKernelGGL((push_kernel_f32<0>), grid, dim3(kPushBlock), 0, s, c->g, c->tab, gp, arrays<float>(P)); break;
     }
   } else {
     GatherPlanesT<double> gp;
@@ -320,9 +328,9 @@ grpic_status push_impl(grpic_ctx* c, const grpic_fields* F, const grpic_particle
       gp.B[k] = (const double*)F->B0[k];
     }
     switch (c->g.ser) {
-      case 2: hipLaunchKernelGGL((push_kernel<2>), grid, dim3(kB), 0, s, c->g, c->tab, gp, arrays<double>(P)); break;
-      case 1: hipLaunchKernelGGL((push_kernel<1>), grid, dim3(kB), 0, s, c->g, c->tab, gp, arrays<double>(P)); break;
-      default: hipLaunchKernelGGL((push_kernel<0>), grid, dim3(kB), 0, s, c->g, c->tab, gp, arrays<double>(P)); break;
+      case 2: launch_push<2>(c, gp, P, grid, s); break;
+      case 1: launch_push<1>(c, gp, P, grid, s); break;
+      default: launch_push<0>(c, gp, P, grid, s); break;
     }
   }
   LAUNCH_CHECK("push");
