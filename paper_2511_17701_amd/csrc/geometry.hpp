@@ -87,11 +87,19 @@ struct Tables {
   const float* __restrict__ cf;
 };
 
+// The type of the constants that go with a value type (tangent.hpp: its
+// numbers take plain constants).
 template <class R>
-__host__ __device__ inline UniT<R> uni(const Grid& g) {
-  if constexpr (sizeof(R) == 4) return g.uf;
-  else return {R(g.a), R(g.a2), R(g.M), R(g.two_M), R(g.dxi), R(g.dth), R(g.inv_dth2),
-               R(g.dt), R(g.inv_dt), R(g.charge_scale), R(g.small_angle)};
+struct ScalarOf {
+  using type = R;
+};
+template <class R>
+using Scalar = typename ScalarOf<R>::type;
+
+template <class R>
+__host__ __device__ inline UniT<Scalar<R>> uni(const Grid& g) {
+  if constexpr (sizeof(Scalar<R>) == 4) return g.uf;
+  else return {g.a, g.a2, g.M, g.two_M, g.dxi, g.dth, g.inv_dth2, g.dt, g.inv_dt, g.charge_scale, g.small_angle};
 }
 
 // Element k of a table or array by a 32-bit byte offset from a uniform base
@@ -290,8 +298,10 @@ __host__ __device__ inline Coeffs coeffs_at(const Grid& g, double x1, double x2)
 template <bool kMap, class R>
 __host__ __device__ inline void frame_from(const Grid& g, RSCT<R> p, FrameT<R>* f, GradT<R>* d) {
   const R r = p.r, s = p.s, c = p.c, T = p.td, Rr = p.rd;
-  const UniT<R> U = uni<R>(g);
-  const R a = U.a, M = U.M, dxi = U.dxi, a2 = U.a2, r2 = r * r;
+  using S = Scalar<R>;
+  const UniT<S> U = uni<R>(g);
+  const S a = U.a, M = U.M, dxi = U.dxi, a2 = U.a2;
+  const R r2 = r * r;
   const R tMr = U.two_M * r;
   const R Sig = r2 + a2 * c * c;
   const R S2 = Sig + tMr;
@@ -318,24 +328,25 @@ __host__ __device__ inline void frame_from(const Grid& g, RSCT<R> p, FrameT<R>* 
   f->is33 = rS * gA * s * is2;
 
   // radial and polar derivatives of Sigma and A (S2 shares dSigma/dtheta)
-  const R dSig_t = (R)-2 * a2 * s * c;
-  const R dA_r = (R)4 * r * ra - a2 * s2 * ((R)2 * r - (R)2 * M);
+  const R dSig_t = (S)-2 * a2 * s * c;
+  const R dA_r = (S)4 * r * ra - a2 * s2 * ((S)2 * r - (S)2 * M);
   const R Tst = T * dSig_t;
   // alpha^2 = 1 - 2 M r / S2, beta^r = 2 M r / S2
   const R e = M * iS2 * iS2, ialpha = rS2 * g1;
-  const R a1 = ((R)2 * r2 - Sig) * e, b1 = Tst * r * e;
+  const R a1 = ((S)2 * r2 - Sig) * e, b1 = Tst * r * e;
   d->alpha[0] = Rr * a1 * ialpha;
   d->alpha[1] = b1 * ialpha;
-  d->beta1[0] = (R)-2 * a1 - dxi * f->c.beta1;
-  d->beta1[1] = (R)-2 * b1 * iR;
+  d->beta1[0] = (S)-2 * a1 - dxi * f->c.beta1;
+  d->beta1[1] = (S)-2 * b1 * iR;
   // h^11 = A / (Sigma S2 R^2)
-  const R dls = (R)2 * r * iSig;
-  d->l11[0] = Rr * (dA_r * iA - dls - (R)2 * (r + M) * iS2) - (R)2 * dxi;
+  const R dls = (S)2 * r * iSig;
+  d->l11[0] = Rr * (dA_r * iA - dls - (S)2 * (r + M) * iS2) - (S)2 * dxi;
   d->l11[1] = Tst * (Del * iA - iSig - iS2);  // dA/dtheta = Del dSigma/dtheta
   d->z[0] = Rr * dls;
   d->z[1] = Tst * iSig;
-  d->ct = (R)2 * T * c * s * is2;
-  d->tt = kMap ? (R)2 * p.dtd * T * p.itd2 : (R)0;
+  d->ct = (S)2 * T * c * s * is2;
+  if constexpr (kMap) d->tt = (S)2 * p.dtd * T * p.itd2;
+  else d->tt = R((S)0);
 }
 
 // Coordinate velocity of a particle at a point: v1 = alpha u^1 / gamma -
@@ -356,10 +367,13 @@ struct VelT {
 };
 
 template <class R>
-__device__ inline VelT<R> velocity_from(const Grid& g, RSCT<R> p, R u1, R u2, R u3, R mass2) {
+__device__ inline VelT<R> velocity_from(const Grid& g, RSCT<R> p, Scalar<R> u1, Scalar<R> u2, Scalar<R> u3,
+                                        Scalar<R> mass2) {
   const R r = p.r, s = p.s, c = p.c, Rr = p.rd;
-  const UniT<R> U = uni<R>(g);
-  const R a = U.a, a2 = U.a2, r2 = r * r;
+  using S = Scalar<R>;
+  const UniT<S> U = uni<R>(g);
+  const S a = U.a, a2 = U.a2, au3 = a * u3;
+  const R r2 = r * r;
   const R tMr = U.two_M * r;
   const R Sig = r2 + a2 * c * c;
   const R S2 = Sig + tMr;
@@ -370,9 +384,9 @@ __device__ inline VelT<R> velocity_from(const Grid& g, RSCT<R> p, R u1, R u2, R 
   const R q = rcp(Rr * x);
   const R iR = x * q, y = Rr * q;  // y = 1 / (S2 sin^2)
   const R iS2 = s2 * y, is2 = S2 * y;
-  const R p1 = u1 * iR, t3 = u3 * is2, au3 = a * u3;
+  const R p1 = u1 * iR, t3 = u3 * is2;
   const R Ap = A * p1;
-  const R B = mass2 * Sig + u2 * u2 * p.itd2 + (R)2 * au3 * p1 + u3 * t3;
+  const R B = mass2 * Sig + (u2 * u2) * p.itd2 + ((S)2 * au3) * p1 + u3 * t3;
   const R gi = rsqrt(S2 * B + Ap * p1);
   VelT<R> v;
   v.v1 = iR * iS2 * ((Ap + au3 * S2) * gi - tMr);

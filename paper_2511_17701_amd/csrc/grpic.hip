@@ -936,8 +936,13 @@ grpic_status grpic_push_adjoint(grpic_ctx* c, const grpic_fields* F, double B0, 
     gp.D[k] = (const double*)F->D[k];
     gp.B[k] = (const double*)F->B0[k];
   }
-  hipLaunchKernelGGL(push_adjoint_kernel, dim3((unsigned)((P->n + 63) / 64)), dim3(64), 0, S(stream), c->g, gp,
-                     1.0 / B0, arrays<double>(P), gbar_in, gbar_out, gbar_B0);
+  const dim3 grid((unsigned)((P->n + kAdjBlock - 1) / kAdjBlock)), block(kAdjBlock);
+  const ParticleArrays a = arrays<double>(P);
+  switch (c->g.ser) {
+    case 2: hipLaunchKernelGGL(push_adjoint_kernel<2>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;
+    case 1: hipLaunchKernelGGL(push_adjoint_kernel<1>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;
+    default: hipLaunchKernelGGL(push_adjoint_kernel<0>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;
+  }
   LAUNCH_CHECK("push_adjoint");
   return GRPIC_OK;
 }

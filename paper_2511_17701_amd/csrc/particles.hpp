@@ -168,8 +168,8 @@ __device__ inline void boris(R& ux, R& uy, R& uz, const R E[3], const R B[3], R 
 // adds it to the covariant u, so u carries one rounding per half step instead
 // of those of a full round trip through the tetrad (which would dominate the
 // error of the single-precision form over many steps).  Double precision
-// (and the adjoint's tangent numbers) take the whole vector back: the round
-// trip costs nothing visible there, and it keeps fewer values live.
+// takes the whole vector back: the round trip costs nothing visible there, and
+// it keeps fewer values live.
 template <class R>
 __device__ inline void em_half(const FrameT<R>& f, const R E[3], const R B[3], R k, R& u1, R& u2,
                                R& u3) {

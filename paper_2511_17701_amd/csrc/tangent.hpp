@@ -1,16 +1,11 @@
 // tangent.hpp -- FP64 value with N directional derivatives (forward-mode
-// tangents), for the per-step Jacobian of the adjoint.  The templated metric,
-// tetrad and Boris code of geometry.hpp / particles.hpp runs on it unchanged.
+// tangents), for the position derivatives of the metric in the adjoint.  The
+// templated metric code of geometry.hpp runs on it unchanged.
 #pragma once
 
 #include "geometry.hpp"
 
 namespace grpic {
-
-// the FP64 library functions stay visible next to the overloads below
-using ::exp;
-using ::sincos;
-using ::sqrt;
 
 template <int N>
 struct Tan {
@@ -22,14 +17,10 @@ struct Tan {
     for (int k = 0; k < N; ++k) d[k] = 0.0;
   }
 };
-
-// the k-th input variable with value x
 template <int N>
-__device__ inline Tan<N> seed(double x, int k) {
-  Tan<N> t(x);
-  t.d[k] = 1.0;
-  return t;
-}
+struct ScalarOf<Tan<N>> {
+  using type = double;
+};
 
 template <int N>
 __device__ inline Tan<N> operator+(const Tan<N>& a, const Tan<N>& b) {
@@ -63,6 +54,41 @@ __device__ inline Tan<N> operator*(const Tan<N>& a, const Tan<N>& b) {
   for (int k = 0; k < N; ++k) r.d[k] = a.d[k] * b.v + a.v * b.d[k];
   return r;
 }
+// with a constant: no operations on its zero tangents
+template <int N>
+__device__ inline Tan<N> operator*(double a, const Tan<N>& b) {
+  Tan<N> r;
+  r.v = a * b.v;
+#pragma unroll
+  for (int k = 0; k < N; ++k) r.d[k] = a * b.d[k];
+  return r;
+}
+template <int N>
+__device__ inline Tan<N> operator*(const Tan<N>& a, double b) {
+  return b * a;
+}
+template <int N>
+__device__ inline Tan<N> operator+(const Tan<N>& a, double b) {
+  Tan<N> r = a;
+  r.v = a.v + b;
+  return r;
+}
+template <int N>
+__device__ inline Tan<N> operator+(double a, const Tan<N>& b) {
+  return b + a;
+}
+template <int N>
+__device__ inline Tan<N> operator-(const Tan<N>& a, double b) {
+  Tan<N> r = a;
+  r.v = a.v - b;
+  return r;
+}
+template <int N>
+__device__ inline Tan<N> operator-(double a, const Tan<N>& b) {
+  Tan<N> r = -b;
+  r.v = a - b.v;
+  return r;
+}
 // x -> f(x) with f' = df at the value
 template <int N>
 __device__ inline Tan<N> chain(const Tan<N>& a, double f, double df) {
@@ -74,34 +100,13 @@ __device__ inline Tan<N> chain(const Tan<N>& a, double f, double df) {
 }
 template <int N>
 __device__ inline Tan<N> rcp(const Tan<N>& a) {
-  const double y = 1.0 / a.v;
+  const double y = rcp(a.v);
   return chain(a, y, -y * y);
 }
 template <int N>
-__device__ inline Tan<N> operator/(const Tan<N>& a, const Tan<N>& b) {
-  return a * rcp(b);
-}
-template <int N>
-__device__ inline Tan<N> sqrt(const Tan<N>& a) {
-  const double y = ::sqrt(a.v);
-  return chain(a, y, 0.5 / y);
-}
-template <int N>
 __device__ inline Tan<N> rsqrt(const Tan<N>& a) {
-  const double y = 1.0 / ::sqrt(a.v);
-  return chain(a, y, -0.5 * y / a.v);
-}
-template <int N>
-__device__ inline Tan<N> exp(const Tan<N>& a) {
-  const double y = ::exp(a.v);
-  return chain(a, y, y);
-}
-template <int N>
-__device__ inline void sincos(const Tan<N>& a, Tan<N>* s, Tan<N>* c) {
-  double sv, cv;
-  ::sincos(a.v, &sv, &cv);
-  *s = chain(a, sv, cv);
-  *c = chain(a, cv, -sv);
+  const double y = rsqrt(a.v);
+  return chain(a, y, -0.5 * y * (y * y));
 }
 
 }  // namespace grpic
