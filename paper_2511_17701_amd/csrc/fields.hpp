@@ -56,10 +56,11 @@ struct FW {
 // logarithmic-r, uniform-theta grid, with R = dxi r and T = deta.
 template <bool kQ>
 __device__ inline FW fw_tab(const Grid& g, const Tables& t, int i, int o1, int j, int o2) {
-  const double r = t.r[o1][i + g.ng], R = g.dxi * (kQ ? r - g.r0 : r);
-  const double s = t.s[o2][j + g.ng], c = t.c[o2][j + g.ng], is = t.is[o2][j + g.ng];
-  const double T = kQ ? t.td[o2][j + g.ng] : g.dth;
-  const double ird = kQ ? t.ird[o1][i + g.ng] * t.eta_t[o2][j + g.ng] : t.ird[o1][i + g.ng];  // 1/(R T)
+  const uint32_t ic = (uint32_t)(i + g.ng), jc = (uint32_t)(j + g.ng);
+  const double r = t.r[o1][ic], R = g.dxi * (kQ ? r - g.r0 : r);
+  const double s = elem(t.s[o2], jc), c = elem(t.c[o2], jc), is = elem(t.is[o2], jc);
+  const double T = kQ ? elem(t.td[o2], jc) : g.dth;
+  const double ird = kQ ? t.ird[o1][ic] * elem(t.eta_t[o2], jc) : t.ird[o1][ic];  // 1/(R T)
   const double a2 = g.a * g.a, r2 = r * r, tMr = 2.0 * g.M * r, s2 = s * s;
   const double Sig = r2 + a2 * c * c;
   const double S2 = Sig + tMr;
@@ -91,33 +92,18 @@ struct CTriT {
 using Tri = TriT<double>;
 using CTri = CTriT<double>;
 
-// X[o] += inc.  In the single-precision form the evolved fields D and B carry
-// a compensation plane L (null otherwise): X + L holds the running sum to about
-// 48 bits and X, what every reader sees, is its rounding to float, so rounding
-// errors of the time integration do not accumulate step after step.
-template <class T>
-__device__ inline void add_to(T* __restrict__ X, T* __restrict__ L, int64_t o, double inc) {
-  if (sizeof(T) == 4 && L) {
-    const double v = ((double)X[o] + (double)L[o]) + inc;
-    const T h = (T)v;
-    X[o] = h;
-    L[o] = (T)(v - (double)h);
-  } else {
-    X[o] = (T)((double)X[o] + inc);
-  }
+// The launch's row of a field-stage thread.  A block is 2 rows of 128 threads,
+// so a wavefront lies in one row: the row is made a scalar, with it the r
+// tables' values and the plane rows' addresses (pt).
+__device__ inline int launch_row() {
+  return __builtin_amdgcn_readfirstlane((int)(blockIdx.y * blockDim.y + threadIdx.y));
 }
+__device__ inline int launch_col() { return (int)(blockIdx.x * blockDim.x + threadIdx.x); }
 
-// Whole-plane thread index (ghosts included): j along theta, i along r.
-struct PlaneIdx {
-  int i, j;
-  bool ok;
-};
-__device__ inline PlaneIdx plane_idx(const Grid& g) {
-  PlaneIdx q;
-  q.j = (int)(blockIdx.x * blockDim.x + threadIdx.x) - g.ng;
-  q.i = (int)(blockIdx.y * blockDim.y + threadIdx.y) - g.ng;
-  q.ok = q.j < g.n_th + g.ng && q.i < g.n_r + g.ng;
-  return q;
+// Plane point (i, j): a scalar row base and a 32-bit column offset.
+template <class T>
+__device__ inline T& pt(const Grid& g, T* __restrict__ p, int i, int j) {
+  return elem(p + (int64_t)(i + g.ng) * g.ld, (uint32_t)(j + g.ng));
 }
 
 // ---------------------------------------------------------------- aux E, H
@@ -126,10 +112,8 @@ __device__ inline PlaneIdx plane_idx(const Grid& g) {
 // kE / kH select the outputs; both read the same B, D and share the weights.
 template <class T, bool kE, bool kH, bool kQ>
 __global__ void aux_kernel(Grid g, Tables t, CTriT<T> Bs, CTriT<T> Ds, TriT<T> E, TriT<T> H) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = blockIdx.y * blockDim.y + threadIdx.y - 1;
+  const int j = launch_col(), i = launch_row() - 1;
   if (j > g.n_th || i > g.n_r) return;
-  const int64_t o = ix(g, i, j), ld = g.ld;
   const bool half = j < g.n_th;  // theta-staggered components exist
   // weights at the points the stencils touch (unused ones are not computed)
   const FW n00 = fw_tab<kQ>(g, t, i, 0, j, 0);       // (i, j)
@@ -142,211 +126,223 @@ __global__ void aux_kernel(Grid g, Tables t, CTriT<T> Bs, CTriT<T> Ds, TriT<T> E
   const FW hm1 = fw_tab<kQ>(g, t, i - 1, 1, j, 1);   // (i-1/2, j+1/2)
   if (kE) {
     {  // E_1 (i+1/2, j)
-      const double av = (n00.w13 * Ds.p[2][o] + n10.w13 * Ds.p[2][o + ld]) * h00.h_sht;
-      E.p[0][o] = h00.alpha * (h00.hl11 * Ds.p[0][o] + av);
+      const double av = (n00.w13 * pt(g, Ds.p[2], i, j) + n10.w13 * pt(g, Ds.p[2], i + 1, j)) * h00.h_sht;
+      pt(g, E.p[0], i, j) = h00.alpha * (h00.hl11 * pt(g, Ds.p[0], i, j) + av);
     }
     {  // E_3 (i, j)
-      const double a1 = (hm0.w13 * Ds.p[0][o - ld] + h00.w13 * Ds.p[0][o]) * n00.h_sht;
-      const double a2 = (hm0.wb * Bs.p[1][o - ld] + h00.wb * Bs.p[1][o]) * n00.h_sht;
-      E.p[2][o] = n00.alpha * (n00.hl33 * Ds.p[2][o] + a1) + a2;
+      const double a1 = (hm0.w13 * pt(g, Ds.p[0], i - 1, j) + h00.w13 * pt(g, Ds.p[0], i, j)) * n00.h_sht;
+      const double a2 = (hm0.wb * pt(g, Bs.p[1], i - 1, j) + h00.wb * pt(g, Bs.p[1], i, j)) * n00.h_sht;
+      pt(g, E.p[2], i, j) = n00.alpha * (n00.hl33 * pt(g, Ds.p[2], i, j) + a1) + a2;
     }
     if (half) {  // E_2 (i, j+1/2)
-      const double a3 = (hm1.wb * Bs.p[2][o - ld] + h01.wb * Bs.p[2][o]) * n01.h_sht;
-      E.p[1][o] = n01.alpha * n01.hl22 * Ds.p[1][o] - a3;
+      const double a3 = (hm1.wb * pt(g, Bs.p[2], i - 1, j) + h01.wb * pt(g, Bs.p[2], i, j)) * n01.h_sht;
+      pt(g, E.p[1], i, j) = n01.alpha * n01.hl22 * pt(g, Ds.p[1], i, j) - a3;
     }
   }
   if (kH) {
     {  // H_2 (i+1/2, j)
-      const double a1 = (n00.wb * Ds.p[2][o] + n10.wb * Ds.p[2][o + ld]) * h00.h_sht;
-      H.p[1][o] = h00.alpha * h00.hl22 * Bs.p[1][o] + a1;
+      const double a1 = (n00.wb * pt(g, Ds.p[2], i, j) + n10.wb * pt(g, Ds.p[2], i + 1, j)) * h00.h_sht;
+      pt(g, H.p[1], i, j) = h00.alpha * h00.hl22 * pt(g, Bs.p[1], i, j) + a1;
     }
     if (half) {
       {  // H_1 (i, j+1/2)
-        const double a2 = (hm1.w13 * Bs.p[2][o - ld] + h01.w13 * Bs.p[2][o]) * n01.h_sht;
-        H.p[0][o] = n01.alpha * (n01.hl11 * Bs.p[0][o] + a2);
+        const double a2 = (hm1.w13 * pt(g, Bs.p[2], i - 1, j) + h01.w13 * pt(g, Bs.p[2], i, j)) * n01.h_sht;
+        pt(g, H.p[0], i, j) = n01.alpha * (n01.hl11 * pt(g, Bs.p[0], i, j) + a2);
       }
       {  // H_3 (i+1/2, j+1/2)
-        const double a3 = (n01.w13 * Bs.p[0][o] + n11.w13 * Bs.p[0][o + ld]) * h01.h_sht;
-        const double a4 = (n01.wb * Ds.p[1][o] + n11.wb * Ds.p[1][o + ld]) * h01.h_sht;
-        H.p[2][o] = h01.alpha * (h01.hl33 * Bs.p[2][o] + a3) - a4;
+        const double a3 = (n01.w13 * pt(g, Bs.p[0], i, j) + n11.w13 * pt(g, Bs.p[0], i + 1, j)) * h01.h_sht;
+        const double a4 = (n01.wb * pt(g, Ds.p[1], i, j) + n11.wb * pt(g, Ds.p[1], i + 1, j)) * h01.h_sht;
+        pt(g, H.p[2], i, j) = h01.alpha * (h01.hl33 * pt(g, Bs.p[2], i, j) + a3) - a4;
       }
-    }
-  }
-}
-
-// ---------------------------------------------------------------- Faraday
-// eq. discretized-faraday on the evolved ranges i in [0, n_r], j in [0, n_th].
-// With kSave the grid spans the whole plane and X0 <- X (the field before the
-// update, ghosts included) is taken in the same pass.
-template <class T, bool kSave, bool kQ>
-__global__ void faraday_kernel(Grid g, Tables t, TriT<T> X, TriT<T> L, CTriT<T> E, TriT<T> X0) {
-  int i, j;
-  if (kSave) {
-    const PlaneIdx q = plane_idx(g);
-    if (!q.ok) return;
-    i = q.i;
-    j = q.j;
-  } else {
-    j = blockIdx.x * blockDim.x + threadIdx.x;
-    i = blockIdx.y * blockDim.y + threadIdx.y;
-  }
-  const int64_t o = ix(g, i, j);
-  if (kSave) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) X0.p[c][o] = X.p[c][o];
-  }
-  if (i < 0 || j < 0 || j > g.n_th || i > g.n_r) return;
-  if (j < g.n_th) {
-    const double ish = fw_tab<kQ>(g, t, i, 0, j, 1).ish;
-    add_to(X.p[0], L.p[0], o, -(g.dt * (E.p[2][o + 1] - E.p[2][o]) * ish));
-  }
-  if (i < g.n_r && j >= 1 && j < g.n_th) {
-    const double ish = fw_tab<kQ>(g, t, i, 1, j, 0).ish;
-    add_to(X.p[1], L.p[1], o, g.dt * (E.p[2][o + g.ld] - E.p[2][o]) * ish);
-  }
-  if (i < g.n_r && j < g.n_th) {
-    const double ish = fw_tab<kQ>(g, t, i, 1, j, 1).ish;
-    const double curl = (E.p[1][o + g.ld] - E.p[1][o]) - (E.p[0][o + 1] - E.p[0][o]);
-    add_to(X.p[2], L.p[2], o, -(g.dt * curl * ish));
-  }
-}
-
-// ---------------------------------------------------------------- Ampere
-// eq. discretized-ampere with the current J = wa Ja + wb Jb; D^1 on the axis
-// rows from the polar-cap integral form (Sec. 3.3.2): cap area A_{i+1/2}, the
-// printed 2 pi with the two-sided (mirrored) axis-row current the deposit
-// leaves there; the theta = pi cap has the opposite orientation.
-// kFinal (the last half of the step): the grid spans the whole plane, the
-// current is Ja alone, and the same pass takes X0 <- X before the update and
-// rotates the currents after it: Jb <- Ja, and the deposit's accumulator is
-// zeroed (Jclear, or Ja itself when Jclear is null: the filter leaves the
-// filtered current in the scratch set or in the accumulator).
-template <class T, bool kFinal, bool kQ>
-__global__ void ampere_kernel(Grid g, Tables t, TriT<T> X, TriT<T> L, CTriT<T> H, TriT<T> Ja, TriT<T> Jb, double wa,
-                              double wb, double polar_k, TriT<T> X0, TriT<T> Jclear) {
-  int i, j;
-  if (kFinal) {
-    const PlaneIdx q = plane_idx(g);
-    if (!q.ok) return;
-    i = q.i;
-    j = q.j;
-  } else {
-    j = blockIdx.x * blockDim.x + threadIdx.x;
-    i = blockIdx.y * blockDim.y + threadIdx.y;
-  }
-  const int64_t o = ix(g, i, j);
-  if (kFinal) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) X0.p[c][o] = X.p[c][o];
-  }
-  if (!(i < 0 || j < 0 || j > g.n_th || i > g.n_r)) {
-    const double fpi = 4.0 * kPi;
-    auto cur = [&](int c) -> double {
-      return kFinal ? (double)Ja.p[c][o] : wa * Ja.p[c][o] + wb * Jb.p[c][o];
-    };
-    if (i < g.n_r) {
-      const double J1 = cur(0);
-      if (j >= 1 && j < g.n_th) {
-        const double ish = fw_tab<kQ>(g, t, i, 1, j, 0).ish;
-        add_to(X.p[0], L.p[0], o, g.dt * ((H.p[2][o] - H.p[2][o - 1]) - fpi * J1) * ish);
-      } else {
-        const double r = t.r[1][i + g.ng];
-        const double ra = r * r + g.a * g.a;
-        const double Ap = g.dxi * (kQ ? r - g.r0 : r) * ra * sqrt(1.0 + 2.0 * g.M * r / ra) * polar_k;
-        const double h3 = (j == 0) ? H.p[2][o] : -H.p[2][o - 1];
-        add_to(X.p[0], L.p[0], o, g.dt * (h3 - 2.0 * kPi * J1) / Ap);
-      }
-    }
-    if (j < g.n_th) {
-      const double ish = fw_tab<kQ>(g, t, i, 0, j, 1).ish;
-      const double J2 = cur(1);
-      add_to(X.p[1], L.p[1], o, g.dt * (-(H.p[2][o] - H.p[2][o - g.ld]) - fpi * J2) * ish);
-    }
-    if (j >= 1 && j < g.n_th) {
-      const double ish = fw_tab<kQ>(g, t, i, 0, j, 0).ish;
-      const double J3 = cur(2);
-      const double curl = (H.p[1][o] - H.p[1][o - g.ld]) - (H.p[0][o] - H.p[0][o - 1]);
-      add_to(X.p[2], L.p[2], o, g.dt * (curl - fpi * J3) * ish);
-    }
-  }
-  if (kFinal) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      Jb.p[c][o] = Ja.p[c][o];
-      (Jclear.p[0] ? Jclear.p[c] : Ja.p[c])[o] = 0.0;
     }
   }
 }
 
 // ---------------------------------------------------------------- boundaries
-// The radial conditions (bc_radial_kernel), then the axis (bc_axis_kernel):
-//  - constant layer inside the horizon (rows i <= n_f take row n_f + 1) and
-//    the absorbing layer (F <- F - lambda (F - F_init), lambda a cubic ramp
-//    over the last n_absorb cells), on every column;  half1[c] = staggering of
-//    component c in x1;
+// An updated triple X and what its boundary conditions need:
+//  - constant layer inside the horizon: rows i <= n_f take row n_f + 1;
+//  - absorbing layer: F <- F - lambda (F - F_init), lambda a cubic ramp over
+//    the last n_absorb cells (and beyond);
 //  - axis reflection (Sec. 3.3.3): r-components even, theta and phi
-//    components odd, ghost columns from the row's updated values; with
-//    zero_comp, the theta component of B (B^2) or the phi component of D (D^3)
-//    vanishes on the axis rows.  half2[c] = staggering in x2.
-// Rows i <= n_f read row n_f + 1, which neither layer changes.  Initial data
-// take only the axis reflection.
-
-// Rows of the two layers: the horizon rows [-ng, n_f] and the absorbing rows
-// [abs_begin, n_r + ng) (a row in both is a horizon row).
-struct BcRows {
-  int n_hor, n_abs;  // number of horizon / absorbing rows
-  int abs_begin;     // first absorbing row
+//    components odd; the component `zero` (B^2, D^3) vanishes on the axis rows.
+// L: in the single-precision form the evolved fields D and B carry a
+// compensation plane (null otherwise): X + L holds the running sum to about 48
+// bits and X, what every reader sees, is its rounding to float, so rounding
+// errors of the time integration do not accumulate step after step.
+// S: receives X as it was before the update, ghosts included (null: not kept).
+template <class T>
+struct UpdateT {
+  TriT<T> X, L;
+  CTriT<T> X0;  // targets of the absorbing layer
+  TriT<T> S;
+  int3 half1, half2;  // staggering of the components in x1, x2
+  int zero;
 };
 
-__host__ __device__ inline BcRows bc_rows(const Grid& g) {
-  BcRows b;
-  const int top = g.n_r + g.ng;                  // one past the last plane row
-  const int hor_end = min(g.n_filter + 1, top);  // horizon rows: i <= n_f
-  b.abs_begin = g.n_absorb > 0 ? max(hor_end, g.n_r - g.n_absorb) : top;
-  b.n_hor = hor_end + g.ng;
-  b.n_abs = top - b.abs_begin;
-  return b;
+// The compensation of component c at a point.
+template <class T>
+__device__ inline double comp_at(const Grid& g, const UpdateT<T>& u, int c, int i, int j) {
+  return sizeof(T) == 4 && u.L.p[0] ? (double)pt(g, u.L.p[c], i, j) : 0.0;
 }
 
-// One thread per (layer row, stored column): grid (ceil(ld / 256), n_hor +
-// n_abs), 256 threads.
+// Stores v, the updated component c at (i, j), i > n_f, j an interior column of
+// the component, through the boundary conditions.  The thread that owns the
+// point also writes the ghost columns that mirror it and, from row n_f + 1, the
+// horizon rows (and saves what was there): every stored value has one writer
+// and no reader among the other threads, so an update and its boundaries are one
+// pass.  was: the stored value before (the update's kernels load everything
+// before their first store).  As passes of their own (two launches per updated triple, eight per
+// step) they took 38 us of a 354 us step at 512^2 and 24 of 79 at 40 x 56.
+// Five steps of the field stages at 1537 x 1023 in double precision: 1912 ->
+// 1707 us, of which the scalar rows give 40 and the loads ahead of the stores 100.
 template <class T>
-__global__ void bc_radial_kernel(Grid g, TriT<T> X, TriT<T> L, CTriT<T> X0, int3 half1) {
-  const BcRows rows = bc_rows(g);
-  const int r = (int)blockIdx.y;
-  const bool horizon = r < rows.n_hor;
-  const int i = horizon ? r - g.ng : rows.abs_begin + (r - rows.n_hor);
-  const int j = (int)(blockIdx.x * blockDim.x + threadIdx.x) - g.ng;
-  if (j >= g.n_th + g.ng) return;
-  const int h1[3] = {half1.x, half1.y, half1.z};
-  const bool comp = sizeof(T) == 4 && L.p[0];
-  const double x0 = (double)(g.n_r - g.n_absorb);
-  const int64_t o = ix(g, i, j);
+__device__ inline void store_bc(const Grid& g, const UpdateT<T>& u, int c, int i, int j, double v, T was) {
+  T* const X = u.X.p[c];
+  T* const S = u.S.p[0] ? u.S.p[c] : nullptr;
+  const bool comp = sizeof(T) == 4 && u.L.p[0];
+  const int h1 = c == 0 ? u.half1.x : c == 1 ? u.half1.y : u.half1.z;
+  const int h2 = c == 0 ? u.half2.x : c == 1 ? u.half2.y : u.half2.z;
+  const int n = g.n_th;
+  if (g.n_absorb > 0) {
+    const double x = (double)i + 0.5 * h1, x0 = (double)(g.n_r - g.n_absorb);
+    if (x > x0) {
+      const double sr = fmin((x - x0) / g.n_absorb, 1.0);
+      const double lam = sr * sr * sr;
+      v = v - lam * (v - (double)pt(g, u.X0.p[c], i, j));
+    }
+  }
+  if (c == u.zero && (j == 0 || j == n)) v = 0.0;
+  const T h = (T)v, l = (T)(v - (double)h);
+  if (S) pt(g, S, i, j) = was;
+  pt(g, X, i, j) = h;
+  if (comp) pt(g, u.L.p[c], i, j) = l;
+  // column q of the rows [first, last], a few at a time (their loads together)
+  auto put = [&](int first, int last, int q, T w) {
+    constexpr int kRows = 4;
+    for (int r0 = first; r0 <= last; r0 += kRows) {
+      T old[kRows];
+      if (S) {
+#pragma unroll
+        for (int e = 0; e < kRows; ++e)
+          if (r0 + e <= last) old[e] = pt(g, X, r0 + e, q);
+      }
+#pragma unroll
+      for (int e = 0; e < kRows; ++e)
+        if (r0 + e <= last) {
+          if (S) pt(g, S, r0 + e, q) = old[e];
+          pt(g, X, r0 + e, q) = w;
+        }
+    }
+  };
+  const bool edge = i == g.n_filter + 1;  // the row that the horizon rows take
+  if (edge) {
+    put(-g.ng, i - 1, j, h);
+    if (comp)
+      for (int r = -g.ng; r < i; ++r) pt(g, u.L.p[c], r, j) = l;
+  }
+  // the ghost column that mirrors column j
+  const int lo = h2 ? j : j - 1;  // 0: column -1, 1: column -2
+  const int hi = n - 1 - j;       // half: 0: column n, 1: column n + 1; node: 0: column n + 1
+  const bool low = lo == 0 || lo == 1, high = h2 ? hi == 0 || hi == 1 : hi == 0;
+  if (low | high) put(edge ? -g.ng : i, i, low ? -1 - lo : h2 ? n + hi : n + 1, c == 0 ? h : -h);
+}
+
+// ---------------------------------------------------------------- Faraday
+// eq. discretized-faraday on the evolved ranges i in [0, n_r], j in [0, n_th],
+// and the boundaries of the updated triple; one thread per point of the rows
+// n_f < i < n_r + ng and the columns [0, n_th].  kPre: the triple is averaged
+// with A first, X <- (X + A)/2 + update (Sec. 3.4, step 2).
+template <class T, bool kPre, bool kQ>
+__global__ void faraday_kernel(Grid g, Tables t, UpdateT<T> u, CTriT<T> E, CTriT<T> A) {
+  const int j = launch_col(), i = launch_row() + g.n_filter + 1;
+  if (j > g.n_th || i >= g.n_r + g.ng) return;
+  T was[3];
+  double v[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    if (horizon) {
-      const int64_t src = ix(g, g.n_filter + 1, j);
-      X.p[c][o] = X.p[c][src];
-      if (comp) L.p[c][o] = L.p[c][src];
-    } else {
-      const double x = (double)i + 0.5 * h1[c];
-      if (x > x0) {
-        const double sr = fmin((x - x0) / g.n_absorb, 1.0);
-        const double lam = sr * sr * sr;
-        if (comp) {
-          const double v = (double)X.p[c][o] + (double)L.p[c][o];
-          const double w = v - lam * (v - X0.p[c][o]);
-          const T h = (T)w;
-          X.p[c][o] = h;
-          L.p[c][o] = (T)(w - (double)h);
+    was[c] = pt(g, u.X.p[c], i, j);
+    v[c] = kPre ? 0.5 * ((double)was[c] + (double)pt(g, A.p[c], i, j)) : (double)was[c] + comp_at(g, u, c, i, j);
+  }
+  const bool half = j < g.n_th;  // theta-staggered components exist
+  if (i <= g.n_r) {
+    const bool below = i < g.n_r;
+    const double e3 = (double)pt(g, E.p[2], i, j);
+    if (half) v[0] -= g.dt * ((double)pt(g, E.p[2], i, j + 1) - e3) * fw_tab<kQ>(g, t, i, 0, j, 1).ish;
+    if (below && j >= 1 && half) v[1] += g.dt * ((double)pt(g, E.p[2], i + 1, j) - e3) * fw_tab<kQ>(g, t, i, 1, j, 0).ish;
+    if (below && half) {
+      const double curl = ((double)pt(g, E.p[1], i + 1, j) - (double)pt(g, E.p[1], i, j)) -
+                          ((double)pt(g, E.p[0], i, j + 1) - (double)pt(g, E.p[0], i, j));
+      v[2] -= g.dt * curl * fw_tab<kQ>(g, t, i, 1, j, 1).ish;
+    }
+  }
+  if (half) store_bc(g, u, 0, i, j, v[0], was[0]);
+  store_bc(g, u, 1, i, j, v[1], was[1]);
+  if (half) store_bc(g, u, 2, i, j, v[2], was[2]);
+}
+
+// ---------------------------------------------------------------- Ampere
+// eq. discretized-ampere with the current J = wa Ja + wb Jb, and the boundaries
+// of the updated triple; D^1 on the axis rows from the polar-cap integral form
+// (Sec. 3.3.2): cap area A_{i+1/2}, the printed 2 pi with the two-sided
+// (mirrored) axis-row current the deposit leaves there; the theta = pi cap has
+// the opposite orientation.  kFinal (the last half of the step): the grid spans
+// the whole plane, the current is Ja alone, and the same pass rotates the
+// currents: Jb <- Ja, and the deposit's accumulator is zeroed (Jclear, or Ja
+// itself when Jclear is null: the filter leaves the filtered current in the
+// scratch set or in the accumulator).
+template <class T, bool kFinal, bool kQ>
+__global__ void ampere_kernel(Grid g, Tables t, UpdateT<T> u, CTriT<T> H, TriT<T> Ja, TriT<T> Jb, double wa, double wb,
+                              double polar_k, TriT<T> Jclear) {
+  const int j = launch_col() - (kFinal ? g.ng : 0), i = launch_row() + (kFinal ? -g.ng : g.n_filter + 1);
+  if (j >= g.n_th + g.ng || i >= g.n_r + g.ng) return;
+  T ja[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) ja[c] = pt(g, Ja.p[c], i, j);
+  if (i > g.n_filter && j >= 0 && j <= g.n_th) {
+    T was[3];
+    double v[3], J[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      was[c] = pt(g, u.X.p[c], i, j);
+      v[c] = (double)was[c] + comp_at(g, u, c, i, j);
+      J[c] = kFinal ? (double)ja[c] : wa * (double)ja[c] + wb * (double)pt(g, Jb.p[c], i, j);
+    }
+    const double fpi = 4.0 * kPi;
+    const bool half = j < g.n_th;  // theta-staggered components exist
+    if (i <= g.n_r) {
+      const double h3 = (double)pt(g, H.p[2], i, j);
+      if (i < g.n_r) {
+        const double h3m = (double)pt(g, H.p[2], i, j - 1);
+        if (j >= 1 && half) {
+          v[0] += g.dt * ((h3 - h3m) - fpi * J[0]) * fw_tab<kQ>(g, t, i, 1, j, 0).ish;
         } else {
-          X.p[c][o] = X.p[c][o] - lam * (X.p[c][o] - X0.p[c][o]);
+          const double r = t.r[1][i + g.ng];
+          const double ra = r * r + g.a * g.a;
+          const double Ap = g.dxi * (kQ ? r - g.r0 : r) * ra * sqrt(1.0 + 2.0 * g.M * r / ra) * polar_k;
+          v[0] += g.dt * ((j == 0 ? h3 : -h3m) - 2.0 * kPi * J[0]) / Ap;
         }
       }
+      if (half) v[1] += g.dt * (-(h3 - (double)pt(g, H.p[2], i - 1, j)) - fpi * J[1]) * fw_tab<kQ>(g, t, i, 0, j, 1).ish;
+      if (j >= 1 && half) {
+        const double curl = ((double)pt(g, H.p[1], i, j) - (double)pt(g, H.p[1], i - 1, j)) -
+                            ((double)pt(g, H.p[0], i, j) - (double)pt(g, H.p[0], i, j - 1));
+        v[2] += g.dt * (curl - fpi * J[2]) * fw_tab<kQ>(g, t, i, 0, j, 0).ish;
+      }
+    }
+    store_bc(g, u, 0, i, j, v[0], was[0]);
+    if (half) store_bc(g, u, 1, i, j, v[1], was[1]);
+    store_bc(g, u, 2, i, j, v[2], was[2]);
+  }
+  if (kFinal) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      pt(g, Jb.p[c], i, j) = ja[c];
+      pt(g, Jclear.p[0] ? Jclear.p[c] : Ja.p[c], i, j) = 0.0;
     }
   }
 }
 
+// ---------------------------------------------------------------- axis reflection of initial data
 // 6 ng lanes per plane row, one per (component, ghost column): bc_axis_rows
 // rows per block of `threads`.
 __host__ __device__ inline int bc_axis_rows(const Grid& g, int threads) { return threads / (6 * g.ng); }
@@ -356,13 +352,12 @@ __host__ __device__ inline int bc_axis_rows(const Grid& g, int threads) { return
 // 0..n-1); the mirrors are interior columns, which this pass only zeroes at
 // j = 0, n for zero_comp, and never reads.
 template <class T>
-__global__ void bc_axis_kernel(Grid g, TriT<T> X, TriT<T> L, int3 half2, int zero_comp) {
+__global__ void bc_axis_kernel(Grid g, TriT<T> X, int3 half2, int zero_comp) {
   const int lanes = 6 * g.ng, rpb = bc_axis_rows(g, (int)blockDim.x);
   const int t = (int)threadIdx.x;
   const int i = (int)blockIdx.x * rpb + t / lanes - g.ng;
   if (t >= rpb * lanes || i >= g.n_r + g.ng) return;
   const int h2[3] = {half2.x, half2.y, half2.z};
-  const bool comp = sizeof(T) == 4 && L.p[0];
   const int c = (t % lanes) / (2 * g.ng), q = (t % lanes) % (2 * g.ng);
   const int n = g.n_th;
   T* C = X.p[c];
@@ -374,22 +369,17 @@ __global__ void bc_axis_kernel(Grid g, TriT<T> X, TriT<T> L, int3 half2, int zer
   if (!h2[c] && c == zero_comp && (q == 0 || q == g.ng)) {
     const int jz = q == 0 ? 0 : n;
     C[ix(g, i, jz)] = 0.0;
-    if (comp) L.p[c][ix(g, i, jz)] = 0.0;
   }
 }
 
 // ---------------------------------------------------------------- misc
 // elementwise over whole planes (ghosts included)
 template <class T>
-__global__ void average_kernel(int64_t n, TriT<T> A, CTriT<T> B, TriT<T> C, CTriT<T> D) {
-  // A <- (A + B) / 2, C <- (C + D) / 2
+__global__ void average_kernel(int64_t n, TriT<T> A, CTriT<T> B) {  // A <- (A + B) / 2
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    A.p[c][k] = 0.5 * (A.p[c][k] + B.p[c][k]);
-    C.p[c][k] = 0.5 * (C.p[c][k] + D.p[c][k]);
-  }
+  for (int c = 0; c < 3; ++c) A.p[c][k] = 0.5 * (A.p[c][k] + B.p[c][k]);
 }
 
 template <class T>

@@ -166,23 +166,22 @@ const dim3 kBlock2(128, 2);
 const int3 kStagD1 = {1, 0, 0}, kStagD2 = {0, 1, 0};  // x1 / x2 staggering of D^i, J^i
 const int3 kStagB1 = {0, 1, 1}, kStagB2 = {1, 0, 1};  // x1 / x2 staggering of B^i
 
-// boundaries of an updated triple: horizon layer + absorbing layer (radial =
-// 1), then the axis
+// axis reflection of a triple of initial data
 template <class T>
-grpic_status field_bc(grpic_ctx* c, TriT<T> X, TriT<T> L, CTriT<T> X0, bool is_B, hipStream_t s,
-                      int radial = 1) {
+grpic_status axis_bc(grpic_ctx* c, TriT<T> X, bool is_B, hipStream_t s) {
   const Grid& g = c->g;
-  const BcRows rows = bc_rows(g);
-  if (radial && rows.n_hor + rows.n_abs > 0) {
-    const dim3 grid((unsigned)((g.ld + kB - 1) / kB), (unsigned)(rows.n_hor + rows.n_abs));
-    hipLaunchKernelGGL(bc_radial_kernel<T>, grid, dim3(kB), 0, s, g, X, L, X0, is_B ? kStagB1 : kStagD1);
-    LAUNCH_CHECK("bc_radial");
-  }
   const int rpb = bc_axis_rows(g, kB);
   hipLaunchKernelGGL(bc_axis_kernel<T>, dim3((unsigned)((g.n_r + 2 * g.ng + rpb - 1) / rpb)), dim3(kB), 0, s, g, X,
-                     L, is_B ? kStagB2 : kStagD2, is_B ? 1 : 2);
+                     is_B ? kStagB2 : kStagD2, is_B ? 1 : 2);
   LAUNCH_CHECK("bc_axis");
   return GRPIC_OK;
+}
+
+// An updated triple with its boundary conditions (X0: absorbing targets; S:
+// where the triple before the update goes)
+template <class T>
+UpdateT<T> update_of(TriT<T> X, TriT<T> L, CTriT<T> X0, TriT<T> S, bool is_B) {
+  return UpdateT<T>{X, L, X0, S, is_B ? kStagB1 : kStagD1, is_B ? kStagB2 : kStagD2, is_B ? 1 : 2};
 }
 
 // n_f binomial passes (Sec. 3.3.4) over the ncomp planes of A, up to
@@ -264,8 +263,8 @@ grpic_status wald_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipStream
                      tri<T>(F->D), tri<T>(F->B), B0);
   LAUNCH_CHECK("wald");
   grpic_status st;
-  if ((st = field_bc<T>(c, tri<T>(F->D), none<T>(), ctri<T>(F->Dinit), false, s, 0))) return st;
-  if ((st = field_bc<T>(c, tri<T>(F->B), none<T>(), ctri<T>(F->Binit), true, s, 0))) return st;
+  if ((st = axis_bc<T>(c, tri<T>(F->D), false, s))) return st;
+  if ((st = axis_bc<T>(c, tri<T>(F->B), true, s))) return st;
   void* const* dst[4] = {F->D0, F->B0, F->Dinit, F->Binit};
   void* const* src[4] = {F->D, F->B, F->D, F->B};
   for (int k = 0; k < 4; ++k) {
@@ -288,8 +287,8 @@ grpic_status monopole_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipSt
                      (T*)F->B[0], B0);
   LAUNCH_CHECK("monopole");
   grpic_status st;
-  if ((st = field_bc<T>(c, tri<T>(F->D), none<T>(), ctri<T>(F->Dinit), false, s, 0))) return st;
-  if ((st = field_bc<T>(c, tri<T>(F->B), none<T>(), ctri<T>(F->Binit), true, s, 0))) return st;
+  if ((st = axis_bc<T>(c, tri<T>(F->D), false, s))) return st;
+  if ((st = axis_bc<T>(c, tri<T>(F->B), true, s))) return st;
   void* const* dst[4] = {F->D0, F->B0, F->Dinit, F->Binit};
   void* const* src[4] = {F->D, F->B, F->D, F->B};
   for (int k = 0; k < 4; ++k) {
@@ -491,20 +490,20 @@ grpic_status field_advance_impl(grpic_ctx* c, const grpic_fields* F, int32_t sta
   grpic_status st;
   const Grid& g = c->g;
   const dim3 gaux = grid2(g.n_r + 2, g.n_th + 1);   // i in [-1, n_r], j in [0, n_th]
-  const dim3 gupd = grid2(g.n_r + 1, g.n_th + 1);   // i in [0, n_r],  j in [0, n_th]
+  const dim3 gupd = grid2(g.n_r + g.ng - (g.n_filter + 1), g.n_th + 1);  // rows (n_f, n_r + ng), columns [0, n_th]
   const dim3 gpl2 = grid2(g.n_r + 2 * g.ng, g.n_th + 2 * g.ng);  // whole plane
   if (stage == GRPIC_FIELDS_PRE_PUSH) {
-    // B0 <- (B0 + B)/2, D0 <- (D0 + D)/2; E from (B, D0); B0 += Faraday(E)
-    hipLaunchKernelGGL(average_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, tri<T>(F->B0),
-                       ctri<T>(F->B), tri<T>(F->D0), ctri<T>(F->D));
+    // D0 <- (D0 + D)/2; E from (B, D0); B0 <- (B0 + B)/2 + Faraday(E)
+    hipLaunchKernelGGL(average_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, tri<T>(F->D0), ctri<T>(F->D));
     LAUNCH_CHECK("average");
     hipLaunchKernelGGL((aux_kernel<T, true, false, kQ>), gaux, kBlock2, 0, s, g, c->tab, ctri<T>(F->B),
                        ctri<T>(F->D0), tri<T>(F->E), none<T>());
     LAUNCH_CHECK("aux_e");
-    hipLaunchKernelGGL((faraday_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab, tri<T>(F->B0), none<T>(),
-                       ctri<T>(F->E), none<T>());
+    hipLaunchKernelGGL((faraday_kernel<T, true, kQ>), gupd, kBlock2, 0, s, g, c->tab,
+                       update_of<T>(tri<T>(F->B0), none<T>(), ctri<T>(F->Binit), none<T>(), true), ctri<T>(F->E),
+                       ctri<T>(F->B));
     LAUNCH_CHECK("faraday");
-    return field_bc<T>(c, tri<T>(F->B0), none<T>(), ctri<T>(F->Binit), true, s);
+    return GRPIC_OK;
   }
   // current filter (n_f passes) on the freshly deposited J^{n+1/2}, T as the
   // second plane set
@@ -515,23 +514,24 @@ grpic_status field_advance_impl(grpic_ctx* c, const grpic_fields* F, int32_t sta
   hipLaunchKernelGGL((aux_kernel<T, true, true, kQ>), gaux, kBlock2, 0, s, g, c->tab, ctri<T>(F->B0),
                      ctri<T>(F->D), tri<T>(F->E), tri<T>(F->H));
   LAUNCH_CHECK("aux_eh");
-  hipLaunchKernelGGL((faraday_kernel<T, true, kQ>), gpl2, kBlock2, 0, s, g, c->tab, tri<T>(F->B), comp<T>(c, F->Bc),
-                     ctri<T>(F->E), tri<T>(F->B0));
+  hipLaunchKernelGGL((faraday_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab,
+                     update_of<T>(tri<T>(F->B), comp<T>(c, F->Bc), ctri<T>(F->Binit), tri<T>(F->B0), true),
+                     ctri<T>(F->E), ctri<T>(F->B));
   LAUNCH_CHECK("faraday");
-  if ((st = field_bc<T>(c, tri<T>(F->B), comp<T>(c, F->Bc), ctri<T>(F->Binit), true, s))) return st;
   // D0 += Ampere(H, (J0 + J)/2)
-  hipLaunchKernelGGL((ampere_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab, tri<T>(F->D0), none<T>(),
-                     ctri<T>(F->H), tri<T>(F->J0), Jf, 0.5, 0.5, c->polar_k, none<T>(), none<T>());
+  hipLaunchKernelGGL((ampere_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab,
+                     update_of<T>(tri<T>(F->D0), none<T>(), ctri<T>(F->Dinit), none<T>(), false), ctri<T>(F->H),
+                     tri<T>(F->J0), Jf, 0.5, 0.5, c->polar_k, none<T>());
   LAUNCH_CHECK("ampere");
-  if ((st = field_bc<T>(c, tri<T>(F->D0), none<T>(), ctri<T>(F->Dinit), false, s))) return st;
   // H from (B, D0); D0 <- D, D += Ampere(H, J), J0 <- J, J <- 0
   hipLaunchKernelGGL((aux_kernel<T, false, true, kQ>), gaux, kBlock2, 0, s, g, c->tab, ctri<T>(F->B),
                      ctri<T>(F->D0), none<T>(), tri<T>(F->H));
   LAUNCH_CHECK("aux_h");
-  hipLaunchKernelGGL((ampere_kernel<T, true, kQ>), gpl2, kBlock2, 0, s, g, c->tab, tri<T>(F->D), comp<T>(c, F->Dc),
-                     ctri<T>(F->H), Jf, tri<T>(F->J0), 1.0, 0.0, c->polar_k, tri<T>(F->D0), Jclear);
+  hipLaunchKernelGGL((ampere_kernel<T, true, kQ>), gpl2, kBlock2, 0, s, g, c->tab,
+                     update_of<T>(tri<T>(F->D), comp<T>(c, F->Dc), ctri<T>(F->Dinit), tri<T>(F->D0), false),
+                     ctri<T>(F->H), Jf, tri<T>(F->J0), 1.0, 0.0, c->polar_k, Jclear);
   LAUNCH_CHECK("ampere");
-  return field_bc<T>(c, tri<T>(F->D), comp<T>(c, F->Dc), ctri<T>(F->Dinit), false, s);
+  return GRPIC_OK;
 }
 
 template <class T>
