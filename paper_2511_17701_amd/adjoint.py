@@ -48,8 +48,18 @@ class FrozenRun:
         return F
 
 
+# what a push step reads and changes (phi is advanced but read by nothing here;
+# the weights are constant, the previous position is scratch)
+MOVING_KEYS = ("i1", "i2", "dx1", "dx2", "u1", "u2", "u3", "tag")
+
+
 def _copy(P):
     return {k: v.clone() for k, v in P.items()}
+
+
+def _snapshot(P):
+    """The moving arrays of P; a replay or an adjoint step takes the others from a working set."""
+    return {k: P[k].clone() for k in MOVING_KEYS}
 
 
 def final_state(P):
@@ -69,9 +79,10 @@ class FrozenFieldPush(torch.autograd.Function):
         checkpoints = []
         for s in range(run.steps):
             if s % run.every == 0:
-                checkpoints.append(_copy(P))
+                checkpoints.append(_snapshot(P))
             run.ctx.push(F, P)
         ctx.run, ctx.F, ctx.b0, ctx.checkpoints = run, F, b0, checkpoints
+        ctx.rest = {k: v for k, v in P.items() if k not in MOVING_KEYS}  # the working set's other arrays
         ctx.b0_device = B0.device if torch.is_tensor(B0) else torch.device("cpu")
         return final_state(P)
 
@@ -82,14 +93,14 @@ class FrozenFieldPush(torch.autograd.Function):
         g = gout.t().contiguous().clone()          # rows x1, x2, u1, u2, u3
         gB0 = torch.zeros(n, dtype=torch.float64, device=gout.device)
         for seg in reversed(range(len(ctx.checkpoints))):
-            P = _copy(ctx.checkpoints[seg])
             count = min(run.every, run.steps - seg * run.every)
-            states = []
-            for _ in range(count):
-                states.append(_copy(P))
+            states = [ctx.checkpoints[seg]]  # the state before each step, kept as the replay goes on
+            for _ in range(count - 1):
+                P = {**{k: v.clone() for k, v in states[-1].items()}, **ctx.rest}
                 run.ctx.push(F, P)
+                states.append({k: P[k] for k in MOVING_KEYS})
             for S in reversed(states):
-                run.ctx.push_adjoint(F, b0, S, g, g, gB0)
+                run.ctx.push_adjoint(F, b0, {**S, **ctx.rest}, g, g, gB0)
         run.stats["gB0_per_particle"] = gB0
         grad_u0 = g[2:5].t().contiguous() if ctx.needs_input_grad[0] else None
         grad_B0 = gB0.sum().reshape(()).to(ctx.b0_device) if ctx.needs_input_grad[1] else None

@@ -14,6 +14,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from ctypes import POINTER, c_char_p, c_double, c_int32, c_int64, c_uint64, c_uint8, c_void_p
 
 import torch
@@ -120,6 +121,9 @@ def _stream():
     return c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+_PARTICLE_PACK = struct.Struct(f"q{len(PARTICLE_FIELDS)}Q").pack
+
+
 def _dtype(precision: int):
     return torch.float64 if precision == GRPIC_FP64 else torch.float32
 
@@ -143,6 +147,12 @@ class Context:
         self.params = q
         self.dtype = _dtype(precision)
         self.n_planes = NPLANE_FP32 if precision == GRPIC_FP32 else NPLANE
+        # what the marshalling of every call needs, laid out once
+        self._field_shape = (self.n_planes,) + self.shape
+        self._plane_bytes = self.shape[0] * self.shape[1] * torch.empty((), dtype=self.dtype).element_size()
+        self._field_pack = struct.Struct(f"{self.n_planes}Q{8 * (NPLANE_FP32 - self.n_planes)}x").pack
+        self._particle_types = [(k, torch.int32 if k in INT_FIELDS else (torch.uint8 if k == "tag" else self.dtype))
+                                for k in PARTICLE_FIELDS]
 
     @property
     def dt(self) -> float:
@@ -179,34 +189,26 @@ class Context:
                 P[k] = torch.zeros(n, dtype=self.dtype, device=device)
         return P
 
+    # The structs are packed in one call each (their members in the order of
+    # PLANES and PARTICLE_FIELDS): a few hundred ctypes and tensor operations per
+    # step otherwise, more host time than the launches of a small grid's kernels.
     def _fields(self, F: torch.Tensor) -> Fields:
-        if F.shape != (self.n_planes,) + self.shape or F.dtype != self.dtype or \
-                not F.is_contiguous():
-            raise GrpicError(f"field tensor must be contiguous {self.dtype} of shape "
-                             f"{(self.n_planes,) + self.shape}")
+        if F.shape != self._field_shape or F.dtype != self.dtype or not F.is_contiguous():
+            raise GrpicError(f"field tensor must be contiguous {self.dtype} of shape {self._field_shape}")
         if not F.is_cuda:
             raise GrpicError("field tensor must be on the GPU")
-        s = Fields()
-        base = F.data_ptr()
-        step = F[0].numel() * F.element_size()
-        for name, first in PLANES.items():
-            if first >= self.n_planes:
-                continue
-            arr = getattr(s, name)
-            for c in range(3):
-                arr[c] = base + (first + c) * step
-        return s
+        base, step = F.data_ptr(), self._plane_bytes
+        return Fields.from_buffer_copy(self._field_pack(*range(base, base + self.n_planes * step, step)))
 
     def _particles(self, P: dict) -> Particles:
         n = P["tag"].numel()
-        s = Particles(n=n)
-        for k in PARTICLE_FIELDS:
+        p = []
+        for k, want in self._particle_types:
             t = P[k]
-            want = torch.int32 if k in INT_FIELDS else (torch.uint8 if k == "tag" else self.dtype)
             if t.dtype != want or t.numel() != n or not t.is_contiguous() or not t.is_cuda:
                 raise GrpicError(f"particle array {k} must be a contiguous GPU {want} of length {n}")
-            setattr(s, k, t.data_ptr())
-        return s
+            p.append(t.data_ptr())
+        return Particles.from_buffer_copy(_PARTICLE_PACK(n, *p))
 
     # ------------------------------------------------------------ calls
     def particles_init(self, P: dict, n_pairs: int, ppc: int, T: float, n_geo: int, seed: int):
@@ -322,10 +324,11 @@ class Context:
     def step(self, F: torch.Tensor, P: dict, fused: bool = False):
         """One PIC step (Sec. 3.4): pre-push field stage, push, deposit, post-deposit
         stage (push and deposit in one pass when fused)."""
-        self.field_advance(F, PRE_PUSH)
+        f, p, st = ctypes.byref(self._fields(F)), ctypes.byref(self._particles(P)), _stream()
+        _check(_lib.grpic_field_advance(self._h, f, PRE_PUSH, st), "grpic_field_advance")
         if fused:
-            self.push_deposit(F, P)
+            _check(_lib.grpic_push_deposit(self._h, f, p, st), "grpic_push_deposit")
         else:
-            self.push(F, P)
-            self.deposit(P, F)
-        self.field_advance(F, POST_DEPOSIT)
+            _check(_lib.grpic_push(self._h, f, p, st), "grpic_push")
+            _check(_lib.grpic_deposit(self._h, p, f, st), "grpic_deposit")
+        _check(_lib.grpic_field_advance(self._h, f, POST_DEPOSIT, st), "grpic_field_advance")
