@@ -382,12 +382,30 @@ __global__ void average_kernel(int64_t n, TriT<T> A, CTriT<T> B) {  // A <- (A +
   for (int c = 0; c < 3; ++c) A.p[c][k] = 0.5 * (A.p[c][k] + B.p[c][k]);
 }
 
+// Initial data are launch-bound on the grids of frozen-field runs, which build
+// them for every amplitude: a field set is cleared in one launch and copied in
+// one (33 and 4 before: 85 of the 270 us that five steps of 1e3 particles
+// kept the GPU busy with, forward and back).
+constexpr int kMaxPlanes = 39;
 template <class T>
-__global__ void copy_kernel(int64_t n, TriT<T> A, CTriT<T> B) {  // A <- B
+struct PlaneSetT {
+  T* p[kMaxPlanes];
+};
+template <class T>
+__global__ void clear_planes_kernel(int64_t n, PlaneSetT<T> s) {  // plane blockIdx.y
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < n) s.p[blockIdx.y][k] = (T)0;
+}
+
+template <class T>
+__global__ void copy_initial_kernel(int64_t n, CTriT<T> D, CTriT<T> B, TriT<T> D0, TriT<T> B0, TriT<T> Di, TriT<T> Bi) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
 #pragma unroll
-  for (int c = 0; c < 3; ++c) A.p[c][k] = B.p[c][k];
+  for (int c = 0; c < 3; ++c) {
+    D0.p[c][k] = Di.p[c][k] = D.p[c][k];
+    B0.p[c][k] = Bi.p[c][k] = B.p[c][k];
+  }
 }
 
 template <class T>

@@ -251,51 +251,47 @@ grpic_status particles_init_impl(grpic_ctx* c, const grpic_particles* P, int64_t
   return GRPIC_OK;
 }
 
+// Zeroes a whole field set in one launch.
+template <class T>
+grpic_status clear_planes(grpic_ctx* c, const grpic_fields* F, hipStream_t s) {
+  PlaneSetT<T> p;
+  const int n = c->f32 ? 39 : 33;
+  void* const* pl = &F->D[0];
+  for (int k = 0; k < n; ++k) p.p[k] = (T*)pl[k];
+  hipLaunchKernelGGL(clear_planes_kernel<T>, dim3(blocks(c->g.plane), (unsigned)n), dim3(kB), 0, s, c->g.plane, p);
+  LAUNCH_CHECK("clear_planes");
+  return GRPIC_OK;
+}
+
 template <class T>
 grpic_status wald_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipStream_t s) {
   const Grid& g = c->g;
-  void* const* pl = &F->D[0];
-  for (int k = 0; k < (c->f32 ? 39 : 33); ++k) {
-    hipLaunchKernelGGL(fill_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, (T*)pl[k], 0.0);
-    LAUNCH_CHECK("fill");
-  }
+  grpic_status st;
+  if ((st = clear_planes<T>(c, F, s))) return st;
   hipLaunchKernelGGL(wald_kernel<T>, grid2(g.n_r + 2 * g.ng, g.n_th + 2 * g.ng), kBlock2, 0, s, g, c->tab,
                      tri<T>(F->D), tri<T>(F->B), B0);
   LAUNCH_CHECK("wald");
-  grpic_status st;
   if ((st = axis_bc<T>(c, tri<T>(F->D), false, s))) return st;
   if ((st = axis_bc<T>(c, tri<T>(F->B), true, s))) return st;
-  void* const* dst[4] = {F->D0, F->B0, F->Dinit, F->Binit};
-  void* const* src[4] = {F->D, F->B, F->D, F->B};
-  for (int k = 0; k < 4; ++k) {
-    hipLaunchKernelGGL(copy_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, tri<T>(dst[k]),
-                       ctri<T>(src[k]));
-    LAUNCH_CHECK("copy");
-  }
+  hipLaunchKernelGGL(copy_initial_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, ctri<T>(F->D), ctri<T>(F->B),
+                     tri<T>(F->D0), tri<T>(F->B0), tri<T>(F->Dinit), tri<T>(F->Binit));
+  LAUNCH_CHECK("copy_initial");
   return GRPIC_OK;
 }
 
 template <class T>
 grpic_status monopole_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipStream_t s) {
   const Grid& g = c->g;
-  void* const* pl = &F->D[0];
-  for (int k = 0; k < (c->f32 ? 39 : 33); ++k) {
-    hipLaunchKernelGGL(fill_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, (T*)pl[k], 0.0);
-    LAUNCH_CHECK("fill");
-  }
+  grpic_status st;
+  if ((st = clear_planes<T>(c, F, s))) return st;
   hipLaunchKernelGGL(monopole_kernel<T>, grid2(g.n_r + 2 * g.ng, g.n_th + 2 * g.ng), kBlock2, 0, s, g, c->tab,
                      (T*)F->B[0], B0);
   LAUNCH_CHECK("monopole");
-  grpic_status st;
   if ((st = axis_bc<T>(c, tri<T>(F->D), false, s))) return st;
   if ((st = axis_bc<T>(c, tri<T>(F->B), true, s))) return st;
-  void* const* dst[4] = {F->D0, F->B0, F->Dinit, F->Binit};
-  void* const* src[4] = {F->D, F->B, F->D, F->B};
-  for (int k = 0; k < 4; ++k) {
-    hipLaunchKernelGGL(copy_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, tri<T>(dst[k]),
-                       ctri<T>(src[k]));
-    LAUNCH_CHECK("copy");
-  }
+  hipLaunchKernelGGL(copy_initial_kernel<T>, dim3(blocks(g.plane)), dim3(kB), 0, s, g.plane, ctri<T>(F->D), ctri<T>(F->B),
+                     tri<T>(F->D0), tri<T>(F->B0), tri<T>(F->Dinit), tri<T>(F->Binit));
+  LAUNCH_CHECK("copy_initial");
   return GRPIC_OK;
 }
 
