@@ -313,7 +313,7 @@ __device__ inline void tetrad_reverse(const Frame& f, const double F[3], const d
 template <int SER>
 __device__ inline void adjoint_one(const Grid& g, const Tables& tab, const GatherPlanesT<double>& fp, double inv_B0,
                                    const ParticleArrays& P, uint32_t k, double gbar[5], double& gB0) {
-  constexpr bool kMap = SER == 0;
+  constexpr bool kMap = is_map(SER);
   const StateT<double> st = load_state(P, k);
   // empty, removed or leaving particles are not moved by the step: identity
   if (!is_live(st.t) || (st.t & kLeaving)) return;

@@ -38,7 +38,7 @@ struct UniT {
 // Everything a kernel needs to know about the grid and the run, by value.
 struct Grid {
   double a, M;
-  double xi_min, dxi, dth, inv_dth2;  // xi_min = log(r_min - r0); dth: eta spacing
+  double xi_min, dxi, dth, inv_dth, inv_dth2;  // xi_min = log(r_min - r0); dth: eta spacing
   double r0, h0;                      // quasi-spherical map (0, 0: log r, uniform theta)
   double dt, inv_dt;
   double small_angle;

@@ -295,6 +295,10 @@ grpic_status monopole_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipSt
   return GRPIC_OK;
 }
 
+// the kernels' form for g.ser = 3 (double precision only)
+template <class T>
+constexpr int kMapForm = sizeof(T) == 8 ? 3 : 0;
+
 template <int SER>
 void launch_push(grpic_ctx* c, const GatherPlanesT<double>& gp, const grpic_particles* P, dim3 grid, hipStream_t s) {
   if (c->g.n_iter > kCycleIter)
@@ -323,6 +327,7 @@ grpic_status push_impl(grpic_ctx* c, const grpic_fields* F, const grpic_particle
       gp.B[k] = (const double*)F->B0[k];
     }
     switch (c->g.ser) {
+      case 3: launch_push<3>(c, gp, P, grid, s); break;
       case 2: launch_push<2>(c, gp, P, grid, s); break;
       case 1: launch_push<1>(c, gp, P, grid, s); break;
       default: launch_push<0>(c, gp, P, grid, s); break;
@@ -363,6 +368,7 @@ void launch_push_deposit(grpic_ctx* c, const grpic_fields* F, const grpic_partic
     CurrentPlanesT<double> cp{{(double*)F->J[0], (double*)F->J[1], (double*)F->J[2]}};
     const ParticleArraysT<double> a = arrays<double>(P);
     switch (c->g.ser) {
+      case 3: hipLaunchKernelGGL((push_deposit_kernel<3, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
       case 2: hipLaunchKernelGGL((push_deposit_kernel<2, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
       case 1: hipLaunchKernelGGL((push_deposit_kernel<1, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
       default: hipLaunchKernelGGL((push_deposit_kernel_lib<kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
@@ -384,6 +390,7 @@ grpic_status deposit_impl(grpic_ctx* c, const grpic_particles* P, const grpic_fi
   constexpr int kBk = kDepBlock;
   const dim3 grid((unsigned)((P->n + kBk - 1) / kBk));
   switch (c->g.ser) {
+    case 3: hipLaunchKernelGGL((deposit_kernel<T, kMapForm<T>>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
     case 2: hipLaunchKernelGGL((deposit_kernel<T, 2>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
     case 1: hipLaunchKernelGGL((deposit_kernel<T, 1>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
     default: hipLaunchKernelGGL((deposit_kernel<T, 0>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
@@ -564,6 +571,7 @@ grpic_status diagnostics_impl(grpic_ctx* c, const grpic_fields* F, const grpic_p
   if (P->n > 0) {
     const dim3 gd(std::min(blocks(P->n), (unsigned)kDiagMaxBlocks)), bd(kDiagBlock);
     switch (g.ser) {
+      case 3: hipLaunchKernelGGL((diag_particles_kernel<T, kMapForm<T>>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
       case 2: hipLaunchKernelGGL((diag_particles_kernel<T, 2>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
       case 1: hipLaunchKernelGGL((diag_particles_kernel<T, 1>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
       default: hipLaunchKernelGGL((diag_particles_kernel<T, 0>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
@@ -654,6 +662,7 @@ grpic_status grpic_create(const grpic_params* p, grpic_ctx** out) {
   g.xi_min = std::log(p->r_min - p->r0);
   g.dxi = std::log((p->r_max - p->r0) / (p->r_min - p->r0)) / p->n_r;
   g.dth = kPi / p->n_th;
+  g.inv_dth = 1.0 / g.dth;
   g.inv_dth2 = 1.0 / (g.dth * g.dth);
   g.small_angle = p->small_angle;
   g.charge_scale = p->charge_scale;
@@ -699,19 +708,25 @@ grpic_status grpic_create(const grpic_params* p, grpic_ctx** out) {
   // the push evaluates exp and sincos of in-cell offsets (at most 1.5 cells)
   // by series that are exact to rounding for arguments up to 0.03 (short) or
   // 0.11 (long)
-  // (the series are written for the logarithmic-r, uniform-theta grid; a
-  // general quasi-spherical map takes the library functions)
+  // (a general quasi-spherical map takes short series of its own in double
+  // precision where the largest polar step allows them, the library functions
+  // elsewhere)
   {
     const double off = 1.5 * std::fmax(g.dxi, g.dth);
     g.ser = (off <= 0.03 && 4.0 * g.dth <= 0.03) ? 2 : (off <= 0.11 ? 1 : 0);
     g.axis_band = 4.0 * g.dth;
     g.band_hi = kPi - g.axis_band;
-    if (g.r0 != 0.0 || g.h0 != 0.0) g.ser = 0;
+    if (g.r0 != 0.0 || g.h0 != 0.0) {
+      const double step = g.dth * std::fmax(1.0 + 2.0 * g.h0, 1.0 - g.h0);  // largest dtheta/dx2
+      g.ser = !c->f32 && 1.5 * std::fmax(g.dxi, step) <= 0.03 && 8.0 * step <= 0.11 ? 3 : 0;
+    }
     // midpoints reach half a cell past the particle's cell: one cell beyond the
     // axis bands (4 cells or 0.11 rad in double, 0.11 rad in single precision)
+    // (on the general map the table form has no band: theta is rounded as the
+    // map rounds it in the cells next to the axes)
     const double wide = std::ceil(0.11 / g.dth) + 1.0;
     g.mid32 = (int)wide;
-    g.mid64 = g.ser == 2 ? 5 : (int)wide;
+    g.mid64 = g.ser >= 2 ? 5 : (int)wide;
     const int64_t bytes = g.plane * (c->f32 ? 4 : 8);
     g.narrow = bytes < ((int64_t)1 << 32) && p->n_r + 2 * p->n_ghost < (1 << 24) && g.ld < (1 << 24);
     const UniT<double> u = uni<double>(g);
@@ -935,6 +950,7 @@ grpic_status grpic_push_adjoint(grpic_ctx* c, const grpic_fields* F, double B0, 
   const dim3 grid((unsigned)((P->n + kAdjBlock - 1) / kAdjBlock)), block(kAdjBlock);
   const ParticleArrays a = arrays<double>(P);
   switch (c->g.ser) {
+    case 3: hipLaunchKernelGGL(push_adjoint_kernel<3>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;
     case 2: hipLaunchKernelGGL(push_adjoint_kernel<2>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;
     case 1: hipLaunchKernelGGL(push_adjoint_kernel<1>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;
     default: hipLaunchKernelGGL(push_adjoint_kernel<0>, grid, block, 0, S(stream), c->g, c->tab, gp, 1.0 / B0, a, gbar_in, gbar_out, gbar_B0); break;

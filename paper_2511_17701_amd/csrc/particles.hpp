@@ -310,6 +310,22 @@ __device__ inline void sincos_short(double x, double* s, double* c) {
   *c = fma(z, pc, 1.0);
 }
 
+// Forms of the position's r, sin and cos (the SER of the kernels below): 0 the
+// library functions; 1, 2 the long and the short series on the logarithmic-r,
+// uniform-theta grid; 3 the short series on the general quasi-spherical map, in
+// double precision only (701 x 533, 24 per cell, ten steps with the fused pass:
+// 8.5 -> 7.3 ms; in single precision, where the library functions are short
+// and the horizon cells take the other, 4.26 -> 4.31 ms).
+constexpr bool is_map(int ser) { return ser == 0 || ser == 3; }
+
+// The general map next to node eta = i2 dth: theta(eta + d) - theta(eta) =
+// d (q0 + q1 d + 2 c d^2) and T / dth = q0 + 2 q1 d + 6 c d^2, c = 2 h0 / pi^2,
+// q0 = T / dth at the node, q1 = c (6 eta - 3 pi).
+template <class R>
+struct MapNodeT {
+  R q0, q1;
+};
+
 // pi - (pi rounded to double)
 constexpr double kPiLo = 1.2246467991473531772e-16;
 
@@ -323,12 +339,43 @@ constexpr double kPiLo = 1.2246467991473531772e-16;
 // would cancel), and by angle addition from the tables elsewhere.
 // SER = 2: offsets |x - i| dxi, dth <= 0.03 and an axis band of 4 cells (its
 // angles <= 0.03): short series throughout.  SER = 1: offsets <= 0.11 and an
-// axis band of 0.11 rad: long series.  SER = 0: library functions (also every
-// general quasi-spherical map).
+// axis band of 0.11 rad: long series.  SER = 3: the general map on grids whose
+// offsets are within 0.03 and whose cells 8 from an axis within 0.11 rad: short
+// series, long ones in an axis band of 0.11 rad, theta as rounded by map_theta
+// there.  SER = 0: library functions.
 template <int SER>
 __device__ inline RSC rsc_near(const Grid& g, const Tables& t, int i1, double x1, int i2, double x2) {
   if (SER == 0) return rsc_direct(g, x1, x2);
   RSC p;
+  if (SER == 3) {
+    const double e = (elem(t.r[0], (uint32_t)(i1 + g.ng)) - g.r0) * exp_short((x1 - (double)i1) * g.dxi);
+    p.r = g.r0 + e;
+    p.rd = g.dxi * e;
+    double th;
+    map_theta(g, x2, &th, &p.td, &p.dtd);
+    const double it = rcp(p.td);
+    p.itd2 = it * it;
+    if (th <= g.small_angle || th >= g.th_hi) {
+      const bool lo = th <= g.small_angle;
+      p.s = lo ? g.sin_lo : g.sin_hi;
+      p.c = lo ? g.cos_lo : g.cos_hi;
+    } else if (th <= 0.11) {
+      sincos_small(th, &p.s, &p.c);
+    } else if (th >= kPi - 0.11) {
+      double cq;
+      sincos_small((kPi - th) + kPiLo, &p.s, &cq);
+      p.c = -cq;
+    } else {
+      const double c6 = 12.0 * g.h0 * (1.0 / (kPi * kPi)), d = (x2 - (double)i2) * g.dth;
+      const double q0 = elem(t.td[0], (uint32_t)(i2 + g.ng)) * g.inv_dth, q1 = c6 * ((double)i2 * g.dth - 0.5 * kPi);
+      double sp, cp;
+      sincos_short(d * (q0 + d * (q1 + (1.0 / 3.0) * c6 * d)), &sp, &cp);
+      const double sj = elem(t.s[0], (uint32_t)(i2 + g.ng)), cj = elem(t.c[0], (uint32_t)(i2 + g.ng));
+      p.s = fma(sj, cp, cj * sp);
+      p.c = fma(cj, cp, -(sj * sp));
+    }
+    return p;
+  }
   const double tr = (x1 - (double)i1) * g.dxi;
   p.r = t.r[0][i1 + g.ng] * (SER == 2 ? exp_short(tr) : exp_small(tr));
   p.rd = g.dxi * p.r;
@@ -445,7 +492,8 @@ __device__ inline RSCT<float> rsc_near_f(const Grid& g, const Tables& t, int i1,
 // then neither read memory nor branch on the angle.
 template <class T>
 struct AnchorT {
-  T r, s, c;
+  T r, s, c;       // r - r0; sin, cos
+  MapNodeT<T> q;   // general map
   bool mid;
 };
 
@@ -457,6 +505,11 @@ __device__ inline AnchorT<double> anchor_at(const Grid& g, const Tables& t, int 
     a.r = elem(t.r[0], (uint32_t)(i1 + g.ng));
     a.s = elem(t.s[0], (uint32_t)(i2 + g.ng));
     a.c = elem(t.c[0], (uint32_t)(i2 + g.ng));
+    if (SER == 3) {
+      a.r -= g.r0;
+      a.q.q0 = elem(t.td[0], (uint32_t)(i2 + g.ng)) * g.inv_dth;
+      a.q.q1 = 12.0 * g.h0 * (1.0 / (kPi * kPi)) * ((double)i2 * g.dth - 0.5 * kPi);
+    }
     a.mid = __all((i2 >= g.mid64) & (i2 < g.n_th - g.mid64));
   }
   return a;
@@ -481,14 +534,24 @@ __device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<doubl
                              int i2, double x2, double f2) {
   if (SER == 0 || !an.mid) return rsc_near<SER>(g, t, i1, x1, i2, x2);
   RSC p;
-  const double tr = f1 * g.dxi, x = f2 * g.dth;
-  double sp, cp;
-  if (SER == 2) sincos_short(x, &sp, &cp); else sincos_small(x, &sp, &cp);
-  p.r = an.r * (SER == 2 ? exp_short(tr) : exp_small(tr));
+  const double tr = f1 * g.dxi;
+  double sp, cp, x = f2 * g.dth;
+  if (SER == 3) {
+    const double c2 = 4.0 * g.h0 * (1.0 / (kPi * kPi)), d = x, w = c2 * d;  // 2 c
+    x = d * (an.q.q0 + d * (an.q.q1 + w));
+    p.td = g.dth * (an.q.q0 + d * (2.0 * an.q.q1 + 3.0 * w));
+    const double it = rcp(p.td);
+    p.itd2 = it * it;
+    p.dtd = g.dth * g.dth * (2.0 * an.q.q1 + 6.0 * w);
+  } else {
+    p.td = g.dth;
+    p.itd2 = g.inv_dth2;
+    p.dtd = 0.0;
+  }
+  if (SER == 1) sincos_small(x, &sp, &cp); else sincos_short(x, &sp, &cp);
+  p.r = an.r * (SER == 1 ? exp_small(tr) : exp_short(tr));
   p.rd = g.dxi * p.r;
-  p.td = g.dth;
-  p.itd2 = g.inv_dth2;
-  p.dtd = 0.0;
+  if (SER == 3) p.r += g.r0;
   p.s = fma(an.s, cp, an.c * sp);
   p.c = fma(an.c, cp, -(an.s * sp));
   return p;
@@ -646,7 +709,7 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   AnchorT<double> an = anchor_at<SER>(g, tab, i1, i2, 0.0);
   Frame f;
   Grad d;
-  frame_from<SER == 0>(g, rsc_at<SER>(g, tab, an, i1, (double)i1 + dx1, dx1, i2, (double)i2 + dx2, dx2), &f, &d);
+  frame_from<is_map(SER)>(g, rsc_at<SER>(g, tab, an, i1, (double)i1 + dx1, dx1, i2, (double)i2 + dx2, dx2), &f, &d);
   const double qm = species_sign(t);
   if (qm != 0.0) {
     // D^i, B^i at x^n -> tetrad components, scaled by the lapse
@@ -657,10 +720,10 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
     const double B[3] = {ais11 * F[3], al * f.s22 * F[4], al * f.s33 * (F[5] - k13 * F[3])};
     const double kb = 0.25 * qm * g.dt;
     em_half(f, E, B, kb, u1, u2, u3);
-    geodesic_u<SER == 0, kCycle>(g, f, d, u1, u2, u3, 1.0);
+    geodesic_u<is_map(SER), kCycle>(g, f, d, u1, u2, u3, 1.0);
     em_half(f, E, B, kb, u1, u2, u3);
   } else {
-    geodesic_u<SER == 0, kCycle>(g, f, d, u1, u2, u3, mass2_of(t));  // EM stage skipped for q = 0
+    geodesic_u<is_map(SER), kCycle>(g, f, d, u1, u2, u3, mass2_of(t));  // EM stage skipped for q = 0
   }
 
   // m^2 and the anchor, taken here again rather than kept from the top: the
@@ -758,7 +821,7 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     Frame fd;
     Grad dd;
     const AnchorT<double> ad = anchor_at<SER>(g, tab, i1, i2, 0.0);
-    frame_from<SER == 0>(g, rsc_at<SER>(g, tab, ad, i1, (double)i1 + dx1, (double)dx1, i2, (double)i2 + dx2, (double)dx2),
+    frame_from<is_map(SER)>(g, rsc_at<SER>(g, tab, ad, i1, (double)i1 + dx1, (double)dx1, i2, (double)i2 + dx2, (double)dx2),
                          &fd, &dd);
     f.c = CoeffsT<float>{(float)fd.c.alpha, (float)fd.c.beta1, (float)fd.c.hu11,
                          (float)fd.c.hu22, (float)fd.c.hu33, (float)fd.c.hu13};
@@ -776,7 +839,7 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     d.ct = (float)dd.ct;
     d.tt = (float)dd.tt;
   } else {
-    frame_from<SER == 0>(g, rsc_at<SER>(g, tab, an, i1, 0.0, dx1, i2, 0.0, dx2), &f, &d);
+    frame_from<is_map(SER)>(g, rsc_at<SER>(g, tab, an, i1, 0.0, dx1, i2, 0.0, dx2), &f, &d);
   }
   const float qm = species_sign<float>(t);
   const float ms = (float)mass2_of(t);
@@ -788,10 +851,10 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     const float B[3] = {ais11 * F[3], al * f.s22 * F[4], al * f.s33 * (F[5] - k13 * F[3])};
     const float kb = 0.25f * qm * g.uf.dt;
     em_half(f, E, B, kb, u1, u2, u3);
-    geodesic_u<SER == 0, false>(g, f, d, u1, u2, u3, 1.0f);
+    geodesic_u<is_map(SER), false>(g, f, d, u1, u2, u3, 1.0f);
     em_half(f, E, B, kb, u1, u2, u3);
   } else {
-    geodesic_u<SER == 0, false>(g, f, d, u1, u2, u3, ms);  // EM stage skipped for q = 0
+    geodesic_u<is_map(SER), false>(g, f, d, u1, u2, u3, ms);  // EM stage skipped for q = 0
   }
 
   // the weight and phi, needed after the iterations: in flight during them
@@ -1315,9 +1378,9 @@ push_deposit_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays
   if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
-// library path in FP64 (coarse grids and the general quasi-spherical map):
-// the library exp and sincos and the map factors need more registers than the
-// series paths; three wavefronts per SIMD leave room for them without spills
+// library path in FP64 (coarse grids): the library exp and sincos and the map
+// factors need more registers than the series paths; three wavefronts per SIMD
+// leave room for them without spills
 template <bool kRank>
 __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(3)))
 push_deposit_kernel_lib(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp,
