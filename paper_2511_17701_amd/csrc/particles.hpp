@@ -86,6 +86,23 @@ __device__ inline ParticleArraysT<T> from_slot(const ParticleArraysT<T>& P, int6
                             P.w + k0, P.phi + k0, P.i1p + k0, P.i2p + k0, P.dx1p + k0, P.dx2p + k0, P.tag + k0, P.n - k0};
 }
 
+// The block of slots that a block of the double-precision fused pass takes.
+// Block b runs on XCD b mod 8.  In a cell-sorted set the blocks beside the axes,
+// which take the longer form of the polar terms, recur with the length of a
+// theta row; where that is a multiple of 8 blocks, slot block b on block b gives
+// them all to one or two XCDs, and the others wait.  So each XCD takes 64 slot
+// blocks in a row of every group of 512; the last, partial group keeps its
+// order.  512^2 with 16 per cell (rows of 64 blocks), ten whole steps: 3.37 to
+// 3.12 ms; 1024^2 with 90 per cell (rows of 720): 58.47 and 58.47 ms.  Runs of 16
+// gave 3.23 and 60.2 ms, of 256 3.15 and 60.3 (60.3 without).  Turning the place of
+// an XCD from group to group cost 1 % at 1024^2, and the single-precision pass, whose polar terms differ
+// less near the axes, gains nothing from either (0 to -1 %).
+__device__ inline int64_t spread_block() {
+  const unsigned b = blockIdx.x;
+  if ((b | 511u) >= gridDim.x) return b;
+  return (int64_t)((b & ~511u) | ((b & 7u) << 6) | ((b >> 3) & 63u));
+}
+
 // First-order interpolation in code coordinates of the six field components
 // (D^1, D^2, D^3, B^1, B^2, B^3) at offsets (dx1, dx2) in cell (i1, i2); a
 // component staggered by half a cell starts at the cell's corner or one row or
@@ -1371,7 +1388,7 @@ __global__ void __launch_bounds__(kDepBlock) deposit_kernel(Grid g, Tables tab, 
 template <int SER, bool kRank>
 __global__ void __launch_bounds__(kDepBlock) GRPIC_FP64_PUSH_OCCUPANCY
 push_deposit_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp, int* counts) {
-  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * kDepBlock);
+  const ParticleArraysT<double> Q = from_slot(P, spread_block() * kDepBlock);
   if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<double> mv = push_one<SER, false>(g, tab, fp, Q, threadIdx.x);
   deposit_block<double, SER>(g, tab, cp, mv, mv.dep);
@@ -1385,7 +1402,7 @@ template <bool kRank>
 __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(3)))
 push_deposit_kernel_lib(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp,
                         int* counts) {
-  const ParticleArraysT<double> Q = from_slot(P, (int64_t)blockIdx.x * kDepBlock);
+  const ParticleArraysT<double> Q = from_slot(P, spread_block() * kDepBlock);
   if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<double> mv = push_one<0, false>(g, tab, fp, Q, threadIdx.x);
   deposit_block<double, 0>(g, tab, cp, mv, mv.dep);
