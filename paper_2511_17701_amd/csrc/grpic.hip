@@ -428,7 +428,15 @@ grpic_status sort_impl(grpic_ctx* c, const grpic_particles* src, const grpic_par
   LAUNCH_CHECK("scan_add");
   hipLaunchKernelGGL(copy_int_kernel, dim3(1), dim3(1), 0, s, w.off + (nkeys - 1), w.live);
   LAUNCH_CHECK("copy_int");
-  hipLaunchKernelGGL(sort_scatter_kernel<T>, dim3(blocks(src->n)), dim3(kB), 0, s, g, a, b, (const int*)w.off);
+  bool ordered = false;
+  if constexpr (sizeof(T) == 4) {
+    ordered = src->n >= kScatOrdered;
+    if (ordered)
+      hipLaunchKernelGGL(sort_scatter_ordered_kernel, dim3((unsigned)((src->n + kScatBlock - 1) / kScatBlock)),
+                         dim3(kScatBlock), 0, s, g, a, b, (const int*)w.off);
+  }
+  if (!ordered)
+    hipLaunchKernelGGL(sort_scatter_kernel<T>, dim3(blocks(src->n)), dim3(kB), 0, s, g, a, b, (const int*)w.off);
   LAUNCH_CHECK("sort_scatter");
   hipLaunchKernelGGL(sort_clear_tail_kernel, dim3(1024), dim3(kB), 0, s, b.tag, dst->n, (const int*)w.live);
   LAUNCH_CHECK("sort_clear_tail");

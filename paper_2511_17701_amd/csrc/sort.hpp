@@ -135,8 +135,7 @@ __device__ inline V scatter_load(const V* p) {
 
 // Moves live slot k of S to slot off[key] + rank of D (rank from
 // sort_rank_kernel, in S.i1p; off the exclusive scan of the cell counts).  No
-// atomics: every load and store of a wavefront is independent, so the pass
-// streams at the memory system's rate.  Empty and leaving slots are not
+// atomics: every load and store of a wavefront is independent.  Empty and leaving slots are not
 // moved (sort_clear_tail_kernel empties the destination after the live
 // slots).  The previous position (scratch between a push and its deposit) is
 // not carried.
@@ -161,6 +160,104 @@ __global__ void __launch_bounds__(256) sort_scatter_kernel(Grid g, ParticleArray
   D.w[o] = scatter_load<T>(S.w + k);
   D.phi[o] = scatter_load<T>(S.phi + k);
   D.tag[o] = t;
+}
+
+// The same scatter for many single-precision slots: each block of kScatBlock
+// puts its particles in the order of their destinations in LDS first, so that
+// a wavefront stores to a few runs of slots instead of one for every two lanes
+// (what bounds the direct form: lines of the L2 that are filled in pieces,
+// often from several XCDs).  The order is by bins of 8 destinations modulo
+// 8 kScatBins, which the few rows that a block's particles go to share without
+// mixing them finely; within a bin it is arbitrary.  Two LDS buffers take
+// turns, one barrier per array.  Measured, a whole sort in single precision on
+// (r, theta) grids whose particles moved by 0.2 to 2.5 cells, direct and this,
+// ms: 512^2 16 per cell 0.219, 0.201; 1024^2 16 0.819, 0.754; 700^2 64 1.89,
+// 1.38; 1024^2 64 3.90, 2.67; 1500 x 1100 24 2.37, 2.20; 2048^2 24 5.53, 4.48.
+// Blocks of 2048 to 8192 slots gain more on some of these (1024^2 64: 2.45,
+// 2.27) and lose on others (2048^2 8: direct 1.68, this 1.62, 8192 slots 1.99;
+// 1500 x 1100 24: 2048 slots 2.55).
+constexpr int kScatBlock = 1024, kScatBins = 1024;
+static_assert(kScatBins == kScatBlock, "one thread per slot and per bin");
+
+// From where on a sort takes it: at 256^2 with 16 per cell the direct form takes
+// 72 us and this one 76, at 512^2 219 and 201.  In double precision, where twice
+// the bytes pass LDS, it gains 15 % there and loses 20 % at 1400^2 with 24 per
+// cell (3.64, 4.37 ms), so the direct form stays.
+constexpr int64_t kScatOrdered = int64_t(1) << 21;
+
+template <class V>
+__device__ inline void scatter_array(V* sh, V v, int pos, bool store, uint32_t o, V* D) {
+  if (pos >= 0) sh[pos] = v;
+  lds_barrier();
+  if (store) D[o] = sh[threadIdx.x];
+}
+
+__global__ void __launch_bounds__(kScatBlock)
+sort_scatter_ordered_kernel(Grid g, ParticleArraysT<float> S, ParticleArraysT<float> D, const int* __restrict__ off) {
+  __shared__ int bin[kScatBins];
+  __shared__ int part[kScatBlock / 64];
+  __shared__ float buf[2][kScatBlock];
+  const int t = threadIdx.x;
+  const ParticleArraysT<float> P = from_slot(S, (int64_t)blockIdx.x * kScatBlock);
+  const bool in = t < P.n;
+  const auto load = [&](const auto* a) {
+    return in ? __builtin_nontemporal_load(a + t) : std::remove_cv_t<std::remove_reference_t<decltype(*a)>>(0);
+  };
+  bin[t] = 0;
+  const uint8_t tag = load(P.tag);
+  const int i1 = load(P.i1), i2 = load(P.i2), rank = load(P.i1p);
+  const float dx1 = load(P.dx1);
+  lds_barrier();
+  const int key = cell_key(g, tag, i1, i2);
+  const int64_t to = key == g.n_r * g.n_th ? -1 : (int64_t)off[key] + rank;
+  const bool moves = to >= 0 && to < D.n;  // (as above)
+  uint32_t o = moves ? (uint32_t)to : 0;
+  const int mine = (int)(o >> 3) & (kScatBins - 1);
+  int pos = moves ? atomicAdd(&bin[mine], 1) : -1;
+  lds_barrier();
+  // exclusive scan of the bins: within the wavefronts, then over them
+  const int cnt = bin[t];
+  int incl = cnt;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int up = __shfl_up(incl, d);
+    if ((t & 63) >= d) incl += up;
+  }
+  if ((t & 63) == 63) part[t >> 6] = incl;
+  lds_barrier();
+  int base = incl - cnt, n = 0;
+#pragma unroll
+  for (int q = 0; q < kScatBlock / 64; ++q) {
+    base += q < (t >> 6) ? part[q] : 0;
+    n += part[q];
+  }
+  bin[t] = base;
+  lds_barrier();
+  if (moves) {
+    pos += bin[mine];
+    ((uint32_t*)buf[0])[pos] = o;
+  }
+  lds_barrier();
+  const bool store = t < n;
+  if (store) o = ((uint32_t*)buf[0])[t];
+  // each array is loaded while the one before it is stored (all loads at the
+  // start: 1500 x 1100 with 24 per cell 2.50 ms instead of 2.20)
+  const float dx2 = load(P.dx2);
+  scatter_array(buf[1], dx1, pos, store, o, D.dx1);
+  const float u1 = load(P.u1);
+  scatter_array(buf[0], dx2, pos, store, o, D.dx2);
+  const float u2 = load(P.u2);
+  scatter_array(buf[1], u1, pos, store, o, D.u1);
+  const float u3 = load(P.u3);
+  scatter_array(buf[0], u2, pos, store, o, D.u2);
+  const float w = load(P.w);
+  scatter_array(buf[1], u3, pos, store, o, D.u3);
+  const float phi = load(P.phi);
+  scatter_array(buf[0], w, pos, store, o, D.w);
+  scatter_array(buf[1], phi, pos, store, o, D.phi);
+  scatter_array((int*)buf[0], i1, pos, store, o, D.i1);
+  scatter_array((int*)buf[1], i2, pos, store, o, D.i2);
+  scatter_array((uint8_t*)buf[0], tag, pos, store, o, D.tag);
 }
 
 // Tag 0 on the destination slots from the live count (*live, the scan's
