@@ -104,9 +104,10 @@ typedef struct {
   double h0;            /* equatorial concentration of the polar map
                            theta = eta + 2 h0 eta (pi - 2 eta)(pi - eta)/pi^2,
                            eta uniform in x2; -1/2 < h0 < 1.  r0 = h0 = 0 is
-                           the logarithmic-r, uniform-theta grid, the only
-                           one whose push takes in-cell series (others take
-                           the library exp and sincos)                       */
+                           the logarithmic-r, uniform-theta grid.  Pushes
+                           take in-cell series there and, in double
+                           precision, on fine grids of other maps (coarse
+                           ones take the library exp and sincos)             */
 } grpic_params;
 
 /* Device pointers to the field planes (Sec. 3.4 storage):

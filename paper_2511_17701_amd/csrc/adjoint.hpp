@@ -18,8 +18,8 @@
 //                its first derivatives, go back to x1, x2.
 // Both implicit stages are differentiated at their fixed points (the implicit-
 // function theorem), which an iterate that has stopped changing is taken for
-// (at_fixed: rounding can keep an iteration from an exact repeat for ever).  An iteration that does not come that far within
-// n_iter (next to the axis the contraction can approach 1) is differentiated
+// (at_fixed: rounding can keep an iteration from an exact repeat for ever).  An
+// iteration that does not come that far within n_iter (next to the axis the contraction can approach 1) is differentiated
 // through the iterations the forward pass ran instead, so the result is always
 // the derivative of the computed map.
 // The metric depends on the position alone: its derivatives are two tangents

@@ -94,9 +94,10 @@ __device__ inline ParticleArraysT<T> from_slot(const ParticleArraysT<T>& P, int6
 // blocks in a row of every group of 512; the last, partial group keeps its
 // order.  512^2 with 16 per cell (rows of 64 blocks), ten whole steps: 3.37 to
 // 3.12 ms; 1024^2 with 90 per cell (rows of 720): 58.47 and 58.47 ms.  Runs of 16
-// gave 3.23 and 60.2 ms, of 256 3.15 and 60.3 (60.3 without).  Turning the place of
-// an XCD from group to group cost 1 % at 1024^2, and the single-precision pass, whose polar terms differ
-// less near the axes, gains nothing from either (0 to -1 %).
+// gave 3.23 and 60.2 ms, of 256 3.15 and 60.3 (60.3 without).  Turning the place
+// of an XCD from group to group cost 1 % at 1024^2, and the single-precision
+// pass, whose polar terms differ less near the axes, gains nothing from either
+// (0 to -1 %).
 __device__ inline int64_t spread_block() {
   const unsigned b = blockIdx.x;
   if ((b | 511u) >= gridDim.x) return b;
@@ -1153,7 +1154,8 @@ __device__ inline bool block_anchor(bool act, int ia, int ja, int& ai, int& aj) 
 // LDS add of 64 floats takes 194 cycles of the CU even without conflicts, one
 // of 64 doubles 9 (21, 93 and 193 with 2, 8 and 64 lanes on one address), and
 // the float adds bound the single-precision pass (2048^2, 16 per cell, ten
-// steps with the filter and a sort: 30.0 ms, with double adds 26.0).  Before the LDS atomics the two lanes of an aligned pair
+// steps with the filter and a sort: 30.0 ms, with double adds 26.0).  Before
+// the LDS atomics the two lanes of an aligned pair
 // that share their nodes are summed by DPP swaps, and only the first adds
 // (cell-sorted particles put runs of one cell in consecutive lanes).  A
 // particle whose footprint leaves the tile (its block's cells wrap from the end
