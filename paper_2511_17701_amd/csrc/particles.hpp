@@ -591,6 +591,14 @@ __device__ inline RSCT<float> rsc_at(const Grid& g, const Tables& t, const Ancho
   return p;
 }
 
+// Whether a move is of one cell at most, which is what the deposit's footprint
+// holds.  A displacement below one cell is not enough: an offset of 1, which
+// in_grid accepts and a reflection at an axis can leave, plus the largest number
+// below 1 rounds to 2.
+__host__ __device__ inline bool one_cell_move(int ia, int ja, int ib, int jb) {
+  return (unsigned)(ib - ia + 1) <= 2u && (unsigned)(jb - ja + 1) <= 2u;
+}
+
 // Sort key of a slot's state: its cell i1 * n_th + i2, or n_cells for a slot
 // that the cell sort drops (empty, invalid, leaving, outside the grid).
 __device__ inline int cell_key(const Grid& g, uint8_t t, int i1, int i2) {
@@ -785,7 +793,7 @@ __device__ inline Move<double> push_one(const Grid& g, const Tables& tab, const 
   elem(P.u2, k) = u2;
   elem(P.u3, k) = u3;
   elem(P.tag, k) = t;
-  mv.dep = is_live(t) && qm != 0.0;
+  mv.dep = is_live(t) && qm != 0.0 && one_cell_move(mv.ia, mv.ja, i1, i2);
   mv.ib = i1;
   mv.jb = i2;
   mv.xb = dx1;
@@ -908,7 +916,7 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
   elem(P.u2, k) = u2;
   elem(P.u3, k) = u3;
   elem(P.tag, k) = t;
-  mv.dep = is_live(t) && qm != 0.0f;
+  mv.dep = is_live(t) && qm != 0.0f && one_cell_move(mv.ia, mv.ja, i1, i2);
   mv.ib = i1;
   mv.jb = i2;
   mv.xb = dx1;
@@ -989,11 +997,12 @@ struct ContribT {
 };
 
 // A stored move that the zigzag can represent: both ends in range, a cell at
-// most apart.  (The moves of a fused pass are, by the push's own checks.)
+// most apart.  (The moves of a fused pass are: the push starts inside the grid,
+// reflects at the axes and deposits one_cell_move only.)
 template <class T>
 __device__ inline bool move_in_range(const Grid& g, const Move<T>& mv) {
   return in_grid(g, mv.ia, mv.xa, mv.ja, mv.ya) & in_deposit_range(g, mv.ib, mv.xb, mv.jb, mv.yb) &
-         (abs(mv.ib - mv.ia) <= 1) & (abs(mv.jb - mv.ja) <= 1);
+         one_cell_move(mv.ia, mv.ja, mv.ib, mv.jb);
 }
 
 template <class T, int SER>
