@@ -179,12 +179,6 @@ struct UpdateT {
   int zero;
 };
 
-// The compensation of component c at a point.
-template <class T>
-__device__ inline double comp_at(const Grid& g, const UpdateT<T>& u, int c, int i, int j) {
-  return sizeof(T) == 4 && u.L.p[0] ? (double)pt(g, u.L.p[c], i, j) : 0.0;
-}
-
 // Stores v, the updated component c at (i, j), i > n_f, j an interior column of
 // the component, through the boundary conditions.  The thread that owns the
 // point also writes the ghost columns that mirror it and, from row n_f + 1, the
@@ -256,14 +250,22 @@ template <class T, bool kPre, bool kQ>
 __global__ void faraday_kernel(Grid g, Tables t, UpdateT<T> u, CTriT<T> E, CTriT<T> A) {
   const int j = launch_col(), i = launch_row() + g.n_filter + 1;
   if (j > g.n_th || i >= g.n_r + g.ng) return;
-  T was[3];
+  const bool half = j < g.n_th;  // theta-staggered components exist
+  // (in column n_th they are ghosts, which the threads of column n_th - 1 write)
+  T was[3] = {}, add[3] = {};  // the stored values and what is added to them: A or the compensation
+  auto load = [&](int c) {
+    was[c] = pt(g, u.X.p[c], i, j);
+    if (kPre) add[c] = pt(g, A.p[c], i, j);
+    else if (sizeof(T) == 4 && u.L.p[0]) add[c] = pt(g, u.L.p[c], i, j);
+  };
+  load(1);
+  if (half) {
+    load(0);
+    load(2);
+  }
   double v[3];
 #pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    was[c] = pt(g, u.X.p[c], i, j);
-    v[c] = kPre ? 0.5 * ((double)was[c] + (double)pt(g, A.p[c], i, j)) : (double)was[c] + comp_at(g, u, c, i, j);
-  }
-  const bool half = j < g.n_th;  // theta-staggered components exist
+  for (int c = 0; c < 3; ++c) v[c] = (kPre ? 0.5 : 1.0) * ((double)was[c] + (double)add[c]);
   if (i <= g.n_r) {
     const bool below = i < g.n_r;
     const double e3 = (double)pt(g, E.p[2], i, j);
@@ -299,16 +301,23 @@ __global__ void ampere_kernel(Grid g, Tables t, UpdateT<T> u, CTriT<T> H, TriT<T
 #pragma unroll
   for (int c = 0; c < 3; ++c) ja[c] = pt(g, Ja.p[c], i, j);
   if (i > g.n_filter && j >= 0 && j <= g.n_th) {
-    T was[3];
+    const bool half = j < g.n_th, comp = sizeof(T) == 4 && u.L.p[0];
+    T was[3] = {}, add[3] = {}, jb[3] = {};  // (add: the compensation)
+    auto load = [&](int c) {
+      was[c] = pt(g, u.X.p[c], i, j);
+      if (comp) add[c] = pt(g, u.L.p[c], i, j);
+      if (!kFinal) jb[c] = pt(g, Jb.p[c], i, j);
+    };
+    load(0);
+    load(2);
+    if (half) load(1);  // (column n_th as in the Faraday update)
     double v[3], J[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      was[c] = pt(g, u.X.p[c], i, j);
-      v[c] = (double)was[c] + comp_at(g, u, c, i, j);
-      J[c] = kFinal ? (double)ja[c] : wa * (double)ja[c] + wb * (double)pt(g, Jb.p[c], i, j);
+      v[c] = (double)was[c] + (double)add[c];
+      J[c] = kFinal ? (double)ja[c] : wa * (double)ja[c] + wb * (double)jb[c];
     }
     const double fpi = 4.0 * kPi;
-    const bool half = j < g.n_th;  // theta-staggered components exist
     if (i <= g.n_r) {
       const double h3 = (double)pt(g, H.p[2], i, j);
       if (i < g.n_r) {
