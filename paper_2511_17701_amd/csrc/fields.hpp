@@ -177,18 +177,22 @@ struct UpdateT {
   TriT<T> S;
   int3 half1, half2;  // staggering of the components in x1, x2
   int zero;
+  int edge;  // the row from which the update writes the horizon rows: n_f + 1, or
+             // none (-1: horizon_kernel follows)
 };
 
-// Stores v, the updated component c at (i, j), i > n_f, j an interior column of
-// the component, through the boundary conditions.  The thread that owns the
-// point also writes the ghost columns that mirror it and, from row n_f + 1, the
-// horizon rows (and saves what was there): every stored value has one writer
-// and no reader among the other threads, so an update and its boundaries are one
-// pass.  was: the stored value before (the update's kernels load everything
-// before their first store).  As passes of their own (two launches per updated triple, eight per
-// step) they took 38 us of a 354 us step at 512^2 and 24 of 79 at 40 x 56.
-// Five steps of the field stages at 1537 x 1023 in double precision: 1912 ->
-// 1707 us, of which the scalar rows give 40 and the loads ahead of the stores 100.
+// Where the threads of row n_f + 1 write the horizon rows of their column, one
+// after the other: for few rows, and for some more where the rest of the update
+// is long enough to hide them.  Elsewhere a launch more (horizon_kernel) is
+// shorter.  A step's field stages with the rows in the updates / in launches of
+// their own, us: 64^2 in double precision n_f = 4 65.3 / 64.2, 6 78.7 / 74.0, 8
+// 88.5 / 80.2, 24 177 / 130; 512^2 4 96.3 / 98.3, 6 114 / 109, 24 230 / 177;
+// 2048^2 4 825 / 837, 8 866 / 878, 16 958 / 963, 24 1066 / 1054 (single
+// precision: the same order, 8 at 512^2 115 / 108, at 2048^2 614 / 625).
+__host__ __device__ inline bool horizon_in_update(const Grid& g) {
+  return g.n_filter <= 4 || (g.n_filter <= 16 && g.plane >= (int64_t)1 << 21);
+}
+
 template <class T>
 __device__ inline void store_bc(const Grid& g, const UpdateT<T>& u, int c, int i, int j, double v, T was) {
   T* const X = u.X.p[c];
@@ -228,7 +232,7 @@ __device__ inline void store_bc(const Grid& g, const UpdateT<T>& u, int c, int i
         }
     }
   };
-  const bool edge = i == g.n_filter + 1;  // the row that the horizon rows take
+  const bool edge = i == u.edge;
   if (edge) {
     put(-g.ng, i - 1, j, h);
     if (comp)
@@ -239,6 +243,30 @@ __device__ inline void store_bc(const Grid& g, const UpdateT<T>& u, int c, int i
   const int hi = n - 1 - j;       // half: 0: column n, 1: column n + 1; node: 0: column n + 1
   const bool low = lo == 0 || lo == 1, high = h2 ? hi == 0 || hi == 1 : hi == 0;
   if (low | high) put(edge ? -g.ng : i, i, low ? -1 - lo : h2 ? n + hi : n + 1, c == 0 ? h : -h);
+}
+
+// The horizon rows of an updated triple as a pass of its own, one thread per
+// point of the rows [-ng, n_f]: what was there goes to S, the value (and
+// compensation) of row n_f + 1 takes its place.  For many filter passes, where
+// store_bc's walk over the rows would outlast the rest of the update.
+template <class T>
+__global__ void horizon_kernel(Grid g, UpdateT<T> u) {
+  const int j = launch_col() - g.ng, i = launch_row() - g.ng, e = g.n_filter + 1;
+  if (j >= g.n_th + g.ng || i >= e) return;
+  T was[3], h[3], l[3];
+  const bool comp = sizeof(T) == 4 && u.L.p[0];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    was[c] = pt(g, u.X.p[c], i, j);
+    h[c] = pt(g, u.X.p[c], e, j);
+    l[c] = comp ? pt(g, u.L.p[c], e, j) : (T)0;
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (u.S.p[0]) pt(g, u.S.p[c], i, j) = was[c];
+    pt(g, u.X.p[c], i, j) = h[c];
+    if (comp) pt(g, u.L.p[c], i, j) = l[c];
+  }
 }
 
 // ---------------------------------------------------------------- Faraday

@@ -180,8 +180,18 @@ grpic_status axis_bc(grpic_ctx* c, TriT<T> X, bool is_B, hipStream_t s) {
 // An updated triple with its boundary conditions (X0: absorbing targets; S:
 // where the triple before the update goes)
 template <class T>
-UpdateT<T> update_of(TriT<T> X, TriT<T> L, CTriT<T> X0, TriT<T> S, bool is_B) {
-  return UpdateT<T>{X, L, X0, S, is_B ? kStagB1 : kStagD1, is_B ? kStagB2 : kStagD2, is_B ? 1 : 2};
+UpdateT<T> update_of(const Grid& g, TriT<T> X, TriT<T> L, CTriT<T> X0, TriT<T> S, bool is_B) {
+  const int edge = horizon_in_update(g) ? g.n_filter + 1 : -1;
+  return UpdateT<T>{X, L, X0, S, is_B ? kStagB1 : kStagD1, is_B ? kStagB2 : kStagD2, is_B ? 1 : 2, edge};
+}
+
+// After the update of u: the horizon rows, where the update leaves them
+template <class T>
+grpic_status horizon_rows(const Grid& g, const UpdateT<T>& u, hipStream_t s) {
+  if (u.edge >= 0) return GRPIC_OK;
+  hipLaunchKernelGGL(horizon_kernel<T>, grid2(g.n_filter + 1 + g.ng, g.n_th + 2 * g.ng), kBlock2, 0, s, g, u);
+  LAUNCH_CHECK("horizon");
+  return GRPIC_OK;
 }
 
 // n_f binomial passes (Sec. 3.3.4) over the ncomp planes of A, up to
@@ -510,11 +520,10 @@ grpic_status field_advance_impl(grpic_ctx* c, const grpic_fields* F, int32_t sta
     hipLaunchKernelGGL((aux_kernel<T, true, false, kQ>), gaux, kBlock2, 0, s, g, c->tab, ctri<T>(F->B),
                        ctri<T>(F->D0), tri<T>(F->E), none<T>());
     LAUNCH_CHECK("aux_e");
-    hipLaunchKernelGGL((faraday_kernel<T, true, kQ>), gupd, kBlock2, 0, s, g, c->tab,
-                       update_of<T>(tri<T>(F->B0), none<T>(), ctri<T>(F->Binit), none<T>(), true), ctri<T>(F->E),
-                       ctri<T>(F->B));
+    const UpdateT<T> u = update_of<T>(g, tri<T>(F->B0), none<T>(), ctri<T>(F->Binit), none<T>(), true);
+    hipLaunchKernelGGL((faraday_kernel<T, true, kQ>), gupd, kBlock2, 0, s, g, c->tab, u, ctri<T>(F->E), ctri<T>(F->B));
     LAUNCH_CHECK("faraday");
-    return GRPIC_OK;
+    return horizon_rows<T>(g, u, s);
   }
   // current filter (n_f passes) on the freshly deposited J^{n+1/2}, T as the
   // second plane set
@@ -525,24 +534,25 @@ grpic_status field_advance_impl(grpic_ctx* c, const grpic_fields* F, int32_t sta
   hipLaunchKernelGGL((aux_kernel<T, true, true, kQ>), gaux, kBlock2, 0, s, g, c->tab, ctri<T>(F->B0),
                      ctri<T>(F->D), tri<T>(F->E), tri<T>(F->H));
   LAUNCH_CHECK("aux_eh");
-  hipLaunchKernelGGL((faraday_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab,
-                     update_of<T>(tri<T>(F->B), comp<T>(c, F->Bc), ctri<T>(F->Binit), tri<T>(F->B0), true),
-                     ctri<T>(F->E), ctri<T>(F->B));
+  const UpdateT<T> ub = update_of<T>(g, tri<T>(F->B), comp<T>(c, F->Bc), ctri<T>(F->Binit), tri<T>(F->B0), true);
+  hipLaunchKernelGGL((faraday_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab, ub, ctri<T>(F->E), ctri<T>(F->B));
   LAUNCH_CHECK("faraday");
+  if ((st = horizon_rows<T>(g, ub, s))) return st;
   // D0 += Ampere(H, (J0 + J)/2)
-  hipLaunchKernelGGL((ampere_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab,
-                     update_of<T>(tri<T>(F->D0), none<T>(), ctri<T>(F->Dinit), none<T>(), false), ctri<T>(F->H),
-                     tri<T>(F->J0), Jf, 0.5, 0.5, c->polar_k, none<T>());
+  const UpdateT<T> ud0 = update_of<T>(g, tri<T>(F->D0), none<T>(), ctri<T>(F->Dinit), none<T>(), false);
+  hipLaunchKernelGGL((ampere_kernel<T, false, kQ>), gupd, kBlock2, 0, s, g, c->tab, ud0, ctri<T>(F->H), tri<T>(F->J0), Jf,
+                     0.5, 0.5, c->polar_k, none<T>());
   LAUNCH_CHECK("ampere");
+  if ((st = horizon_rows<T>(g, ud0, s))) return st;
   // H from (B, D0); D0 <- D, D += Ampere(H, J), J0 <- J, J <- 0
   hipLaunchKernelGGL((aux_kernel<T, false, true, kQ>), gaux, kBlock2, 0, s, g, c->tab, ctri<T>(F->B),
                      ctri<T>(F->D0), none<T>(), tri<T>(F->H));
   LAUNCH_CHECK("aux_h");
-  hipLaunchKernelGGL((ampere_kernel<T, true, kQ>), gpl2, kBlock2, 0, s, g, c->tab,
-                     update_of<T>(tri<T>(F->D), comp<T>(c, F->Dc), ctri<T>(F->Dinit), tri<T>(F->D0), false),
-                     ctri<T>(F->H), Jf, tri<T>(F->J0), 1.0, 0.0, c->polar_k, Jclear);
+  const UpdateT<T> ud = update_of<T>(g, tri<T>(F->D), comp<T>(c, F->Dc), ctri<T>(F->Dinit), tri<T>(F->D0), false);
+  hipLaunchKernelGGL((ampere_kernel<T, true, kQ>), gpl2, kBlock2, 0, s, g, c->tab, ud, ctri<T>(F->H), Jf, tri<T>(F->J0),
+                     1.0, 0.0, c->polar_k, Jclear);
   LAUNCH_CHECK("ampere");
-  return GRPIC_OK;
+  return horizon_rows<T>(g, ud, s);
 }
 
 template <class T>
