@@ -106,6 +106,12 @@ __device__ inline T& pt(const Grid& g, T* __restrict__ p, int i, int j) {
   return elem(p + (int64_t)(i + g.ng) * g.ld, (uint32_t)(j + g.ng));
 }
 
+// Plane point (i, j) of a if first, else of b.
+template <class T>
+__device__ inline T pt_of(const Grid& g, bool first, const T* __restrict__ a, const T* __restrict__ b, int i, int j) {
+  return (first ? a : b)[(int64_t)(i + g.ng) * g.ld + (j + g.ng)];
+}
+
 // ---------------------------------------------------------------- aux E, H
 // eq. discretized-auxE/-auxH with the volume-weighted radial averages of
 // Sec. 3.3.1 (weights sqrt(h)/sin(theta)); for i in [-1, n_r], j in [0, n_th].
@@ -193,6 +199,16 @@ __host__ __device__ inline bool horizon_in_update(const Grid& g) {
   return g.n_filter <= 4 || (g.n_filter <= 16 && g.plane >= (int64_t)1 << 21);
 }
 
+// Stores v, the updated component c at (i, j), i > n_f, j an interior column of
+// the component, through the boundary conditions.  The thread that owns the
+// point also writes the ghost columns that mirror it and, from row u.edge, the
+// horizon rows (and saves what was there): every stored value has one writer
+// and no reader among the other threads, so an update and its boundaries are one
+// pass.  was: the stored value before (the update's kernels load everything
+// before their first store).  As passes of their own (two launches per updated triple, eight per
+// step) they took 38 us of a 354 us step at 512^2 and 24 of 79 at 40 x 56.
+// Five steps of the field stages at 1537 x 1023 in double precision: 1912 ->
+// 1707 us, of which the scalar rows give 40 and the loads ahead of the stores 100.
 template <class T>
 __device__ inline void store_bc(const Grid& g, const UpdateT<T>& u, int c, int i, int j, double v, T was) {
   T* const X = u.X.p[c];
@@ -329,21 +345,19 @@ __global__ void ampere_kernel(Grid g, Tables t, UpdateT<T> u, CTriT<T> H, TriT<T
 #pragma unroll
   for (int c = 0; c < 3; ++c) ja[c] = pt(g, Ja.p[c], i, j);
   if (i > g.n_filter && j >= 0 && j <= g.n_th) {
-    const bool half = j < g.n_th, comp = sizeof(T) == 4 && u.L.p[0];
-    T was[3] = {}, add[3] = {}, jb[3] = {};  // (add: the compensation)
-    auto load = [&](int c) {
-      was[c] = pt(g, u.X.p[c], i, j);
-      if (comp) add[c] = pt(g, u.L.p[c], i, j);
-      if (!kFinal) jb[c] = pt(g, Jb.p[c], i, j);
-    };
-    load(0);
-    load(2);
-    if (half) load(1);  // (column n_th as in the Faraday update)
+    const bool half = j < g.n_th;  // theta-staggered components exist
+    T was[3];
     double v[3], J[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      v[c] = (double)was[c] + (double)add[c];
-      J[c] = kFinal ? (double)ja[c] : wa * (double)ja[c] + wb * (double)jb[c];
+      // component 1 in column n_th is a ghost, which the thread of column n_th - 1
+      // writes: a value of its target plane instead (unused), since a branch
+      // around these loads costs 6 % of the pass (4096^2, single precision)
+      const bool own = half || c != 1;
+      was[c] = pt_of(g, own, u.X.p[c], u.X0.p[c], i, j);
+      const double add = sizeof(T) == 4 && u.L.p[0] ? (double)pt_of(g, own, u.L.p[c], u.X0.p[c], i, j) : 0.0;
+      v[c] = (double)was[c] + add;
+      J[c] = kFinal ? (double)ja[c] : wa * (double)ja[c] + wb * (double)pt(g, Jb.p[c], i, j);
     }
     const double fpi = 4.0 * kPi;
     if (i <= g.n_r) {
