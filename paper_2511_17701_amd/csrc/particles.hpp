@@ -665,13 +665,14 @@ __device__ inline void coordinate_update(const Grid& g, const Tables& tab, const
                                          int i1, R dx1, int i2, R dx2, R u1, R u2, R u3, R mass2, R& d1, R& d2,
                                          R& w3) {
   const R dt = uni<R>(g).dt, half = (R)0.5;
-  const R iu0 = m.alpha * rsqrt(mass2 + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 +
-                                (R)2 * m.hu13 * u1 * u3);
+  const R ig = rsqrt(mass2 + m.hu11 * u1 * u1 + m.hu22 * u2 * u2 + m.hu33 * u3 * u3 + (R)2 * m.hu13 * u1 * u3);
+  const R iu0 = m.alpha * ig;
   R n1 = dt * ((m.hu11 * u1 + m.hu13 * u3) * iu0 - m.beta1);
   R n2 = dt * (m.hu22 * u2 * iu0);
   w3 = (m.hu13 * u1 + m.hu33 * u3) * iu0;
   d1 = (R)0;
   d2 = (R)0;
+  scale_momenta(ig, u1, u2, u3, mass2);
   R o1 = (R)__builtin_nan(""), o2 = o1;  // the iterate before d (none yet)
   for (int it = 1;; ++it) {
     const bool repeat = n1 == d1 && n2 == d2, cycle = kCycle && n1 == o1 && n2 == o2;
@@ -983,9 +984,12 @@ constexpr int kDepRep = 2;  // copies of the deposit tile
 // lapse-weighted phi velocity alpha u^3 / gamma at the path midpoint (ia + xm, ja + ym)
 template <int SER, class T>
 __device__ inline T vphi_mid(const Grid& g, const Tables& tab, int ia, T xm, int ja, T ym, T u1, T u2, T u3) {
+  T mass2 = (T)1;
+  if constexpr (sizeof(T) == 4)  // an estimate of 1 / gamma, up to factors of r and the cell sizes
+    scale_momenta(rcp(fmaxf(fmaxf(fabsf(u1), fabsf(u2)), fmaxf(fabsf(u3), mass2))), u1, u2, u3, mass2);
   const AnchorT<T> an = anchor_at<SER>(g, tab, ia, ja, (T)0);
   return velocity_from(g, rsc_at<SER>(g, tab, an, ia, (double)ia + (double)xm, xm, ja, (double)ja + (double)ym, ym), u1,
-                       u2, u3, (T)1).w3;
+                       u2, u3, mass2).w3;
 }
 
 // The nodes and weights of one move: footprint [ia-1, ia+2] x [ja-1, ja+2].
