@@ -146,13 +146,13 @@ __global__ void __launch_bounds__(kChargeBlock) charge_kernel(Grid g, ParticleAr
   }
   // the anchor: the first chunk from the middle on that has a live particle
   // (block-uniform votes), else the first of the others
-  int ai = 0, aj = 0;
+  int ai = 0, aj = 0, span = 0;
   bool any = false;
 #pragma unroll
   for (int c = 0; c < kChargeChunks; ++c) {
     const Slot& s = sl[(c + kChargeChunks / 2) % kChargeChunks];
     if (!any) {
-      any = block_anchor(s.act, s.i1, s.i2, ai, aj);
+      any = block_anchor(g, s.act, s.i1, s.i2, ai, aj, span);
       lds_barrier();  // the anchor's LDS cells are read before the next vote writes them
     }
   }

@@ -349,7 +349,7 @@ grpic_status push_impl(grpic_ctx* c, const grpic_fields* F, const grpic_particle
 
 // counts: null, or the sort's zeroed cell counters, which the ranked kernels
 // fill (with each live slot's rank in its cell written to i1p)
-template <bool kRank>
+template <bool kRank, bool kSparse>
 void launch_push_deposit(grpic_ctx* c, const grpic_fields* F, const grpic_particles* P, int* counts,
                          hipStream_t s) {
   if (c->f32) {
@@ -363,9 +363,9 @@ void launch_push_deposit(grpic_ctx* c, const grpic_fields* F, const grpic_partic
     CurrentPlanesT<float> cp{{(float*)F->J[0], (float*)F->J[1], (float*)F->J[2]}};
     const ParticleArraysT<float> a = arrays<float>(P);
     switch (c->g.ser) {
-      case 2: hipLaunchKernelGGL((push_deposit_kernel_f32<2, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
-      case 1: hipLaunchKernelGGL((push_deposit_kernel_f32<1, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
-      default: hipLaunchKernelGGL((push_deposit_kernel_f32_lib<kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      case 2: hipLaunchKernelGGL((push_deposit_kernel_f32<2, kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      case 1: hipLaunchKernelGGL((push_deposit_kernel_f32<1, kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      default: hipLaunchKernelGGL((push_deposit_kernel_f32_lib<kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
     }
   } else {
     constexpr int kBk = kDepBlock;
@@ -378,33 +378,42 @@ void launch_push_deposit(grpic_ctx* c, const grpic_fields* F, const grpic_partic
     CurrentPlanesT<double> cp{{(double*)F->J[0], (double*)F->J[1], (double*)F->J[2]}};
     const ParticleArraysT<double> a = arrays<double>(P);
     switch (c->g.ser) {
-      case 3: hipLaunchKernelGGL((push_deposit_kernel<3, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
-      case 2: hipLaunchKernelGGL((push_deposit_kernel<2, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
-      case 1: hipLaunchKernelGGL((push_deposit_kernel<1, kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
-      default: hipLaunchKernelGGL((push_deposit_kernel_lib<kRank>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      case 3: hipLaunchKernelGGL((push_deposit_kernel<3, kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      case 2: hipLaunchKernelGGL((push_deposit_kernel<2, kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      case 1: hipLaunchKernelGGL((push_deposit_kernel<1, kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
+      default: hipLaunchKernelGGL((push_deposit_kernel_lib<kRank, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, gp, a, cp, counts); break;
     }
   }
 }
 
 grpic_status push_deposit_impl(grpic_ctx* c, const grpic_fields* F, const grpic_particles* P, int* counts,
                                hipStream_t s) {
-  if (counts) launch_push_deposit<true>(c, F, P, counts, s);
-  else launch_push_deposit<false>(c, F, P, nullptr, s);
+  const bool sparse = is_sparse(c->g, P->n);
+  if (counts && sparse) launch_push_deposit<true, true>(c, F, P, counts, s);
+  else if (counts) launch_push_deposit<true, false>(c, F, P, counts, s);
+  else if (sparse) launch_push_deposit<false, true>(c, F, P, nullptr, s);
+  else launch_push_deposit<false, false>(c, F, P, nullptr, s);
   LAUNCH_CHECK("push_deposit");
   return GRPIC_OK;
 }
 
-template <class T>
-grpic_status deposit_impl(grpic_ctx* c, const grpic_particles* P, const grpic_fields* F, hipStream_t s) {
+template <class T, bool kSparse>
+void launch_deposit(grpic_ctx* c, const grpic_particles* P, const grpic_fields* F, hipStream_t s) {
   CurrentPlanesT<T> cp{{(T*)F->J[0], (T*)F->J[1], (T*)F->J[2]}};
   constexpr int kBk = kDepBlock;
   const dim3 grid((unsigned)((P->n + kBk - 1) / kBk));
   switch (c->g.ser) {
-    case 3: hipLaunchKernelGGL((deposit_kernel<T, kMapForm<T>>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
-    case 2: hipLaunchKernelGGL((deposit_kernel<T, 2>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
-    case 1: hipLaunchKernelGGL((deposit_kernel<T, 1>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
-    default: hipLaunchKernelGGL((deposit_kernel<T, 0>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
+    case 3: hipLaunchKernelGGL((deposit_kernel<T, kMapForm<T>, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
+    case 2: hipLaunchKernelGGL((deposit_kernel<T, 2, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
+    case 1: hipLaunchKernelGGL((deposit_kernel<T, 1, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
+    default: hipLaunchKernelGGL((deposit_kernel<T, 0, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
   }
+}
+
+template <class T>
+grpic_status deposit_impl(grpic_ctx* c, const grpic_particles* P, const grpic_fields* F, hipStream_t s) {
+  if (is_sparse(c->g, P->n)) launch_deposit<T, true>(c, P, F, s);
+  else launch_deposit<T, false>(c, P, F, s);
   LAUNCH_CHECK("deposit");
   return GRPIC_OK;
 }

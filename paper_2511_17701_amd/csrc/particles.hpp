@@ -978,13 +978,34 @@ __device__ inline void atomic_add(float* p, float v) { unsafeAtomicAdd(p, v); }
 // deposits J^1 and J^2 (normalised by 1/dt) on the edges of the cell it lies
 // in, with first-order weights at the segment midpoint; J^3 = q alpha u^3 /
 // gamma goes to the four nodes around the path midpoint.
-// Particles per block of the deposit passes (two wavefronts) and the LDS tile
-// of kTI rows x kTJ columns around the block's anchor cell, which holds the
-// footprints of cells up to 2 rows and 6 columns from it.  Blocks of 64 in
+// Particles per block of the deposit passes (two wavefronts).  Blocks of 64 in
 // single precision: +1.6 % (2048^2, 16 per cell).
 constexpr int kDepBlock = 128;
-constexpr int kTI = 8, kTJ = 16;
-constexpr int kDepRep = 2;  // copies of the deposit tile
+
+// The LDS tile around the block's anchor cell has kTilePlane nodes per
+// component, laid out as 1 << LC columns: 8 rows of 16 in two copies, between
+// which the adding lanes alternate (a cell's run of lanes then hits one address
+// with half of its lanes per copy), 8 rows of 32, or 4 of 64.  It holds the
+// footprints of cells up to kI rows and kJ - 1 columns from the anchor.
+constexpr int kTilePlane = 2 * kDepBlock;
+template <int LC>
+struct TileT {
+  static constexpr int kC = 1 << LC, kRows = LC == 6 ? 4 : 8, kRep = kTilePlane / (kC * kRows);
+  static constexpr int kI = kRows / 2 - 1, kJ = kC / 2 - 1;  // the anchor cell's row and column
+};
+
+// Sets of at least kDenseSlots slots per cell take the tile of 16 columns: 128
+// cell-sorted slots then span 12 cells at most, of the 13 that it holds.  Below,
+// every block takes its tile by the columns that its particles span (kSparse; 0:
+// no tile).  Fused pass at 1024^2 in single precision, just sorted / after ten
+// steps without a sort, us, with 16 columns and by the span: 16 per cell 450 /
+// 459 and 456 / 473; 12 345 / 381 and 354 / 377; 10 299 / 380 and 299 / 321; 6 408
+// / 542 and 194 / 212; 4 347 / 457 and 156 / 201; 2 214 / 285 and 84 / 208; in double
+// precision 12 637 / 648 and 658 / 642; 10 556 / 552 and 559 / 552; 6 439 / 561 and
+// 363 / 361; 2 241 / 319 and 141 / 249.
+constexpr int kDenseSlots = 11;
+inline bool is_sparse(const Grid& g, int64_t n) { return n < (int64_t)kDenseSlots * g.n_r * g.n_th; }
+__device__ inline int tile_columns(int span) { return span <= 40 ? 5 : span <= 160 ? 6 : 0; }
 
 // lapse-weighted phi velocity alpha u^3 / gamma at the path midpoint (ia + xm, ja + ym)
 template <int SER, class T>
@@ -1143,32 +1164,90 @@ __device__ inline void lds_barrier() {
 
 // The cell a block's tile is laid around: that of a live particle in the
 // middle of the block's slots (cell-sorted: near the middle of its cells), the
-// second wavefront's first or else the first one's last.  Every thread of the
-// block (two wavefronts) calls this; false if the block has no live particle.
-// It passes a block barrier.
-__device__ inline bool block_anchor(bool act, int ia, int ja, int& ai, int& aj) {
-  __shared__ int cell[2][2];
+// second wavefront's first or else the first one's last.  span: the columns from
+// the block's first live particle to its last (the shorter way where the cells
+// wrap from the end of one theta row to the next).  Every thread of the block
+// (two wavefronts) calls this; false if the block has no live particle.  It
+// passes a block barrier.
+__device__ inline bool block_anchor(const Grid& g, bool act, int ia, int ja, int& ai, int& aj, int& span) {
+  __shared__ int4 cell[2];  // row (INT_MIN: no live particle) and column of a wavefront's particle next to the
+                            // block's middle, column of that at its end of the block
   const unsigned long long live = __ballot(act);
   const int wv = (int)threadIdx.x >> 6;
-  const int lane = wv ? __ffsll((long long)live) - 1 : 63 - __clzll((long long)live);
-  const int wi = __builtin_amdgcn_readlane(ia, lane & 63), wj = __builtin_amdgcn_readlane(ja, lane & 63);
-  if ((threadIdx.x & 63) == 0) {
-    cell[wv][0] = live ? wi : INT_MIN;
-    cell[wv][1] = wj;
-  }
+  const int first = (__ffsll((long long)live) - 1) & 63, last = (63 - __clzll((long long)live)) & 63;
+  const int mid = wv ? first : last, end = wv ? last : first;
+  const int wi = __builtin_amdgcn_readlane(ia, mid), wj = __builtin_amdgcn_readlane(ja, mid);
+  const int we = __builtin_amdgcn_readlane(ja, end);
+  if ((threadIdx.x & 63) == 0) cell[wv] = int4{live ? wi : INT_MIN, wj, we, 0};
   lds_barrier();
-  const int s = __builtin_amdgcn_readfirstlane(cell[1][0]) != INT_MIN;
-  ai = __builtin_amdgcn_readfirstlane(cell[s][0]);
-  aj = __builtin_amdgcn_readfirstlane(cell[s][1]);
-  return ai != INT_MIN;
+  const int4 c0 = cell[0], c1 = cell[1];
+  const int r0 = __builtin_amdgcn_readfirstlane(c0.x), r1 = __builtin_amdgcn_readfirstlane(c1.x);
+  const int m0 = __builtin_amdgcn_readfirstlane(c0.y), m1 = __builtin_amdgcn_readfirstlane(c1.y);
+  const int e0 = __builtin_amdgcn_readfirstlane(c0.z), e1 = __builtin_amdgcn_readfirstlane(c1.z);
+  const bool s0 = r0 != INT_MIN, s1 = r1 != INT_MIN;
+  ai = s1 ? r1 : r0;
+  aj = s1 ? m1 : m0;
+  const int d = abs((s0 ? e0 : m1) - (s1 ? e1 : m0));
+  span = min(d, g.n_th - d);
+  return s0 | s1;
+}
+
+// Adds a lane's contributions to the tile, its cell (di, dj) from the anchor;
+// false if the footprint leaves the tile.
+template <int LC, class T>
+__device__ inline bool tile_add(double* tile, int di, int dj, const ContribT<T>& c, const T a[4], const T m[4], bool stay,
+                                bool own_a, bool own_m) {
+  using L = TileT<LC>;
+  const int row = di + L::kI - 1, col = dj + L::kJ - 1;  // the footprint's first row and column
+  if ((unsigned)row > (unsigned)(L::kRows - 4) || (unsigned)col > (unsigned)(L::kC - 4)) return false;
+  double* t = tile + (row + 1) * L::kC + (col + 1);
+  if (L::kRep == 2) t += (threadIdx.x & 2) * (kTilePlane / 4);
+  if (own_a) {
+    atomicAdd(t, (double)a[0]);
+    atomicAdd(t + 1, (double)a[1]);
+    atomicAdd(t + kTilePlane, (double)a[2]);
+    atomicAdd(t + kTilePlane + L::kC, (double)a[3]);
+  }
+  if (!stay) {
+    double* p = t + c.di * L::kC + c.dj;
+    atomicAdd(p, (double)c.j1[2]);
+    atomicAdd(p + 1, (double)c.j1[3]);
+    atomicAdd(p + kTilePlane, (double)c.j2[2]);
+    atomicAdd(p + kTilePlane + L::kC, (double)c.j2[3]);
+  }
+  if (own_m) {
+    double* p = t + 2 * kTilePlane + c.km * L::kC + c.lm;
+    atomicAdd(p, (double)m[0]);
+    atomicAdd(p + 1, (double)m[1]);
+    atomicAdd(p + L::kC, (double)m[2]);
+    atomicAdd(p + L::kC + 1, (double)m[3]);
+  }
+  return true;
+}
+
+// Adds the tile to the planes, the copies summed in a fixed order (nodes outside
+// the planes are nobody's: their values are zero and never added).
+template <int LC, class T>
+__device__ inline void tile_flush(const Grid& g, const CurrentPlanesT<T>& cp, const double* tile, int ai, int aj) {
+  using L = TileT<LC>;
+  constexpr int kNodes = L::kRows * L::kC;
+  const int t = (int)threadIdx.x;
+  const int64_t base = ix(g, ai - L::kI, aj - L::kJ), off = (int64_t)(t >> LC) * g.ld + (t & (L::kC - 1));
+#pragma unroll
+  for (int comp = 0; comp < 3; ++comp) {
+#pragma unroll
+    for (int e = 0; e < kNodes; e += kDepBlock) {
+      double val = tile[comp * kTilePlane + e + t];
+      if (L::kRep == 2) val += tile[comp * kTilePlane + kNodes + e + t];
+      if (val != 0.0) atomic_add(cp.J[comp] + (base + (int64_t)(e / L::kC) * g.ld) + off, (T)val);
+    }
+  }
 }
 
 // Block-level deposit: the lanes add their contributions (12 values, 8 when a
 // particle stays in its cell) with LDS atomics to an LDS tile around the
-// block's anchor cell, in kDepRep copies between which the adding lanes
-// alternate (a cell's run of lanes then hits one address with half of its
-// lanes per copy); the tile is then added to the planes with one global atomic
-// per touched node.  The tile is in double precision in both forms: on gfx950 an
+// block's anchor cell; the tile is then added to the planes with one global
+// atomic per touched node.  The tile is in double precision in both forms: on gfx950 an
 // LDS add of 64 floats takes 194 cycles of the CU even without conflicts, one
 // of 64 doubles 9 (21, 93 and 193 with 2, 8 and 64 lanes on one address), and
 // the float adds bound the single-precision pass (2048^2, 16 per cell, ten
@@ -1180,25 +1259,27 @@ __device__ inline bool block_anchor(bool act, int ia, int ja, int& ai, int& aj) 
 // of one theta row to the next, or the slots have lost their cell order) adds
 // straight to the planes.  The anchor takes the place of a reduction of the
 // block's footprint (four wavefront minima and a round trip through LDS), and
-// of a second form for whole blocks that do not fit, with run sums over lanes.
+// the wider tiles that of a second form with run sums over lanes for whole blocks that
+// do not fit.
 // (ten steps and a sort: 512^2 with 16 per cell in double precision 3832 ->
 // 3574 us, 2048^2 with 32 in single 57.2 -> 54.3 ms; without the flush 2 %,
 // without any deposit 6 % (single) to 10 % (double) less.)
 // Every lane of the block calls this; it passes a block barrier.
-template <class T, int SER>
+template <class T, int SER, bool kSparse>
 __device__ inline void deposit_block(const Grid& g, const Tables& tab, const CurrentPlanesT<T>& cp, const Move<T>& mv,
                                      bool act) {
-  constexpr int kBlk = kDepBlock, kPlane = kTI * kTJ;
-  __shared__ __align__(16) double tile[kDepRep][3][kPlane];
+  constexpr int kBlk = kDepBlock, kPlane = kTilePlane;
+  __shared__ __align__(16) double tile[3][kPlane];
   {  // zero the tile (16-byte stores)
-    double2* fv = reinterpret_cast<double2*>(&tile[0][0][0]);
-    static_assert(kDepRep * 3 * kPlane % (2 * kBlk) == 0, "whole stores per thread");
+    double2* fv = reinterpret_cast<double2*>(&tile[0][0]);
+    static_assert(3 * kPlane % (2 * kBlk) == 0, "whole stores per thread");
 #pragma unroll
-    for (int e = 0; e < kDepRep * 3 * kPlane / 2; e += kBlk) fv[e + (int)threadIdx.x] = double2{};
+    for (int e = 0; e < 3 * kPlane / 2; e += kBlk) fv[e + (int)threadIdx.x] = double2{};
   }
-  int ai, aj;
-  if (!block_anchor(act, mv.ia, mv.ja, ai, aj)) return;  // no live charged particle in this block (uniform)
-  const int i0 = ai - (kTI / 2 - 1), j0 = aj - (kTJ / 2 - 1);  // the tile's first row and column
+  int ai, aj, span;
+  if (!block_anchor(g, act, mv.ia, mv.ja, ai, aj, span)) return;  // no live charged particle in this block (uniform)
+  const int lc = kSparse ? tile_columns(span) : 4;  // (uniform)
+  double* const t = &tile[0][0];
   if (act) {
     const ContribT<T> c = make_contrib<T, SER>(g, tab, mv);
     const bool stay = (c.di | c.dj) == 0;
@@ -1210,10 +1291,10 @@ __device__ inline void deposit_block(const Grid& g, const Tables& tab, const Cur
       a[3] += c.j2[3];
     }
     T m[4] = {c.j3[0], c.j3[1], c.j3[2], c.j3[3]};
-    const int corner = c.km * kTJ + c.lm;
     // whether the pair's lanes share their cell, and the J^3 corner too
-    const bool fa = (pair_swap(mv.ia, -1) == mv.ia) & (pair_swap(mv.ja, -1) == mv.ja);
-    const bool fm = fa & (pair_swap(corner, INT_MIN) == corner);
+    const int corner = c.km * 16 + c.lm;
+    const int oi = pair_swap(mv.ia, -1), oj = pair_swap(mv.ja, -1), oc = pair_swap(corner, INT_MIN);
+    const bool fa = (oi == mv.ia) & (oj == mv.ja), fm = fa & (oc == corner);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const T sa = a[q] + pair_swap(a[q]), sm = m[q] + pair_swap(m[q]);
@@ -1222,30 +1303,12 @@ __device__ inline void deposit_block(const Grid& g, const Tables& tab, const Cur
     }
     const bool second = (threadIdx.x & 1) != 0;
     const bool own_a = !(fa & second), own_m = !(fm & second);
-    const int row = mv.ia - 1 - i0, col = mv.ja - 1 - j0;  // the footprint's first row and column
-    if ((unsigned)row <= (unsigned)(kTI - 4) && (unsigned)col <= (unsigned)(kTJ - 4)) {
-      double* t = &tile[(threadIdx.x >> 1) % kDepRep][0][0] + (row + 1) * kTJ + (col + 1);
-      if (own_a) {
-        atomicAdd(t, (double)a[0]);
-        atomicAdd(t + 1, (double)a[1]);
-        atomicAdd(t + kPlane, (double)a[2]);
-        atomicAdd(t + kPlane + kTJ, (double)a[3]);
-      }
-      if (!stay) {
-        double* p = t + c.di * kTJ + c.dj;
-        atomicAdd(p, (double)c.j1[2]);
-        atomicAdd(p + 1, (double)c.j1[3]);
-        atomicAdd(p + kPlane, (double)c.j2[2]);
-        atomicAdd(p + kPlane + kTJ, (double)c.j2[3]);
-      }
-      if (own_m) {
-        double* p = t + 2 * kPlane + corner;
-        atomicAdd(p, (double)m[0]);
-        atomicAdd(p + 1, (double)m[1]);
-        atomicAdd(p + kTJ, (double)m[2]);
-        atomicAdd(p + kTJ + 1, (double)m[3]);
-      }
-    } else {
+    const int di = mv.ia - ai, dj = mv.ja - aj;
+    bool in = false;
+    if constexpr (!kSparse) in = tile_add<4>(t, di, dj, c, a, m, stay, own_a, own_m);
+    else if (lc == 5) in = tile_add<5>(t, di, dj, c, a, m, stay, own_a, own_m);
+    else if (lc == 6) in = tile_add<6>(t, di, dj, c, a, m, stay, own_a, own_m);
+    if (!in) {
       const int64_t o = ix(g, mv.ia, mv.ja), ld = g.ld;
       if (own_a) {
         atomic_add(cp.J[0] + o, a[0]);
@@ -1269,21 +1332,11 @@ __device__ inline void deposit_block(const Grid& g, const Tables& tab, const Cur
       }
     }
   }
+  if (lc == 0) return;
   lds_barrier();
-  // flush, the copies summed in a fixed order (nodes outside the planes are
-  // nobody's: their values are zero and never added)
-  const int64_t base = ix(g, i0, j0);
-  const int64_t off = (int64_t)(threadIdx.x / kTJ) * g.ld + threadIdx.x % kTJ;
-#pragma unroll
-  for (int comp = 0; comp < 3; ++comp) {
-#pragma unroll
-    for (int e = 0; e < kPlane; e += kBlk) {
-      double val = tile[0][comp][e + threadIdx.x];
-#pragma unroll
-      for (int r = 1; r < kDepRep; ++r) val += tile[r][comp][e + threadIdx.x];
-      if (val != 0.0) atomic_add(cp.J[comp] + (base + (int64_t)(e / kTJ) * g.ld) + off, (T)val);
-    }
-  }
+  if (!kSparse) tile_flush<4>(g, cp, t, ai, aj);
+  else if (lc == 5) tile_flush<5>(g, cp, t, ai, aj);
+  else tile_flush<6>(g, cp, t, ai, aj);
 }
 
 // ------------------------------------------------------------------ cell ranks
@@ -1394,69 +1447,69 @@ __global__ void __launch_bounds__(kPushBlock) push_kernel_f32(Grid g, Tables tab
   (void)push_one_f32<SER>(g, tab, fp, from_slot(P, (int64_t)blockIdx.x * kPushBlock), threadIdx.x);
 }
 
-template <class T, int SER>
+template <class T, int SER, bool kSparse>
 __global__ void __launch_bounds__(kDepBlock) deposit_kernel(Grid g, Tables tab, ParticleArraysT<T> P,
                                                             CurrentPlanesT<T> cp) {
   const Move<T> mv = load_move(g, from_slot(P, (int64_t)blockIdx.x * kDepBlock), threadIdx.x);
-  deposit_block<T, SER>(g, tab, cp, mv, mv.dep && move_in_range(g, mv));
+  deposit_block<T, SER, kSparse>(g, tab, cp, mv, mv.dep && move_in_range(g, mv));
 }
 
 // Push and deposit in one pass: the deposit takes the move from registers and
 // J^3 from the push's own midpoint metric; the previous position is not
 // stored.  kRank: the pass also ranks the slots by their cell after the push
 // for the cell sort (rank_fused; counts: the sort's zeroed cell counters).
-template <int SER, bool kRank>
+template <int SER, bool kRank, bool kSparse>
 __global__ void __launch_bounds__(kDepBlock) GRPIC_FP64_PUSH_OCCUPANCY
 push_deposit_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp, int* counts) {
   const ParticleArraysT<double> Q = from_slot(P, spread_block() * kDepBlock);
   if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<double> mv = push_one<SER, false>(g, tab, fp, Q, threadIdx.x);
-  deposit_block<double, SER>(g, tab, cp, mv, mv.dep);
+  deposit_block<double, SER, kSparse>(g, tab, cp, mv, mv.dep);
   if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 // library path in FP64 (coarse grids): the library exp and sincos and the map
 // factors need more registers than the series paths; three wavefronts per SIMD
 // leave room for them without spills
-template <bool kRank>
+template <bool kRank, bool kSparse>
 __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(3)))
 push_deposit_kernel_lib(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P, CurrentPlanes cp,
                         int* counts) {
   const ParticleArraysT<double> Q = from_slot(P, spread_block() * kDepBlock);
   if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<double> mv = push_one<0, false>(g, tab, fp, Q, threadIdx.x);
-  deposit_block<double, 0>(g, tab, cp, mv, mv.dep);
+  deposit_block<double, 0, kSparse>(g, tab, cp, mv, mv.dep);
   if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
-template <int SER, bool kRank>
+template <int SER, bool kRank, bool kSparse>
 __device__ inline void push_deposit_f32(const Grid& g, const Tables& tab, const GatherPlanesT<float>& fp,
                                         const ParticleArraysT<float>& P, const CurrentPlanesT<float>& cp,
                                         int* counts) {
   const ParticleArraysT<float> Q = from_slot(P, (int64_t)blockIdx.x * kDepBlock);
   if constexpr (kRank) rank_clear(block_rank_table<kPushRankBits>());
   const Move<float> mv = push_one_f32<SER, false>(g, tab, fp, Q, threadIdx.x);
-  deposit_block<float, SER>(g, tab, cp, mv, mv.dep);
+  deposit_block<float, SER, kSparse>(g, tab, cp, mv, mv.dep);
   if constexpr (kRank) rank_fused(g, Q.i1p, threadIdx.x, mv.cell, counts);
 }
 
 // series paths: 6 wavefronts per SIMD (80 VGPRs; the compiler's own allocation
 // takes a few more and 5 wavefronts, 1 to 2 % slower at 2048^2 with 16 per cell)
-template <int SER, bool kRank>
+template <int SER, bool kRank, bool kSparse>
 __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(6))) push_deposit_kernel_f32(Grid g, Tables tab, GatherPlanesT<float> fp,
                                                                      ParticleArraysT<float> P,
                                                                      CurrentPlanesT<float> cp, int* counts) {
-  push_deposit_f32<SER, kRank>(g, tab, fp, P, cp, counts);
+  push_deposit_f32<SER, kRank, kSparse>(g, tab, fp, P, cp, counts);
 }
 
 // library path (coarse grids and the general quasi-spherical map): held to 5
 // wavefronts per SIMD (a few spilled registers), 11 % faster than the 4 that
 // its 100 VGPRs would give
-template <bool kRank>
+template <bool kRank, bool kSparse>
 __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(5)))
 push_deposit_kernel_f32_lib(Grid g, Tables tab, GatherPlanesT<float> fp, ParticleArraysT<float> P,
                             CurrentPlanesT<float> cp, int* counts) {
-  push_deposit_f32<0, kRank>(g, tab, fp, P, cp, counts);
+  push_deposit_f32<0, kRank, kSparse>(g, tab, fp, P, cp, counts);
 }
 
 }  // namespace grpic
