@@ -101,102 +101,120 @@ diag_particles_kernel(Grid g, Tables tab, ParticleArraysT<T> P, double B0, T* __
 // particle's mirror image in the nearer axis doubles an axis-row value).  A
 // block of kChargeBlock threads takes kChargeChunks chunks of consecutive
 // slots and adds them with LDS atomics to a tile around the cell of a particle
-// in the middle of its first chunk, in two copies between which the lane pairs
-// alternate (pairs on one cell summed first, as in the deposit); a particle
+// in their middle (pairs on one cell summed first, as in the deposit); a particle
 // outside the tile adds straight to the plane.  The tile is in double precision
 // (see deposit_block) and the flush adds one global atomic per touched node.
 // Bound by the LDS adds: with float adds the pass took 0.83 ms, with these
 // 0.43, and the former run sums by shuffles with four global atomics per run
 // 3.12 (2048 x 1536 cells, 16 per cell, single precision).
 constexpr int kChargeBlock = 128, kChargeChunks = 2;
-constexpr int kChargeTI = 16, kChargeTJ = 32, kChargeRep = 2;
 
-template <class T>
+// The tile's nodes as 1 << LC columns: 16 rows of 32 in two copies between which
+// the lane pairs alternate, 16 of 64, or 8 of 128.  Sparse sets (is_sparse) take
+// one of the wider ones by the columns that the block spans (0: none).  Whole
+// diagnostics at 1024^2 in single precision, just sorted / ten steps later, us,
+// with 32 columns around slot 192 of the 256 and this: 8 per cell 386 / 445 and 309
+// / 312; 4 289 / 336 and 197 / 205; 2 221 / 257 and 162 / 182.
+constexpr int kChargeNodes = 1024;
+template <int LC>
+struct ChargeTile {
+  static constexpr int kC = 1 << LC, kRows = LC == 7 ? 8 : 16, kRep = kChargeNodes / (kC * kRows);
+  static constexpr int kI = kRows / 2 - 1, kJ = kC / 2 - 1;  // the anchor cell's row and column
+};
+__device__ inline int charge_columns(int span) { return span <= 56 ? 6 : span <= 320 ? 7 : 0; }
+
+// Adds the four node values of a cell (di, dj) from the anchor; false if they leave the tile.
+template <int LC>
+__device__ inline bool charge_add(double* tile, int di, int dj, const double v[4]) {
+  using L = ChargeTile<LC>;
+  const int row = di + L::kI, col = dj + L::kJ;
+  if ((unsigned)row >= (unsigned)(L::kRows - 1) || (unsigned)col >= (unsigned)(L::kC - 1)) return false;
+  double* p = tile + row * L::kC + col;
+  if (L::kRep == 2) p += (threadIdx.x & 2) * (kChargeNodes / 4);
+  atomicAdd(p, v[0]);
+  atomicAdd(p + 1, v[1]);
+  atomicAdd(p + L::kC, v[2]);
+  atomicAdd(p + L::kC + 1, v[3]);
+  return true;
+}
+
+template <int LC, class T>
+__device__ inline void charge_flush(const Grid& g, T* Q, const double* tile, int ai, int aj) {
+  using L = ChargeTile<LC>;
+  constexpr int kNodes = L::kRows * L::kC;
+  T* const q0 = Q + ix(g, ai - L::kI, aj - L::kJ);
+#pragma unroll
+  for (int e = 0; e < kNodes; e += kChargeBlock) {
+    const int n = e + (int)threadIdx.x;
+    double val = tile[n];
+    if (L::kRep == 2) val += tile[kNodes + n];
+    if (val != 0.0) atomic_add(q0 + (int64_t)(n / L::kC) * g.ld + n % L::kC, (T)val);
+  }
+}
+
+template <class T, bool kSparse>
 __global__ void __launch_bounds__(kChargeBlock) charge_kernel(Grid g, ParticleArraysT<T> P, T* __restrict__ Q) {
-  constexpr int kPlane = kChargeTI * kChargeTJ;
-  __shared__ double tile[kChargeRep][kPlane];
+  __shared__ double tile[kChargeNodes];
   const int tid = (int)threadIdx.x;
   const ParticleArraysT<T> B = from_slot(P, (int64_t)blockIdx.x * (kChargeBlock * kChargeChunks));
-  for (int e = tid; e < kChargeRep * kPlane; e += kChargeBlock) (&tile[0][0])[e] = 0.0;
+  for (int e = tid; e < kChargeNodes; e += kChargeBlock) tile[e] = 0.0;
   // every chunk's loads first: a slot's state is a few registers
-  struct Slot {
-    bool act;
-    int i1, i2;
-    T dx1, dx2, w;
-    uint8_t t;
-  } sl[kChargeChunks];
+  bool act[kChargeChunks];
+  int i1[kChargeChunks] = {}, i2[kChargeChunks] = {};
+  T dx1[kChargeChunks] = {}, dx2[kChargeChunks] = {}, w[kChargeChunks] = {};
+  uint8_t t[kChargeChunks] = {};
 #pragma unroll
   for (int c = 0; c < kChargeChunks; ++c) {
     const uint32_t k = (uint32_t)(c * kChargeBlock + tid);
-    Slot& s = sl[c];
-    s = Slot{false, 0, 0, (T)0, (T)0, (T)0, 0};
     if ((int64_t)k < B.n) {
-      s.t = elem(B.tag, k);
-      s.i1 = elem(B.i1, k);
-      s.i2 = elem(B.i2, k);
-      s.dx1 = elem(B.dx1, k);
-      s.dx2 = elem(B.dx2, k);
-      s.w = elem(B.w, k);
+      t[c] = elem(B.tag, k);
+      i1[c] = elem(B.i1, k);
+      i2[c] = elem(B.i2, k);
+      dx1[c] = elem(B.dx1, k);
+      dx2[c] = elem(B.dx2, k);
+      w[c] = elem(B.w, k);
     }
   }
 #pragma unroll
-  for (int c = 0; c < kChargeChunks; ++c) {
-    Slot& s = sl[c];
-    s.act = is_live(s.t) && species_sign(s.t) != 0.0 && in_deposit_range(g, s.i1, s.dx1, s.i2, s.dx2);
-  }
-  // the anchor: the first chunk from the middle on that has a live particle
-  // (block-uniform votes), else the first of the others
-  int ai = 0, aj = 0, span = 0;
-  bool any = false;
-#pragma unroll
-  for (int c = 0; c < kChargeChunks; ++c) {
-    const Slot& s = sl[(c + kChargeChunks / 2) % kChargeChunks];
-    if (!any) {
-      any = block_anchor(g, s.act, s.i1, s.i2, ai, aj, span);
-      lds_barrier();  // the anchor's LDS cells are read before the next vote writes them
-    }
-  }
-  if (!any) return;
-  const int i0 = ai - (kChargeTI / 2 - 1), j0 = aj - (kChargeTJ / 2 - 1);
+  for (int c = 0; c < kChargeChunks; ++c)
+    act[c] = is_live(t[c]) && species_sign(t[c]) != 0.0 && in_deposit_range(g, i1[c], dx1[c], i2[c], dx2[c]);
+  int ai, aj, span;
+  if (!block_anchor<kChargeChunks>(g, act, i1, i2, ai, aj, span)) return;
+  const int lc = kSparse ? charge_columns(span) : 5;  // (uniform)
   const bool second = (tid & 1) != 0;
 #pragma unroll
   for (int c = 0; c < kChargeChunks; ++c) {
-    const Slot& s = sl[c];
-    if (!s.act) continue;
-    const double q = species_sign(s.t) * g.charge_scale * s.w, w1 = s.dx1, w2 = s.dx2;
-    const double e0 = (s.i2 == 0) ? 2.0 : 1.0, e1 = (s.i2 + 1 == g.n_th) ? 2.0 : 1.0;
+    if (!act[c]) continue;
+    const double q = species_sign(t[c]) * g.charge_scale * w[c], w1 = dx1[c], w2 = dx2[c];
+    const double e0 = (i2[c] == 0) ? 2.0 : 1.0, e1 = (i2[c] + 1 == g.n_th) ? 2.0 : 1.0;
     double v[4] = {q * (1.0 - w1) * (1.0 - w2) * e0, q * (1.0 - w1) * w2 * e1, q * w1 * (1.0 - w2) * e0,
                    q * w1 * w2 * e1};
-    const bool pair = (pair_swap(s.i1, INT_MIN) == s.i1) & (pair_swap(s.i2, INT_MIN) == s.i2);
+    const int o1 = pair_swap(i1[c], INT_MIN), o2 = pair_swap(i2[c], INT_MIN);
+    const bool pair = (o1 == i1[c]) & (o2 == i2[c]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const double sum = v[e] + pair_swap(v[e]);
       v[e] = pair ? sum : v[e];
     }
     if (pair & second) continue;
-    const int row = s.i1 - i0, col = s.i2 - j0;
-    if ((unsigned)row < (unsigned)(kChargeTI - 1) && (unsigned)col < (unsigned)(kChargeTJ - 1)) {
-      double* p = &tile[(tid >> 1) % kChargeRep][row * kChargeTJ + col];
-      atomicAdd(p, v[0]);
-      atomicAdd(p + 1, v[1]);
-      atomicAdd(p + kChargeTJ, v[2]);
-      atomicAdd(p + kChargeTJ + 1, v[3]);
-    } else {
-      T* p = Q + ix(g, s.i1, s.i2);
+    const int di = i1[c] - ai, dj = i2[c] - aj;
+    bool in = false;
+    if constexpr (!kSparse) in = charge_add<5>(tile, di, dj, v);
+    else if (lc == 6) in = charge_add<6>(tile, di, dj, v);
+    else if (lc == 7) in = charge_add<7>(tile, di, dj, v);
+    if (!in) {
+      T* p = Q + ix(g, i1[c], i2[c]);
       atomic_add(p, (T)v[0]);
       atomic_add(p + 1, (T)v[1]);
       atomic_add(p + g.ld, (T)v[2]);
       atomic_add(p + g.ld + 1, (T)v[3]);
     }
   }
+  if (lc == 0) return;
   lds_barrier();
-  T* const q0 = Q + ix(g, i0, j0);
-#pragma unroll
-  for (int e = 0; e < kPlane; e += kChargeBlock) {
-    const int n = e + tid;
-    const double val = tile[0][n] + tile[1][n];
-    if (val != 0.0) atomic_add(q0 + (int64_t)(n / kChargeTJ) * g.ld + n % kChargeTJ, (T)val);
-  }
+  if (!kSparse) charge_flush<5>(g, Q, tile, ai, aj);
+  else if (lc == 6) charge_flush<6>(g, Q, tile, ai, aj);
+  else charge_flush<7>(g, Q, tile, ai, aj);
 }
 
 // residual div D - 4 pi rho at nodes i in [n_f + 2, i_hi), j in [0, n_th]:

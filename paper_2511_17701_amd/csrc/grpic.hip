@@ -612,8 +612,9 @@ grpic_status diagnostics_impl(grpic_ctx* c, const grpic_fields* F, const grpic_p
   LAUNCH_CHECK("fill");
   if (P->n > 0) {
     constexpr int64_t kSlots = kChargeBlock * kChargeChunks;
-    hipLaunchKernelGGL(charge_kernel<T>, dim3((unsigned)((P->n + kSlots - 1) / kSlots)), dim3(kChargeBlock), 0, s, g,
-                       arrays<T>(P), Q);
+    const dim3 gc((unsigned)((P->n + kSlots - 1) / kSlots));
+    if (is_sparse(g, P->n)) hipLaunchKernelGGL((charge_kernel<T, true>), gc, dim3(kChargeBlock), 0, s, g, arrays<T>(P), Q);
+    else hipLaunchKernelGGL((charge_kernel<T, false>), gc, dim3(kChargeBlock), 0, s, g, arrays<T>(P), Q);
     LAUNCH_CHECK("charge");
   }
   {

@@ -1164,32 +1164,55 @@ __device__ inline void lds_barrier() {
 
 // The cell a block's tile is laid around: that of a live particle in the
 // middle of the block's slots (cell-sorted: near the middle of its cells), the
-// second wavefront's first or else the first one's last.  span: the columns from
-// the block's first live particle to its last (the shorter way where the cells
-// wrap from the end of one theta row to the next).  Every thread of the block
-// (two wavefronts) calls this; false if the block has no live particle.  It
+// first of their second half or else the last of the first.  span: the columns
+// from the block's first live particle to its last (the shorter way where the
+// cells wrap from the end of one theta row to the next).  The slots are kChunks
+// chunks of two wavefronts; ia, ja: the cells of a thread's particles.  Every
+// thread of the block calls this; false if the block has no live particle.  It
 // passes a block barrier.
-__device__ inline bool block_anchor(const Grid& g, bool act, int ia, int ja, int& ai, int& aj, int& span) {
-  __shared__ int4 cell[2];  // row (INT_MIN: no live particle) and column of a wavefront's particle next to the
-                            // block's middle, column of that at its end of the block
-  const unsigned long long live = __ballot(act);
+template <int kChunks>
+__device__ inline bool block_anchor(const Grid& g, const bool (&act)[kChunks], const int (&ia)[kChunks],
+                                    const int (&ja)[kChunks], int& ai, int& aj, int& span) {
+  // of each wavefront's 64 slots: row (INT_MIN: none is live) and column of the particle nearest to the
+  // block's middle, column of the one nearest to its ends
+  __shared__ int4 cell[2 * kChunks];
   const int wv = (int)threadIdx.x >> 6;
-  const int first = (__ffsll((long long)live) - 1) & 63, last = (63 - __clzll((long long)live)) & 63;
-  const int mid = wv ? first : last, end = wv ? last : first;
-  const int wi = __builtin_amdgcn_readlane(ia, mid), wj = __builtin_amdgcn_readlane(ja, mid);
-  const int we = __builtin_amdgcn_readlane(ja, end);
-  if ((threadIdx.x & 63) == 0) cell[wv] = int4{live ? wi : INT_MIN, wj, we, 0};
+#pragma unroll
+  for (int c = 0; c < kChunks; ++c) {
+    const unsigned long long live = __ballot(act[c]);
+    const int first = (__ffsll((long long)live) - 1) & 63, last = (63 - __clzll((long long)live)) & 63;
+    const bool second = 2 * c + wv >= kChunks;
+    const int mid = second ? first : last, end = second ? last : first;
+    const int wi = __builtin_amdgcn_readlane(ia[c], mid), wj = __builtin_amdgcn_readlane(ja[c], mid);
+    const int we = __builtin_amdgcn_readlane(ja[c], end);
+    if ((threadIdx.x & 63) == 0) cell[2 * c + wv] = int4{live ? wi : INT_MIN, wj, we, 0};
+  }
   lds_barrier();
-  const int4 c0 = cell[0], c1 = cell[1];
-  const int r0 = __builtin_amdgcn_readfirstlane(c0.x), r1 = __builtin_amdgcn_readfirstlane(c1.x);
-  const int m0 = __builtin_amdgcn_readfirstlane(c0.y), m1 = __builtin_amdgcn_readfirstlane(c1.y);
-  const int e0 = __builtin_amdgcn_readfirstlane(c0.z), e1 = __builtin_amdgcn_readfirstlane(c1.z);
-  const bool s0 = r0 != INT_MIN, s1 = r1 != INT_MIN;
-  ai = s1 ? r1 : r0;
-  aj = s1 ? m1 : m0;
-  const int d = abs((s0 ? e0 : m1) - (s1 ? e1 : m0));
+  int r[2 * kChunks], m[2 * kChunks], x[2 * kChunks];
+#pragma unroll
+  for (int e = 0; e < 2 * kChunks; ++e) {
+    const int4 v = cell[e];
+    r[e] = __builtin_amdgcn_readfirstlane(v.x);
+    m[e] = __builtin_amdgcn_readfirstlane(v.y);
+    x[e] = __builtin_amdgcn_readfirstlane(v.z);
+  }
+  int from = 0, to = 0;
+  ai = INT_MIN;
+  aj = 0;
+#pragma unroll
+  for (int q = 0; q < 2 * kChunks; ++q) {
+    const int up = q, down = 2 * kChunks - 1 - q;
+    if (r[up] != INT_MIN) to = up < kChunks ? m[up] : x[up];
+    if (r[down] != INT_MIN) from = down < kChunks ? x[down] : m[down];
+    const int e = q < kChunks ? q : 3 * kChunks - 1 - q;  // the first half upwards, then the second downwards
+    if (r[e] != INT_MIN) {
+      ai = r[e];
+      aj = m[e];
+    }
+  }
+  const int d = abs(from - to);
   span = min(d, g.n_th - d);
-  return s0 | s1;
+  return ai != INT_MIN;
 }
 
 // Adds a lane's contributions to the tile, its cell (di, dj) from the anchor;
@@ -1277,7 +1300,7 @@ __device__ inline void deposit_block(const Grid& g, const Tables& tab, const Cur
     for (int e = 0; e < 3 * kPlane / 2; e += kBlk) fv[e + (int)threadIdx.x] = double2{};
   }
   int ai, aj, span;
-  if (!block_anchor(g, act, mv.ia, mv.ja, ai, aj, span)) return;  // no live charged particle in this block (uniform)
+  if (!block_anchor<1>(g, {act}, {mv.ia}, {mv.ja}, ai, aj, span)) return;  // no live charged particle (uniform)
   const int lc = kSparse ? tile_columns(span) : 4;  // (uniform)
   double* const t = &tile[0][0];
   if (act) {

@@ -2,8 +2,8 @@
 cell), against the FP64 oracle: cell-sorted sets of 1 to 12 particles per cell
 on both sides of the rule, whose blocks wrap from one theta row to the next or
 reach over both axes and the radial edges, the same sets with some order lost,
-and blocks too wide for any tile.  Fused and separate, double precision to the
-bars of test_gpu_parity.py; single precision against the double-precision
+and blocks too wide for any tile.  The same for the Gauss residual's charge
+pass.  Fused and separate, double precision to the bars of test_gpu_parity.py; single precision against the double-precision
 deposit of the same moves, to 200 roundings of a plane's largest value (a
 node takes that many additions at most)."""
 import numpy as np
@@ -66,3 +66,22 @@ def test_sparse_deposit(O, G, n_r, n_th, ppc, kind):
         scale = ref[c].abs().max().item()
         for name, X in (("fused", A), ("separate", B)):
             assert (X[c].double() - ref[c]).abs().max().item() <= 200 * 2.0 ** -24 * scale, (name, c)
+
+
+@pytest.mark.parametrize("fp32", [False, True])
+@pytest.mark.parametrize("kind", ["sorted", "edges", "moved"])
+@pytest.mark.parametrize("n_r,n_th,ppc", [(12, 800, 0.3), (16, 400, 1), (16, 150, 2), (24, 40, 2), (9, 9, 4), (24, 33, 6),
+                                         (24, 33, 12)])
+def test_sparse_charge(O, G, n_r, n_th, ppc, kind, fp32):
+    w = wl("c1_64").scaled(n_r, n_th)
+    prm, ctx = pair(O, G, w, charge_scale=0.03, precision=G.GRPIC_FP32 if fp32 else G.GRPIC_FP64)
+    F, P = _state(O, prm, w, ppc, kind, 5)
+    F[:3] = 0.0  # (the residual is then the charge)
+    if fp32:  # (the oracle sees the rounded offsets)
+        P = {q: (v.astype(np.float32).astype(np.float64) if v.dtype == np.float64 else v) for q, v in P.items()}
+    res, mx, scale = O.gauss_residual(prm, F, P)
+    Fg = ctx.new_fields()
+    Pg = {q: (v.to(ctx.dtype) if v.is_floating_point() else v) for q, v in up(P).items()}
+    d = ctx.diagnostics(Fg, Pg, w.B0, gauss_plane=True)
+    err = np.abs(d["gauss_res"].double().cpu().numpy() - res).max()
+    assert err <= (200 * 2.0 ** -24 if fp32 else 1e-12) * max(scale, np.abs(res).max())
