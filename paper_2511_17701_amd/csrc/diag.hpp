@@ -55,7 +55,13 @@ diag_particles_kernel(Grid g, Tables tab, ParticleArraysT<T> P, double B0, T* __
       // midpoint within the grid's cells)
       const double f1 = floor(x1), f2 = floor(x2);
       const bool tabled = f1 >= -1.0 && f1 <= (double)g.n_r && f2 >= 0.0 && f2 <= (double)g.n_th;
-      const RSC p = tabled ? rsc_near<SER>(g, tab, (int)f1, x1, (int)f2, x2) : rsc_direct(g, x1, x2);
+      RSC p;
+      if (tabled) {
+        const int j1 = (int)f1, j2 = (int)f2;
+        p = rsc_at<SER>(g, tab, anchor_at<SER>(g, tab, j1, j2, 0.0), j1, x1, x1 - f1, j2, x2, x2 - f2);
+      } else {
+        p = rsc_direct(g, x1, x2);
+      }
       const Coeffs m = coeffs_from(g, p);
       const WaldPot w = wald_pot(g, p.r, p.s, p.c, B0);
       const double qm = species_sign(t);

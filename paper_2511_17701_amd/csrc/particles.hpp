@@ -347,85 +347,6 @@ struct MapNodeT {
 // pi - (pi rounded to double)
 constexpr double kPiLo = 1.2246467991473531772e-16;
 
-// r, sin, cos and the map factors at code position (x1, x2) near cell
-// (i1, i2) (|x - i| <= 1.5) on the logarithmic-r, uniform-theta grid:
-// r = r_i exp((x1 - i1) dxi); the polar angle is first rounded and clamped as
-// theta = clamp(x2 dth), and the result is the sine and cosine of that double:
-// by a series on theta itself next to theta = 0, on psi = pi - theta (exact
-// subtraction plus the low part of pi) next to theta = pi, so that sin keeps
-// its relative precision next to both axes (within the band, angle addition
-// would cancel), and by angle addition from the tables elsewhere.
-// SER = 2: offsets |x - i| dxi, dth <= 0.03 and an axis band of 4 cells (its
-// angles <= 0.03): short series throughout.  SER = 1: offsets <= 0.11 and an
-// axis band of 0.11 rad: long series.  SER = 3: the general map on grids whose
-// offsets are within 0.03 and whose cells 8 from an axis within 0.11 rad: short
-// series, long ones in an axis band of 0.11 rad, theta as rounded by map_theta
-// there.  SER = 0: library functions.
-template <int SER>
-__device__ inline RSC rsc_near(const Grid& g, const Tables& t, int i1, double x1, int i2, double x2) {
-  if (SER == 0) return rsc_direct(g, x1, x2);
-  RSC p;
-  if (SER == 3) {
-    const double e = (elem(t.r[0], (uint32_t)(i1 + g.ng)) - g.r0) * exp_short((x1 - (double)i1) * g.dxi);
-    p.r = g.r0 + e;
-    p.rd = g.dxi * e;
-    double th;
-    map_theta(g, x2, &th, &p.td, &p.dtd);
-    const double it = rcp(p.td);
-    p.itd2 = it * it;
-    if (th <= g.small_angle || th >= g.th_hi) {
-      const bool lo = th <= g.small_angle;
-      p.s = lo ? g.sin_lo : g.sin_hi;
-      p.c = lo ? g.cos_lo : g.cos_hi;
-    } else if (th <= 0.11) {
-      sincos_small(th, &p.s, &p.c);
-    } else if (th >= kPi - 0.11) {
-      double cq;
-      sincos_small((kPi - th) + kPiLo, &p.s, &cq);
-      p.c = -cq;
-    } else {
-      const double c6 = 12.0 * g.h0 * (1.0 / (kPi * kPi)), d = (x2 - (double)i2) * g.dth;
-      const double q0 = elem(t.td[0], (uint32_t)(i2 + g.ng)) * g.inv_dth, q1 = c6 * ((double)i2 * g.dth - 0.5 * kPi);
-      double sp, cp;
-      sincos_short(d * (q0 + d * (q1 + (1.0 / 3.0) * c6 * d)), &sp, &cp);
-      const double sj = elem(t.s[0], (uint32_t)(i2 + g.ng)), cj = elem(t.c[0], (uint32_t)(i2 + g.ng));
-      p.s = fma(sj, cp, cj * sp);
-      p.c = fma(cj, cp, -(sj * sp));
-    }
-    return p;
-  }
-  const double tr = (x1 - (double)i1) * g.dxi;
-  p.r = t.r[0][i1 + g.ng] * (SER == 2 ? exp_short(tr) : exp_small(tr));
-  p.rd = g.dxi * p.r;
-  p.td = g.dth;
-  p.itd2 = g.inv_dth2;
-  p.dtd = 0.0;
-  const double th = x2 * g.dth;
-  const double band = SER == 2 ? g.axis_band : 0.11;
-  if (th <= g.small_angle) {
-    p.s = g.sin_lo;
-    p.c = g.cos_lo;
-  } else if (th >= g.th_hi) {
-    p.s = g.sin_hi;
-    p.c = g.cos_hi;
-  } else if (th <= band) {
-    if (SER == 2) sincos_short(th, &p.s, &p.c); else sincos_small(th, &p.s, &p.c);
-  } else if (th >= (SER == 2 ? g.band_hi : kPi - 0.11)) {
-    double cq;
-    if (SER == 2) sincos_short((kPi - th) + kPiLo, &p.s, &cq);
-    else sincos_small((kPi - th) + kPiLo, &p.s, &cq);
-    p.c = -cq;
-  } else {
-    double sp, cp;
-    if (SER == 2) sincos_short(th - (double)i2 * g.dth, &sp, &cp);
-    else sincos_small(th - (double)i2 * g.dth, &sp, &cp);
-    const double sj = t.s[0][i2 + g.ng], cj = t.c[0][i2 + g.ng];
-    p.s = fma(sj, cp, cj * sp);
-    p.c = fma(cj, cp, -(sj * sp));
-  }
-  return p;
-}
-
 // single-precision series for |x| <= 0.11 (truncation below 1e-9 relative)
 __device__ inline float exp_small_f(float t) {
   float p = fmaf(t, 1.0f / 720.0f, 1.0f / 120.0f);
@@ -508,9 +429,10 @@ __device__ inline RSCT<float> rsc_near_f(const Grid& g, const Tables& t, int i1,
 // the cells at least mid64 / mid32 from both axes (mid) need nothing else, and
 // the iterations of the coordinate update then neither read memory nor branch on
 // the angle.  The form depends on the particle's cell alone, so a result does not
-// depend on the other lanes (a vote of the wavefront for it gave the others the
-// form of the cells next to an axis, which rounds otherwise; it saves nothing on
-// the fused passes and 1.8 % of the separate one at 512^2 with 16 per cell).
+// depend on the other lanes.  In double precision the lanes beside an axis that
+// are outside its band share the table form with those of other cells: a
+// wavefront with both then runs two forms, not three (separate push, 512^2 with 16
+// per cell: 264 -> 242 us).
 template <class T>
 struct AnchorT {
   T r, s, c;       // r - r0; sin, cos
@@ -549,34 +471,67 @@ __device__ inline AnchorT<float> anchor_at(const Grid& g, const Tables& t, int i
 }
 
 // r, sin, cos and the map factors at offsets (f1, f2) from the corner of cell
-// (i1, i2), position (x1, x2): the anchor's form, or rsc_near / rsc_near_f.  (The
-// anchor's takes the polar offset as it is; rsc_near rounds the angle first, as
-// sin needs it beside an axis.)
+// (i1, i2), |f| <= 1.5, position (x1, x2): r = r0 + (r_i - r0) exp(f1 dxi), and the
+// polar angle by angle addition from the table node.  Within an axis band, which
+// only the cells that are not `mid` can reach, that would cancel: there the angle
+// is rounded and clamped as theta = clamp(x2 dth) (or the general map's) first,
+// and the result is the sine and cosine of that double, by a series on theta
+// itself next to theta = 0, on psi = pi - theta (exact subtraction plus the low
+// part of pi) next to theta = pi, so that sin keeps its relative precision.
+// SER = 2: offsets |f| dxi, |f| dth <= 0.03 and a band of 4 cells (its angles <=
+// 0.03): short series throughout.  SER = 1: offsets <= 0.11 and a band of 0.11
+// rad: long series.  SER = 3: the general map on grids whose offsets are within
+// 0.03 and whose cells 8 from an axis within 0.11 rad: short series, long ones
+// in a band of 0.11 rad.  SER = 0: library functions.
 template <int SER>
 __device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<double>& an, int i1, double x1, double f1,
                              int i2, double x2, double f2) {
-  if (SER == 0 || !an.mid) return rsc_near<SER>(g, t, i1, x1, i2, x2);
+  if (SER == 0) return rsc_direct(g, x1, x2);
   RSC p;
   const double tr = f1 * g.dxi;
-  double sp, cp, x = f2 * g.dth;
-  if (SER == 3) {
-    const double c2 = 4.0 * g.h0 * (1.0 / (kPi * kPi)), d = x, w = c2 * d;  // 2 c
-    x = d * (an.q.q0 + d * (an.q.q1 + w));
-    p.td = g.dth * (an.q.q0 + d * (2.0 * an.q.q1 + 3.0 * w));
-    const double it = rcp(p.td);
-    p.itd2 = it * it;
-    p.dtd = g.dth * g.dth * (2.0 * an.q.q1 + 6.0 * w);
-  } else {
-    p.td = g.dth;
-    p.itd2 = g.inv_dth2;
-    p.dtd = 0.0;
-  }
-  if (SER == 1) sincos_small(x, &sp, &cp); else sincos_short(x, &sp, &cp);
   p.r = an.r * (SER == 1 ? exp_small(tr) : exp_short(tr));
   p.rd = g.dxi * p.r;
   if (SER == 3) p.r += g.r0;
-  p.s = fma(an.s, cp, an.c * sp);
-  p.c = fma(an.c, cp, -(an.s * sp));
+  p.td = g.dth;
+  p.itd2 = g.inv_dth2;
+  p.dtd = 0.0;
+  bool table = an.mid;
+  if (!table) {
+    double th;
+    if (SER == 3) map_theta(g, x2, &th, &p.td, &p.dtd);
+    else th = x2 * g.dth;
+    const double lo = SER == 2 ? g.axis_band : 0.11, hi = SER == 2 ? g.band_hi : kPi - 0.11;
+    table = th > lo && th < hi;
+    if (!table) {
+      const bool upper = th >= hi;
+      const double q = upper ? (kPi - th) + kPiLo : th;
+      if (SER == 2) sincos_short(q, &p.s, &p.c); else sincos_small(q, &p.s, &p.c);
+      p.c = upper ? -p.c : p.c;
+      if (th <= g.small_angle) {
+        p.s = g.sin_lo;
+        p.c = g.cos_lo;
+      } else if (th >= g.th_hi) {
+        p.s = g.sin_hi;
+        p.c = g.cos_hi;
+      }
+    }
+  }
+  if (table) {
+    double sp, cp, x = f2 * g.dth;
+    if (SER == 3) {
+      const double c2 = 4.0 * g.h0 * (1.0 / (kPi * kPi)), d = x, w = c2 * d;  // 2 c
+      x = d * (an.q.q0 + d * (an.q.q1 + w));
+      p.td = g.dth * (an.q.q0 + d * (2.0 * an.q.q1 + 3.0 * w));
+      p.dtd = g.dth * g.dth * (2.0 * an.q.q1 + 6.0 * w);
+    }
+    if (SER == 1) sincos_small(x, &sp, &cp); else sincos_short(x, &sp, &cp);
+    p.s = fma(an.s, cp, an.c * sp);
+    p.c = fma(an.c, cp, -(an.s * sp));
+  }
+  if (SER == 3) {
+    const double it = rcp(p.td);
+    p.itd2 = it * it;
+  }
   return p;
 }
 template <int SER>
