@@ -347,6 +347,42 @@ struct MapNodeT {
 // pi - (pi rounded to double)
 constexpr double kPiLo = 1.2246467991473531772e-16;
 
+template <int SER>
+__device__ inline RSC rsc_near(const Grid& g, const Tables& t, int i1, double x1, int i2, double x2) {
+  if (SER == 0) return rsc_direct(g, x1, x2);
+  RSC p;
+  const double tr = (x1 - (double)i1) * g.dxi;
+  p.r = t.r[0][i1 + g.ng] * (SER == 2 ? exp_short(tr) : exp_small(tr));
+  p.rd = g.dxi * p.r;
+  p.td = g.dth;
+  p.itd2 = g.inv_dth2;
+  p.dtd = 0.0;
+  const double th = x2 * g.dth;
+  const double band = SER == 2 ? g.axis_band : 0.11;
+  if (th <= g.small_angle) {
+    p.s = g.sin_lo;
+    p.c = g.cos_lo;
+  } else if (th >= g.th_hi) {
+    p.s = g.sin_hi;
+    p.c = g.cos_hi;
+  } else if (th <= band) {
+    if (SER == 2) sincos_short(th, &p.s, &p.c); else sincos_small(th, &p.s, &p.c);
+  } else if (th >= (SER == 2 ? g.band_hi : kPi - 0.11)) {
+    double cq;
+    if (SER == 2) sincos_short((kPi - th) + kPiLo, &p.s, &cq);
+    else sincos_small((kPi - th) + kPiLo, &p.s, &cq);
+    p.c = -cq;
+  } else {
+    double sp, cp;
+    if (SER == 2) sincos_short(th - (double)i2 * g.dth, &sp, &cp);
+    else sincos_small(th - (double)i2 * g.dth, &sp, &cp);
+    const double sj = t.s[0][i2 + g.ng], cj = t.c[0][i2 + g.ng];
+    p.s = fma(sj, cp, cj * sp);
+    p.c = fma(cj, cp, -(sj * sp));
+  }
+  return p;
+}
+
 // single-precision series for |x| <= 0.11 (truncation below 1e-9 relative)
 __device__ inline float exp_small_f(float t) {
   float p = fmaf(t, 1.0f / 720.0f, 1.0f / 120.0f);
@@ -440,6 +476,9 @@ struct AnchorT {
   bool mid;
 };
 
+// Whether column i2 is at least m cells from both axes.
+__device__ inline bool in_middle(const Grid& g, int m, int i2) { return i2 >= m && i2 < g.n_th - m; }
+
 template <int SER>
 __device__ inline AnchorT<double> anchor_at(const Grid& g, const Tables& t, int i1, int i2, double) {
   AnchorT<double> a;
@@ -453,7 +492,7 @@ __device__ inline AnchorT<double> anchor_at(const Grid& g, const Tables& t, int 
       a.q.q0 = elem(t.td[0], (uint32_t)(i2 + g.ng)) * g.inv_dth;
       a.q.q1 = 12.0 * g.h0 * (1.0 / (kPi * kPi)) * ((double)i2 * g.dth - 0.5 * kPi);
     }
-    a.mid = i2 >= g.mid64 && i2 < g.n_th - g.mid64;
+    a.mid = in_middle(g, g.mid64, i2);
   }
   return a;
 }
@@ -465,9 +504,31 @@ __device__ inline AnchorT<float> anchor_at(const Grid& g, const Tables& t, int i
     a.r = elem(t.rf, (uint32_t)(i1 + g.ng));
     a.s = elem(t.sf, (uint32_t)(i2 + g.ng));
     a.c = elem(t.cf, (uint32_t)(i2 + g.ng));
-    a.mid = i2 >= g.mid32 && i2 < g.n_th - g.mid32;
+    a.mid = in_middle(g, g.mid32, i2);
   }
   return a;
+}
+
+// The same as rsc_at below for the horizon cells of the single-precision push
+// (r0 = 0 where SER > 0), whose kernels have no registers to keep an anchor
+// through the axis form (spilled, a ranked pass takes 10 % longer).
+template <int SER>
+__device__ inline RSC rsc_horizon(const Grid& g, const Tables& t, const AnchorT<double>& an, int i1, double x1, double f1,
+                                  int i2, double x2, double f2) {
+  if (SER == 0 || !an.mid) return rsc_near<SER>(g, t, i1, x1, i2, x2);
+  RSC p;
+  const double tr = f1 * g.dxi;
+  double sp, cp;
+  const double x = f2 * g.dth;
+  p.td = g.dth;
+  p.itd2 = g.inv_dth2;
+  p.dtd = 0.0;
+  if (SER == 1) sincos_small(x, &sp, &cp); else sincos_short(x, &sp, &cp);
+  p.r = an.r * (SER == 1 ? exp_small(tr) : exp_short(tr));
+  p.rd = g.dxi * p.r;
+  p.s = fma(an.s, cp, an.c * sp);
+  p.c = fma(an.c, cp, -(an.s * sp));
+  return p;
 }
 
 // r, sin, cos and the map factors at offsets (f1, f2) from the corner of cell
@@ -488,10 +549,6 @@ __device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<doubl
                              int i2, double x2, double f2) {
   if (SER == 0) return rsc_direct(g, x1, x2);
   RSC p;
-  const double tr = f1 * g.dxi;
-  p.r = an.r * (SER == 1 ? exp_small(tr) : exp_short(tr));
-  p.rd = g.dxi * p.r;
-  if (SER == 3) p.r += g.r0;
   p.td = g.dth;
   p.itd2 = g.inv_dth2;
   p.dtd = 0.0;
@@ -532,6 +589,10 @@ __device__ inline RSC rsc_at(const Grid& g, const Tables& t, const AnchorT<doubl
     const double it = rcp(p.td);
     p.itd2 = it * it;
   }
+  const double tr = f1 * g.dxi;
+  p.r = an.r * (SER == 1 ? exp_small(tr) : exp_short(tr));
+  p.rd = g.dxi * p.r;
+  if (SER == 3) p.r += g.r0;
   return p;
 }
 template <int SER>
@@ -808,7 +869,7 @@ __device__ inline Move<float> push_one_f32(const Grid& g, const Tables& tab, con
     Frame fd;
     Grad dd;
     const AnchorT<double> ad = anchor_at<SER>(g, tab, i1, i2, 0.0);
-    frame_from<is_map(SER)>(g, rsc_at<SER>(g, tab, ad, i1, (double)i1 + dx1, (double)dx1, i2, (double)i2 + dx2, (double)dx2),
+    frame_from<is_map(SER)>(g, rsc_horizon<SER>(g, tab, ad, i1, (double)i1 + dx1, (double)dx1, i2, (double)i2 + dx2, (double)dx2),
                          &fd, &dd);
     f.c = CoeffsT<float>{(float)fd.c.alpha, (float)fd.c.beta1, (float)fd.c.hu11,
                          (float)fd.c.hu22, (float)fd.c.hu33, (float)fd.c.hu13};
