@@ -449,7 +449,7 @@ grpic_status sort_impl(grpic_ctx* c, const grpic_particles* src, const grpic_par
   LAUNCH_CHECK("copy_int");
   bool ordered = false;
   if constexpr (sizeof(T) == 4) {
-    ordered = src->n >= kScatOrdered;
+    ordered = scatter_ordered(src->n, (int64_t)g.n_r * g.n_th);
     if (ordered)
       hipLaunchKernelGGL(sort_scatter_ordered_kernel, dim3((unsigned)((src->n + kScatBlock - 1) / kScatBlock)),
                          dim3(kScatBlock), 0, s, g, a, b, (const int*)w.off);

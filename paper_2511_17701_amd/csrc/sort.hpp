@@ -179,11 +179,16 @@ __global__ void __launch_bounds__(256) sort_scatter_kernel(Grid g, ParticleArray
 constexpr int kScatBlock = 1024, kScatBins = 1024;
 static_assert(kScatBins == kScatBlock, "one thread per slot and per bin");
 
-// From where on a sort takes it: at 256^2 with 16 per cell the direct form takes
-// 72 us and this one 76, at 512^2 219 and 201.  In double precision, where twice
-// the bytes pass LDS, it gains 15 % there and loses 20 % at 1400^2 with 24 per
-// cell (3.64, 4.37 ms), so the direct form stays.
-constexpr int64_t kScatOrdered = int64_t(1) << 21;
+// Where a sort takes it: n^2 / cells >= 2^26.  The gain grows with the slots and
+// with the slots per cell; whole sorts of sets ten steps old, us, direct and
+// this: 2^20 slots 256^2 16 per cell 83, 86; 2^21 256^2 32 118, 106, 512^2 8 122, 133,
+// 1024^2 2 152, 163; 2^22 512^2 16 207, 177, 1024^2 4 235, 250, 2048^2 1 308, 328;
+// 2^23 512^2 32 361, 325, 1024^2 8 380, 369, 2048^2 2 493, 519; 2^24 1024^2 16 691, 628,
+// 2048^2 4 806, 768; 2^26 2048^2 16 2751, 2372.  Sets in order already lose 3 %,
+// and sets in no order 0 to 7 % at 2^22 (beyond that 0 to 60 % less).  In double
+// precision, where twice the bytes pass LDS, it gains 15 % at 512^2 with 16 per
+// cell and loses 20 % at 1400^2 with 24 (3.64, 4.37 ms): the direct form stays.
+inline bool scatter_ordered(int64_t n, int64_t cells) { return (double)n * (double)n >= 0x1p26 * (double)cells; }
 
 template <class V>
 __device__ inline void scatter_array(V* sh, V v, int pos, bool store, uint32_t o, V* D) {
