@@ -1114,10 +1114,9 @@ __device__ inline ContribT<T> make_contrib(const Grid& g, const Tables& tab, con
 }
 
 // Runs of equal keys in consecutive lanes of a wavefront: `end` is the last
-// lane of this lane's run, `head` marks the first lane of a run; `longest` is
-// the longest run (wave-uniform).
+// lane of this lane's run, `head` marks the first lane of a run.
 struct Runs {
-  int end, longest;
+  int end;
   bool head;
 };
 
@@ -1129,16 +1128,6 @@ __device__ inline Runs runs_of(int key) {
   const unsigned long long heads = __ballot(r.head);
   const unsigned long long after = lane == 63 ? 0ull : (heads >> (lane + 1));
   r.end = after ? lane + __ffsll((long long)after) - 1 : 63;
-  // longest gap between consecutive heads (bit 0 is always set)
-  unsigned long long m = heads & ~1ull;
-  int last = 0, best = 0;
-  while (m) {
-    const int b = __ffsll((long long)m) - 1;
-    best = max(best, b - last);
-    last = b;
-    m &= m - 1;
-  }
-  r.longest = max(best, 64 - last);
   return r;
 }
 
@@ -1147,9 +1136,11 @@ __device__ inline Runs runs_of(int key) {
 template <class T>
 __device__ inline T run_sum(T v, const Runs& r) {
   const int lane = threadIdx.x & 63;
-  for (int off = 1; off < r.longest; off <<= 1) {
+  for (int off = 1; off < 64; off <<= 1) {
+    const bool more = lane + off <= r.end;
+    if (!__any(more)) break;  // no run is that long
     const T o = __shfl_down(v, off, 64);
-    if (lane + off <= r.end) v += o;
+    if (more) v += o;
   }
   return v;
 }
