@@ -1460,11 +1460,12 @@ __device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, uint32_t
 constexpr int kPushBlock = 256;
 #define GRPIC_FP64_PUSH_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4)))
 
-// kCycle: the iterations end when two values alternate (n_iter above kCycleIter:
-// up to there the test costs more than the iterations it saves, -4 % on the
-// fused passes at n_iter = 10; frozen-field runs of 1e6 particles at 256^2 with
-// up to 200 iterations and their adjoint take 41.9 ms with it, 46.5 without).
-constexpr int kCycleIter = 16;
+// kCycle: the iterations end when two values alternate, for n_iter above
+// kCycleIter: up to there the test costs more than the iterations it saves.
+// Without / with it, us, 1e6 particles at 256^2 (slots in no order): n_iter = 10 89 /
+// 95, 17 92 / 100, 30 102 / 106, 60 123 / 109, 200 233 / 150; 512^2 with 16 per cell
+// (sorted): 10 228 / 239, 30 247 / 252, 60 278 / 251, 200 435 / 264.
+constexpr int kCycleIter = 32;
 template <int SER, bool kCycle>
 __global__ void __launch_bounds__(kPushBlock) GRPIC_FP64_PUSH_OCCUPANCY
 push_kernel(Grid g, Tables tab, GatherPlanesT<double> fp, ParticleArrays P) {
