@@ -235,9 +235,12 @@ grpic_status grpic_push_deposit_ranked(grpic_ctx* ctx, const grpic_fields* F, co
  * computes per particle
  *   gbar_out = (ds'/ds)^T gbar_in,   gbar_B0 += (ds'/dB0) . gbar_in.
  * The implicit momentum and coordinate stages are differentiated at their
- * fixed points (implicit-function theorem), so the forward pass must run its
- * iterations to convergence (n_iter large enough; they stop at an exact
- * repeat).  gbar_in, gbar_out: device arrays of 5 n doubles, rows x1, x2, u1,
+ * fixed points (implicit-function theorem) where the iteration reaches one
+ * within n_iter: an iterate whose relative change (|n1| + |n2|) is at most
+ * 1e-14, or at most 1e-12 and no longer shrinking.  Elsewhere they are
+ * differentiated through n_iter iterations.  iter_tol is not looked at: a
+ * forward pass that ends early by it has another derivative, by about
+ * iter_tol.  gbar_in, gbar_out: device arrays of 5 n doubles, rows x1, x2, u1,
  * u2, u3 (row c at offset c n); they may be the same array.  gbar_B0: n
  * doubles, accumulated.  Slots that the step does not move (empty, leaving,
  * dropped) pass gbar through unchanged.  P is not modified. */

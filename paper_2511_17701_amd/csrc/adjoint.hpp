@@ -19,9 +19,10 @@
 // Both implicit stages are differentiated at their fixed points (the implicit-
 // function theorem), which an iterate that has stopped changing is taken for
 // (at_fixed: rounding can keep an iteration from an exact repeat for ever).  An
-// iteration that does not come that far within n_iter (next to the axis the contraction can approach 1) is differentiated
-// through the iterations the forward pass ran instead, so the result is always
-// the derivative of the computed map.
+// iteration that does not come that far within n_iter (next to the axis the
+// contraction can approach 1) is differentiated through n_iter iterations
+// instead.  So the result is the derivative of the map of n_iter iterations; a
+// context's iter_tol, which lets the push end earlier, is not looked at.
 // The metric depends on the position alone: its derivatives are two tangents
 // (Tan<2>) of the same code as the push's, with second derivatives from the
 // tangents of its analytic first derivatives.
@@ -34,6 +35,7 @@
 #pragma once
 
 #include "particles.hpp"
+#include "replay.hpp"
 #include "tangent.hpp"
 
 namespace grpic {
@@ -199,8 +201,7 @@ __device__ inline void momentum_map(const Grid& g, const Frame& f, const Grad& d
 }
 
 // Reverse of one evaluation of the momentum force f at (b1, b2, u3): (m1, m2),
-// the bars of f; b1b, b2b, those of b; u3b and the frame's accumulate.  fb
-// (if wanted): fb[i][j] = df_i/db_j.
+// the bars of f; b1b, b2b, those of b; u3b and the frame's accumulate.
 template <bool kMap>
 __device__ inline void force_reverse(const Grid& g, const Frame& f, const Grad& d, const MomentumMap& e, double u3,
                                      double b1, double b2, double m1, double m2, double& b1b, double& b2b, double& u3b,
@@ -444,46 +445,19 @@ __device__ inline void adjoint_one(const Grid& g, const Tables& tab, const Gathe
     u1b = l1 + 0.5 * b1b;
     u2b = l2 + 0.5 * b2b;
   } else {
-    // through the n_iter iterations run, last to first: kKeep iterates are
-    // kept on the way forward, then each segment's from its first one again
-    // (up to kKeep of them; longer segments, n_iter > kKeep^2, repeat)
-    constexpr int kKeep = 16;
-    double keep[kKeep][2], seg[kKeep][2];
-    const int len = (g.n_iter + kKeep - 1) / kKeep;  // iterations per segment
-    double y1 = a1, y2 = a2;
-    for (int it = 0; it < g.n_iter; ++it) {
-      if (it % len == 0) {
-        keep[it / len][0] = y1;
-        keep[it / len][1] = y2;
-      }
-      momentum_map<kMap>(g, f, d, e, y1, y2, y1, y2);
-    }
+    // through the n_iter iterations run, last to first
     double z1b = u1b, z2b = u2b;
     u1b = u2b = 0.0;
-    int have = g.n_iter;  // seg holds the iterates [have, have + kKeep)
-    for (int it = g.n_iter - 1; it >= 0; --it) {
-      if (it < have) {
-        const int first = it / len * len;
-        have = max(first, it - (kKeep - 1));
-        y1 = keep[it / len][0];
-        y2 = keep[it / len][1];
-        for (int q = first; q <= it; ++q) {
-          if (q >= have) {
-            seg[q - have][0] = y1;
-            seg[q - have][1] = y2;
-          }
-          momentum_map<kMap>(g, f, d, e, y1, y2, y1, y2);
-        }
-      }
-      y1 = seg[it - have][0];
-      y2 = seg[it - have][1];
-      double b1b, b2b;
-      force_reverse<kMap>(g, f, d, e, a3, 0.5 * (a1 + y1), 0.5 * (a2 + y2), g.dt * z1b, g.dt * z2b, b1b, b2b, u3b, m);
-      u1b += z1b + 0.5 * b1b;
-      u2b += z2b + 0.5 * b2b;
-      z1b = 0.5 * b1b;
-      z2b = 0.5 * b2b;
-    }
+    reverse_iterates<16>(
+        g.n_iter, a1, a2, [&](double& y1, double& y2) { momentum_map<kMap>(g, f, d, e, y1, y2, y1, y2); },
+        [&](double y1, double y2) {
+          double b1b, b2b;
+          force_reverse<kMap>(g, f, d, e, a3, 0.5 * (a1 + y1), 0.5 * (a2 + y2), g.dt * z1b, g.dt * z2b, b1b, b2b, u3b, m);
+          u1b += z1b + 0.5 * b1b;
+          u2b += z2b + 0.5 * b2b;
+          z1b = 0.5 * b1b;
+          z2b = 0.5 * b2b;
+        });
     u1b += z1b;  // the first iterate starts from Z = s
     u2b += z2b;
   }
