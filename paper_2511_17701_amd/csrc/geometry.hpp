@@ -260,25 +260,22 @@ __host__ __device__ inline RSC rsc_direct(const Grid& g, double x1, double x2) {
 }
 
 // Inverse metric, lapse and shift at a point (R = dr/dx1).
-template <class R>
-__host__ __device__ inline CoeffsT<R> coeffs_from(const Grid& g, RSCT<R> p) {
-  const R r = p.r, s = p.s, c = p.c;
-  // (FP64: a^2 and 2 M from the grid, held in scalar registers; the
-  // single-precision form keeps forming them, which suits its allocation)
-  const R a = (R)g.a, a2 = sizeof(R) == 8 ? (R)g.a2 : a * a, r2 = r * r;
-  const R tMr = (sizeof(R) == 8 ? (R)g.two_M : (R)(2.0 * g.M)) * r;
-  const R Sig = r2 + a2 * c * c;
-  const R S2 = Sig + tMr;
-  const R ra = r2 + a2;
-  const R s2 = s * s;
-  const R A = ra * ra - a2 * (ra - tMr) * s2;
-  const R Rr = p.rd;
+__host__ __device__ inline Coeffs coeffs_from(const Grid& g, RSC p) {
+  const double r = p.r, s = p.s, c = p.c;
+  const double a = g.a, a2 = g.a2, r2 = r * r;
+  const double tMr = g.two_M * r;
+  const double Sig = r2 + a2 * c * c;
+  const double S2 = Sig + tMr;
+  const double ra = r2 + a2;
+  const double s2 = s * s;
+  const double A = ra * ra - a2 * (ra - tMr) * s2;
+  const double Rr = p.rd;
   // one reciprocal for 1/Sigma, 1/S2, 1/sin^2 and 1/R
-  const R q = rcp(Sig * S2 * s2 * Rr);
-  const R iSig = S2 * s2 * Rr * q, iS2 = Sig * s2 * Rr * q;
-  const R is2 = Sig * S2 * Rr * q, iR = Sig * S2 * s2 * q;
-  CoeffsT<R> m;
-  const R y = Sig * iS2;
+  const double q = rcp(Sig * S2 * s2 * Rr);
+  const double iSig = S2 * s2 * Rr * q, iS2 = Sig * s2 * Rr * q;
+  const double is2 = Sig * S2 * Rr * q, iR = Sig * S2 * s2 * q;
+  Coeffs m;
+  const double y = Sig * iS2;
   m.alpha = y * rsqrt(y);
   m.beta1 = tMr * iS2 * iR;
   m.hu11 = A * iSig * iS2 * iR * iR;

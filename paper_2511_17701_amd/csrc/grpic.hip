@@ -305,10 +305,6 @@ grpic_status monopole_impl(grpic_ctx* c, const grpic_fields* F, double B0, hipSt
   return GRPIC_OK;
 }
 
-// the kernels' form for g.ser = 3 (double precision only)
-template <class T>
-constexpr int kMapForm = sizeof(T) == 8 ? 3 : 0;
-
 template <int SER>
 void launch_push(grpic_ctx* c, const GatherPlanesT<double>& gp, const grpic_particles* P, dim3 grid, hipStream_t s) {
   if (c->g.n_iter > kCycleIter)
@@ -403,7 +399,10 @@ void launch_deposit(grpic_ctx* c, const grpic_particles* P, const grpic_fields* 
   constexpr int kBk = kDepBlock;
   const dim3 grid((unsigned)((P->n + kBk - 1) / kBk));
   switch (c->g.ser) {
-    case 3: hipLaunchKernelGGL((deposit_kernel<T, kMapForm<T>, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
+    case 3:  // (double precision only)
+      if constexpr (sizeof(T) == 8)
+        hipLaunchKernelGGL((deposit_kernel<T, 3, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp);
+      break;
     case 2: hipLaunchKernelGGL((deposit_kernel<T, 2, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
     case 1: hipLaunchKernelGGL((deposit_kernel<T, 1, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
     default: hipLaunchKernelGGL((deposit_kernel<T, 0, kSparse>), grid, dim3(kBk), 0, s, c->g, c->tab, arrays<T>(P), cp); break;
@@ -598,7 +597,10 @@ grpic_status diagnostics_impl(grpic_ctx* c, const grpic_fields* F, const grpic_p
   if (P->n > 0) {
     const dim3 gd(std::min(blocks(P->n), (unsigned)kDiagMaxBlocks)), bd(kDiagBlock);
     switch (g.ser) {
-      case 3: hipLaunchKernelGGL((diag_particles_kernel<T, kMapForm<T>>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
+      case 3:  // (double precision only)
+        if constexpr (sizeof(T) == 8)
+          hipLaunchKernelGGL((diag_particles_kernel<T, 3>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc);
+        break;
       case 2: hipLaunchKernelGGL((diag_particles_kernel<T, 2>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
       case 1: hipLaunchKernelGGL((diag_particles_kernel<T, 1>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;
       default: hipLaunchKernelGGL((diag_particles_kernel<T, 0>), gd, bd, 0, s, g, c->tab, arrays<T>(P), B0, (T*)E_out, (T*)L_out, c->acc); break;

@@ -164,7 +164,8 @@ __device__ inline void boris_delta(R ux, R uy, R uz, const R E[3], const R B[3],
 }
 
 // The same Boris step applied to u in place (reciprocal and reciprocal square
-// root as in boris_delta; in double precision two Newton steps, about an ulp).
+// root as in boris_delta; in double precision seeds with one third-order step,
+// about an ulp).
 template <class R>
 __device__ inline void boris(R& ux, R& uy, R& uz, const R E[3], const R B[3], R k /* = qm tau / 2 */) {
   const R mx = ux + k * E[0], my = uy + k * E[1], mz = uz + k * E[2];
@@ -1047,8 +1048,8 @@ struct ContribT {
 // reflects at the axes and deposits one_cell_move only.)
 template <class T>
 __device__ inline bool move_in_range(const Grid& g, const Move<T>& mv) {
-  return in_grid(g, mv.ia, mv.xa, mv.ja, mv.ya) & in_deposit_range(g, mv.ib, mv.xb, mv.jb, mv.yb) &
-         one_cell_move(mv.ia, mv.ja, mv.ib, mv.jb);
+  const bool from = in_grid(g, mv.ia, mv.xa, mv.ja, mv.ya), to = in_deposit_range(g, mv.ib, mv.xb, mv.jb, mv.yb);
+  return from & to & one_cell_move(mv.ia, mv.ja, mv.ib, mv.jb);
 }
 
 template <class T, int SER>
@@ -1452,11 +1453,13 @@ __device__ inline void rank_fused(const Grid& g, int* __restrict__ i1p, uint32_t
 }
 
 // ------------------------------------------------------------------ kernels
-// The FP64 push kernels are held to 128 VGPRs (4 wavefronts per SIMD; no
-// spills on the series paths): on gfx950 the push is latency- and issue-bound,
-// and the fourth wavefront hides more than the compiler's own choice (~160
-// VGPRs, 3 wavefronts, a 10-15 % slower pass); a fifth (96 VGPRs) spills
-// 148 B per lane and runs about 30 % slower.
+// The FP64 push kernels are held to 128 VGPRs (4 wavefronts per SIMD; the
+// series paths of the logarithmic-r, uniform-theta grid do not spill, the general
+// map's ranked pass two registers, the library path of the separate push two to
+// four): on gfx950 the push is latency- and issue-bound, and the fourth wavefront
+// hides more than the compiler's own choice (~160 VGPRs, 3 wavefronts, a 10-15 %
+// slower pass); a fifth (96 VGPRs) spills 148 B per lane and runs about 30 %
+// slower.
 constexpr int kPushBlock = 256;
 #define GRPIC_FP64_PUSH_OCCUPANCY __attribute__((amdgpu_waves_per_eu(4)))
 
@@ -1533,9 +1536,8 @@ __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(
   push_deposit_f32<SER, kRank, kSparse>(g, tab, fp, P, cp, counts);
 }
 
-// library path (coarse grids and the general quasi-spherical map): held to 5
-// wavefronts per SIMD (a few spilled registers), 11 % faster than the 4 that
-// its 100 VGPRs would give
+// library path (coarse grids and the general quasi-spherical map): at least 5
+// wavefronts per SIMD (80 VGPRs and 6 without the rank pass, 81 and 5 with it)
 template <bool kRank, bool kSparse>
 __global__ void __launch_bounds__(kDepBlock) __attribute__((amdgpu_waves_per_eu(5)))
 push_deposit_kernel_f32_lib(Grid g, Tables tab, GatherPlanesT<float> fp, ParticleArraysT<float> P,

@@ -2,8 +2,8 @@
 //
 // Not part of the paper's method: a layout device that keeps particles of one
 // cell adjacent in memory, so that a wavefront streams contiguous SoA data,
-// gathers from a few neighbouring field entries, and the deposit's per-block
-// footprint stays inside its shared-memory tile.  Empty and leaving slots get
+// gathers from a few neighbouring field entries, and a deposit block's cells
+// lie in the shared-memory tile around its middle one.  Empty and leaving slots get
 // the key n_cells: they take no counter and no rank and are not moved; the
 // destination's slots after the live particles get tag 0.
 #pragma once
