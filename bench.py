@@ -347,6 +347,8 @@ def adjoint_leg(grpic, dev):
     ev = [he.create() for _ in range(3)]
     u0 = torch.stack([P["u1"], P["u2"], P["u3"]], 1).clone().requires_grad_(True)
     B0 = torch.tensor(w.B0, dtype=torch.float64, requires_grad=True)
+    FrozenFieldPush.apply(u0, B0, run)[:, 2].mean().backward()  # (the first call pays for its buffers and kernels' code)
+    u0.grad = B0.grad = None
     torch.cuda.synchronize()
     he.record(ev[0])
     out = FrozenFieldPush.apply(u0, B0, run)
