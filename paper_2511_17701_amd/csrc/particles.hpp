@@ -348,6 +348,9 @@ struct MapNodeT {
 // pi - (pi rounded to double)
 constexpr double kPiLo = 1.2246467991473531772e-16;
 
+// r, sin and cos at code position (x1, x2) near cell (i1, i2) on the
+// logarithmic-r, uniform-theta grid, as rsc_at below has them for the cells next
+// to an axis (rsc_horizon; SER = 0: the library functions on any grid).
 template <int SER>
 __device__ inline RSC rsc_near(const Grid& g, const Tables& t, int i1, double x1, int i2, double x2) {
   if (SER == 0) return rsc_direct(g, x1, x2);
